@@ -1,0 +1,502 @@
+"""The work whose time is looked after: what a program does with this package
+through its public entry points, from one short signal to a large image and a
+training step, with float64 values to hold the results against.
+
+``listed()`` names the cases, ``draw(rng)`` gives another one of the same
+ranges, ``prepare(case, seed)`` makes what a program has in hand before the
+call (the operator and, from the seed, the signals), ``run(state)`` is one pass
+and ``exact(case, seed)`` the same outputs in float64 by plain torch.
+
+A pass of the evaluation kinds is one application of the normal operator
+(y = H u, x = H^* y: the body of every least-squares or gradient iteration).
+A pass of the training kinds is a gradient step on the spectra of the impulse
+responses: forward, both gradients of 0.5 ||H u - f||^2, update of the spectra.
+"""
+import functools
+import math
+
+import numpy as np
+import torch
+
+import paper_1604_04374_amd as pc
+from paper_1604_04374_amd.autograd import ExpansionOperator
+
+# 4-tap Daubechies lowpass filter (two vanishing moments), as float32 values
+DB2 = (np.array([1 + 3 ** 0.5, 3 + 3 ** 0.5, 3 - 3 ** 0.5, 1 - 3 ** 0.5]) / (4 * 2 ** 0.5)).astype(np.float32)
+HAAR = (np.array([1.0, 1.0]) / 2 ** 0.5).astype(np.float32)
+LENGTHS = sorted([64 << a for a in range(8)] + [96 << a for a in range(7)])         # 64 ... 8192
+LONG = [12288, 16384, 24576, 32768, 49152, 65536, 98304, 131072]
+UNEVEN_SIDES = (128, 192, 256, 384, 512)
+
+
+def listed():
+    return [
+        # one short signal, one operator: a control loop or a single trace; all latency
+        dict(name="signal_1024", kind="signals", n=1024, batch=1, m=8, degree=1, lo=0.01, hi=0.03, pconv=False),
+        # a handful of traces of an odd count at a length with a factor 3, m not a power of two
+        dict(name="signals_37x3072", kind="signals", n=3072, batch=37, m=12, degree=3, lo=0.004, hi=0.012, pconv=True),
+        # the 1D batch configuration: 64 long signals, 32 cubic windows
+        dict(name="signals_64x65536", kind="signals", n=65536, batch=64, m=32, degree=3, lo=0.002, hi=0.012,
+             pconv=False),
+        # identification of a time-varying filter from a few long recordings
+        dict(name="train_signals_5x24576", kind="train_signals", n=24576, batch=5, m=9, degree=3, lo=0.002, hi=0.008),
+        # a few small frames with few terms: video at low resolution, patches
+        dict(name="frames_3x192x384", kind="images", n1=192, n2=384, g1=2, g2=3, windows="hat", lo=1.0, hi=4.0,
+             batch=3, pconv=False, full_grid=False),
+        # the single-image configuration with overlapping windows (full grid)
+        dict(name="image_1024_hats", kind="images", n1=1024, n2=1024, g1=4, g2=4, windows="hat", lo=1.0, hi=4.0,
+             batch=1, pconv=False, full_grid=False),
+        # many operators of uneven sizes run together, one graph launch per direction
+        dict(name="uneven_256", kind="uneven", count=256, draw=4),
+        # the large image with compact windows (sections): the headline configuration
+        dict(name="image_2048_tiles", kind="images", n1=2048, n2=2048, g1=8, g2=8, windows="tile", lo=1.0, hi=4.0,
+             batch=1, pconv=False, full_grid=False),
+        # learning that operator's responses: the training step over its sections
+        dict(name="train_image_2048_tiles", kind="train_images", n1=2048, n2=2048, g1=8, g2=8, windows="tile",
+             lo=1.25, hi=5.0, batch=1),
+        # learning responses under overlapping windows, a small batch of images (full grid)
+        dict(name="train_images_2x384x512", kind="train_images", n1=384, n2=512, g1=3, g2=3, windows="hat",
+             lo=1.0, hi=4.0, batch=2),
+        # making an operator from a measured time-varying response: L2 projection on the windows
+        dict(name="project_65536", kind="project", n=65536, m=32, degree=3, lo=0.002, hi=0.012),
+        # wavelet coefficients of an operator's matrix (both axes), and back
+        dict(name="coefficients_2048", kind="coefficients", n1=2048, n2=2048, levels=7, taps=4),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["signals", "signals", "signals", "images", "images", "images", "train_signals",
+                       "train_images", "uneven", "project", "coefficients"])
+    lo = rng.uniform(0.002, 0.01)
+    if kind in ("signals", "train_signals"):
+        train = kind == "train_signals"
+        n = rng.choice(LENGTHS[4:] + LONG)
+        degree = rng.choice([1, 3])
+        m = rng.randint(degree + 2, 16 if train else 32)
+        batch = _log_int(rng, 1, 64)
+        while batch > 1 and batch * n * m > (1 << 25 if train else 1 << 27):
+            batch = (batch + 1) // 2
+        c = dict(kind=kind, n=n, batch=batch, m=m, degree=degree, lo=lo, hi=lo * rng.uniform(1.5, 3.0))
+        return c if train else dict(c, pconv=rng.random() < 0.25)
+    if kind in ("images", "train_images"):
+        train = kind == "train_images"
+        lo2 = rng.uniform(0.8, 1.5)
+        c = dict(kind=kind, windows=rng.choice(["hat", "hat", "tile"]), lo=lo2, hi=lo2 * rng.uniform(2.0, 4.0))
+        if c["windows"] == "hat":
+            c.update(n1=rng.choice(LENGTHS[:10]), n2=rng.choice(LENGTHS[:10]), g1=rng.randint(2, 4), g2=rng.randint(2, 4))
+        else:
+            c.update(n1=rng.choice(LENGTHS[4:11]), n2=rng.choice(LENGTHS[4:11]), g1=rng.choice([2, 4, 8]),
+                     g2=rng.choice([2, 4, 8]))
+        terms = c["g1"] * c["g2"]
+        batch = _log_int(rng, 1, 8)
+        while batch > 1 and batch * c["n1"] * c["n2"] * terms > (1 << 24 if train else 1 << 26):
+            batch = (batch + 1) // 2
+        c["batch"] = batch
+        return c if train else dict(c, pconv=rng.random() < 0.25, full_grid=rng.random() < 0.2)
+    if kind == "uneven":
+        return dict(kind=kind, count=rng.randint(9, 160), draw=rng.randrange(1 << 20))
+    if kind == "project":
+        n = rng.choice([4096, 6144, 8192, 16384, 32768])
+        return dict(kind=kind, n=n, m=rng.randint(8, 32), degree=rng.choice([1, 3]), lo=lo, hi=2.0 * lo)
+    return dict(kind=kind, n1=rng.choice(LENGTHS[4:11]), n2=rng.choice(LENGTHS[4:11]), levels=rng.randint(3, 6),
+                taps=rng.choice([2, 4]))
+
+
+# ---------------------------------------------------------------------------
+# operators (host arrays, the same for every seed)
+# ---------------------------------------------------------------------------
+
+def _gauss(x, s):
+    return np.exp(-x * x / (2.0 * s * s)) / (math.sqrt(2.0 * math.pi) * s)
+
+
+def _lags(n):
+    return (((np.arange(n) + n // 2) % n) - n // 2).astype(np.float64)
+
+
+def _bspline(n, m, degree):
+    """B-spline windows of degree 1 or 3 centred at k/m on the circle (m x n)."""
+    d = np.arange(n)[None, :] / n - np.arange(m)[:, None] / m
+    t = np.abs((d - np.floor(d + 0.5)) * m)
+    if degree == 1:
+        w = np.maximum(1.0 - t, 0.0)
+    else:
+        w = np.where(t < 1.0, 2.0 / 3.0 - t * t + 0.5 * t ** 3, np.where(t < 2.0, (2.0 - t) ** 3 / 6.0, 0.0))
+    return w.astype(np.float32)
+
+
+def _tiles(n, m):
+    w = np.zeros((m, n), np.float32)
+    for k in range(m):
+        w[k, (k * n) // m:((k + 1) * n) // m] = 1.0
+    return w
+
+
+def _width(c, y):
+    return c["lo"] + (c["hi"] - c["lo"]) * np.sin(math.pi * np.asarray(y, np.float64)) ** 2
+
+
+@functools.lru_cache(maxsize=1)
+def _operator1(n, m, degree, lo, hi):
+    w = _bspline(n, m, degree)
+    lam = _lags(n) / n
+    s = _width(dict(lo=lo, hi=hi), np.arange(m) / m)
+    h = (np.stack([_gauss(lam, sk) for sk in s]) / n).astype(np.float32)
+    return w, h
+
+
+@functools.lru_cache(maxsize=1)
+def _operator2(n1, n2, g1, g2, windows, lo, hi):
+    """Window factors and anisotropic Gaussian responses (widths in pixels
+    growing from lo to hi across the image) at the window centres."""
+    make = _tiles if windows == "tile" else (lambda n, m: _bspline(n, m, 1))
+    shift = 0.5 if windows == "tile" else 0.0
+    h = np.zeros((g1 * g2, n1, n2), np.float32)
+    for k1 in range(g1):
+        gy = _gauss(_lags(n1), lo + (hi - lo) * (k1 + shift) / g1)
+        r = np.flatnonzero(gy)
+        for k2 in range(g2):
+            gx = _gauss(_lags(n2), lo + (hi - lo) * (k2 + shift) / g2)
+            q = np.flatnonzero(gx)
+            h[k1 * g2 + k2][np.ix_(r, q)] = gy[r][:, None] * gx[q][None, :]
+    return make(n1, g1), make(n2, g2), h
+
+
+@functools.lru_cache(maxsize=1)
+def _uneven(count, seed):
+    rng = np.random.default_rng(seed)
+    out = []
+    for _ in range(count):
+        n1, n2 = int(rng.choice(UNEVEN_SIDES)), int(rng.choice(UNEVEN_SIDES))
+        g = int(rng.integers(2, 5))
+        out.append((n1, n2) + _operator2.__wrapped__(n1, n2, g, g, "hat", float(rng.uniform(1.0, 2.0)),
+                                                     float(rng.uniform(2.0, 4.0))))
+    return out
+
+
+def _op1(c):
+    return _operator1(c["n"], c["m"], c["degree"], c["lo"], c["hi"])
+
+
+def _op2(c):
+    return _operator2(c["n1"], c["n2"], c["g1"], c["g2"], c["windows"], c["lo"], c["hi"])
+
+
+# ---------------------------------------------------------------------------
+# inputs
+# ---------------------------------------------------------------------------
+
+def _gen(seed):
+    return torch.Generator(device="cuda").manual_seed(int(seed))
+
+
+def _signal(c, g, normal):
+    shape = (c["batch"], c["n"]) if "n" in c else (c["batch"], c["n1"], c["n2"])
+    f = torch.randn if normal else torch.rand
+    return f(shape, generator=g, device="cuda")
+
+
+def _band(c, seed):
+    """TVIR rows T(lam, .) at every lag within 15 widths (beyond, the float32
+    values are zero), each position's response scaled by a seeded factor."""
+    n = c["n"]
+    width = torch.from_numpy(_width(c, np.arange(n) / n)).cuda()
+    cut = min(int(math.ceil(15.0 * c["hi"] * n)), n // 2 - 1)
+    lags = np.concatenate([np.arange(cut + 1), np.arange(n - cut, n)]).astype(np.int64)
+    lam = torch.from_numpy(_lags(n)[lags] / n).cuda()
+    gain = 0.5 + torch.rand(n, generator=_gen(seed), device="cuda", dtype=torch.float64)
+    t = torch.empty((lags.shape[0], n), device="cuda")
+    for i in range(0, lags.shape[0], 1024):
+        t[i:i + 1024] = torch.exp(-0.5 * (lam[i:i + 1024, None] / width) ** 2) * (gain / (math.sqrt(2 * math.pi) * width))
+    return t, lags
+
+
+def _matrix(c, seed):
+    """A seeded operator matrix (rows: lags, columns: positions)."""
+    n1, n2 = c["n1"], c["n2"]
+    g = _gen(seed)
+    lam = torch.from_numpy(_lags(n1) / n1).cuda()[:, None]
+    y = torch.arange(n2, device="cuda", dtype=torch.float64)[None, :] / n2
+    s = 0.02 + 0.05 * torch.rand(1, generator=g, device="cuda", dtype=torch.float64) * torch.sin(math.pi * y) ** 2
+    t = torch.exp(-0.5 * (lam / s) ** 2) / (math.sqrt(2 * math.pi) * s)
+    return (t + 0.01 * torch.randn((n1, n2), generator=g, device="cuda", dtype=torch.float64)).float()
+
+
+STEP = {"train_signals": 1e-3, "train_images": 1e-6}
+
+
+def prepare(case, seed):
+    kind, c = case["kind"], case
+    g = _gen(seed)
+    if kind == "signals":
+        w, h = _op1(c)
+        return dict(kind=kind, plan=pc.Plan(w, h, batch=c["batch"], product_convolution=c["pconv"]),
+                    u=_signal(c, g, True))
+    if kind == "images":
+        a, b, h = _op2(c)
+        return dict(kind=kind, plan=pc.Plan((a, b), h, batch=c["batch"], product_convolution=c["pconv"],
+                                            full_grid=c["full_grid"]), u=_signal(c, g, False))
+    if kind in ("train_signals", "train_images"):
+        if kind == "train_signals":
+            w, h = _op1(c)
+        else:
+            a, b, h = _op2(c)
+            w = (a, b)
+        # zero-mean, as a training program centres its data
+        u = _signal(c, g, True).requires_grad_(True)
+        f = _signal(c, g, True)
+        return dict(kind=kind, op=ExpansionOperator(w, h, batch=c["batch"]), u=u, f=f)
+    if kind == "uneven":
+        ops = _uneven(c["count"], c["draw"])
+        plans = [pc.Plan((a, b), h, full_grid=True) for _, _, a, b, h in ops]
+        sizes = [n1 * n2 for n1, n2, *_ in ops]
+        flat = [torch.rand(sum(sizes), generator=g, device="cuda")] + [torch.empty(sum(sizes), device="cuda")
+                                                                      for _ in range(2)]
+        views = [[v.view(o[0], o[1]) for v, o in zip(t.split(sizes), ops)] for t in flat]
+        return dict(kind=kind, batch=pc.Batch(plans), flat=flat, views=views)
+    if kind == "project":
+        t, lags = _band(c, seed)
+        return dict(kind=kind, t=t, lags=lags, w=torch.from_numpy(_bspline(c["n"], c["m"], c["degree"])).cuda())
+    return dict(kind=kind, t=_matrix(c, seed), lp=DB2 if c["taps"] == 4 else HAAR, levels=c["levels"])
+
+
+def run(state):
+    kind = state["kind"]
+    if kind in ("signals", "images"):
+        y = state["plan"].apply(state["u"])
+        return y, state["plan"].apply_adjoint(y)
+    if kind in ("train_signals", "train_images"):
+        op, u = state["op"], state["u"]
+        y = op(u)
+        gu, gs = torch.autograd.grad(y, (u, op.spec), y.detach() - state["f"])
+        with torch.no_grad():
+            op.spec.sub_(gs, alpha=STEP[kind])
+        return y.detach(), gu, gs, op.spec.detach()
+    if kind == "uneven":
+        u, y, x = state["views"]
+        state["batch"].apply(u, outputs=y)
+        state["batch"].apply_adjoint(y, outputs=x)
+        return state["flat"][1], state["flat"][2]
+    if kind == "project":
+        return pc.construct_project(state["t"], state["lags"], state["w"])
+    t, lp, levels = state["t"], state["lp"], state["levels"]
+    coef = pc.wavelet_transform(pc.wavelet_transform(t, lp, levels, axis=1), lp, levels, axis=0)
+    back = pc.wavelet_transform(pc.wavelet_transform(coef, lp, levels, inverse=True, axis=0), lp, levels,
+                                inverse=True, axis=1)
+    return coef, back
+
+
+# ---------------------------------------------------------------------------
+# the work of a pass: nominal transforms (2.5 n log2 n operations for a real
+# one), and every signal, spectrum and nonzero window sample once per direction
+# ---------------------------------------------------------------------------
+
+def _sections(c):
+    """The sections of a tiled operator, or None where it is evaluated on the
+    full grid: per term (window origin, extent, first lag, lag extent, grid)
+    per axis; the grid is the shortest supported length that holds the linear
+    convolution."""
+    if c.get("full_grid") or c["windows"] != "tile":
+        return None
+    axes = []
+    terms = []
+    a, b, h = _op2(c)
+    for w, n in ((a, c["n1"]), (b, c["n2"])):
+        axes.append([(int(np.flatnonzero(r)[0]), int(np.count_nonzero(r)), n) for r in w])
+    for k1, (o1, p1, n1) in enumerate(axes[0]):
+        for k2, (o2, p2, n2) in enumerate(axes[1]):
+            hk = h[k1 * c["g2"] + k2]
+            # Gaussian responses are nonzero on an interval around lag zero
+            q1 = int(np.count_nonzero(hk[:, 0]))
+            q2 = int(np.count_nonzero(hk[0]))
+            sec = []
+            for o, p, q, n in ((o1, p1, q1, n1), (o2, p2, q2, n2)):
+                grid = next((v for v in LENGTHS if v >= min(p + q - 1, n)), n)
+                sec.append((o, p, 0 if q == n else -(q // 2), q, min(grid, n)))
+            terms.append(sec)
+    return terms
+
+
+def _real_fft(n):
+    return 2.5 * n * math.log2(n)
+
+
+def work(case):
+    c, kind = case, case["kind"]
+    if kind in ("signals", "train_signals"):
+        n, m, b = c["n"], c["m"], c["batch"]
+        spec = 8.0 * m * (n // 2 + 1)
+        nnz = min(n, (c["degree"] + 1) * n // m) * m
+        flops = b * ((m + 1) * _real_fft(n) + spec + nnz)
+        if kind == "signals":
+            return {"bytes": 2 * (8.0 * b * n + spec + 4 * nnz), "flops": 2 * flops}
+        # read u, f, the spectra (both directions), the windows; write y, gu, the gradient, the updated spectra
+        return {"bytes": 16.0 * b * n + 4 * spec + 8.0 * nnz, "flops": 3 * flops}
+    if kind in ("images", "train_images"):
+        n1, n2, b, m = c["n1"], c["n2"], c["batch"], c["g1"] * c["g2"]
+        secs = _sections(c)
+        full = (m + 1) * _real_fft(n1 * n2)
+        if secs and sum(2 * _real_fft(s[0][4] * s[1][4]) for s in secs) < 0.5 * full:
+            grids = [s[0][4] * (s[1][4] // 2 + 1) for s in secs]
+            flops = sum(2 * _real_fft(s[0][4] * s[1][4]) for s in secs)
+        else:
+            grids = [n1 * (n2 // 2 + 1)] * m
+            flops = full
+        nnz = n1 * n2 * (4 if c["windows"] == "hat" else 1)
+        flops = b * (flops + 8.0 * sum(grids) + nnz)
+        spec, win = 8.0 * sum(grids), 4.0 * (c["g1"] * n1 + c["g2"] * n2)
+        if kind == "images":
+            return {"bytes": 2 * (8.0 * b * n1 * n2 + spec + win), "flops": 2 * flops}
+        return {"bytes": 16.0 * b * n1 * n2 + 4 * spec + 2 * win, "flops": 3 * flops}
+    if kind == "uneven":
+        bytes_, flops = 0.0, 0.0
+        for n1, n2, a, b, h in _uneven(c["count"], c["draw"]):
+            m = h.shape[0]
+            bytes_ += 2 * (8.0 * n1 * n2 + 8.0 * m * n1 * (n2 // 2 + 1) + 4.0 * (a.size + b.size))
+            flops += 2 * ((m + 1) * _real_fft(n1 * n2) + 8.0 * m * n1 * (n2 // 2 + 1) + 4 * n1 * n2)
+        return {"bytes": bytes_, "flops": flops}
+    if kind == "project":
+        n, m = c["n"], c["m"]
+        rows = 2 * min(int(math.ceil(15.0 * c["hi"] * n)), n // 2 - 1) + 1
+        return {"bytes": 4.0 * (rows * n + 2 * m * n), "flops": 2.0 * m * n * (rows + m)}
+    n = c["n1"] * c["n2"]
+    # four one-dimensional transforms, each about 2 levels' worth of a full pass of `taps` multiply-adds
+    return {"bytes": 4.0 * n * 3, "flops": 4 * 4.0 * n * c["taps"]}
+
+
+# ---------------------------------------------------------------------------
+# float64 by plain torch
+# ---------------------------------------------------------------------------
+
+def _apply64(u, w, h, adjoint=False):
+    """H u = sum_k h_k * (w_k . u), or its adjoint; w(k), h(k) give term k."""
+    dims = tuple(range(1, u.dim()))
+    s = u.shape[1:]
+    if not adjoint:
+        acc = 0.0
+        for wk, hk in zip(w, h):
+            acc = acc + torch.fft.rfftn(hk) * torch.fft.rfftn(wk * u, dim=dims)
+        return torch.fft.irfftn(acc, s=s, dim=dims)
+    v = torch.fft.rfftn(u, dim=dims)
+    x = torch.zeros_like(u)
+    for wk, hk in zip(w, h):
+        x += wk * torch.fft.irfftn(torch.fft.rfftn(hk).conj() * v, s=s, dim=dims)
+    return x
+
+
+def _flip(h):
+    """h~[l] = h[-l] on the torus."""
+    dims = tuple(range(h.dim()))
+    return torch.roll(torch.flip(h, dims), (1,) * len(dims), dims)
+
+
+class _Terms:
+    """Windows and responses of an operator, one float64 tensor per term."""
+
+    def __init__(self, c, device):
+        self.c, self.device = c, device
+        self.ops = _op1(c) if "n" in c else _op2(c)
+
+    def windows(self):
+        if "n" in self.c:
+            return (torch.from_numpy(r).to(self.device).double() for r in self.ops[0])
+        a, b = (torch.from_numpy(x).to(self.device).double() for x in self.ops[:2])
+        return (x[:, None] * y[None, :] for x in a for y in b)
+
+    def responses(self):
+        return (torch.from_numpy(x).to(self.device).double() for x in self.ops[-1])
+
+
+def _weights(n):
+    w = torch.full((n // 2 + 1,), 2.0, dtype=torch.float64, device="cuda")
+    w[0] = 1.0
+    w[-1] = 1.0  # every supported length is even
+    return w
+
+
+def _train64(c, seed):
+    g = _gen(seed)
+    u, f = _signal(c, g, True).double(), _signal(c, g, True).double()
+    t = _Terms(c, "cuda")
+    y = _apply64(u, t.windows(), t.responses())
+    gy = y - f
+    gu = _apply64(gy, t.windows(), t.responses(), adjoint=True)
+    secs = None if "n" in c else _sections(c)
+    if secs and sum(2 * _real_fft(s[0][4] * s[1][4]) for s in secs) >= 0.5 * (len(secs) + 1) * _real_fft(u[0].numel()):
+        secs = None
+    gs, spec = [], []
+    if secs is None:
+        dims = tuple(range(1, u.dim()))
+        gh = torch.fft.rfftn(gy, dim=dims) * _weights(u.shape[-1]) / u[0].numel()
+        for wk, hk in zip(t.windows(), t.responses()):
+            gs.append((torch.fft.rfftn(wk * u, dim=dims).conj() * gh).sum(0))
+            spec.append(torch.fft.rfftn(hk))
+        gs, spec = torch.stack(gs), torch.stack(spec)
+    else:
+        n1, n2 = c["n1"], c["n2"]
+        for hk, ((o1, p1, a1, q1, m1), (o2, p2, a2, q2, m2)) in zip(t.responses(), secs):
+            def box(x, i, j, e1, e2):
+                r = (i + torch.arange(e1, device="cuda")) % n1
+                s = (j + torch.arange(e2, device="cuda")) % n2
+                out = torch.zeros(x.shape[:-2] + (m1, m2), dtype=torch.float64, device="cuda")
+                out[..., :e1, :e2] = x[..., r[:, None], s[None, :]]
+                return out
+            z = torch.fft.rfft2(box(u, o1, o2, p1, p2))
+            v = torch.fft.rfft2(box(gy, o1 + a1, o2 + a2, min(p1 + q1 - 1, m1), min(p2 + q2 - 1, m2)))
+            gs.append((z.conj() * v).sum(0).mul(_weights(m2) / (m1 * m2)).reshape(-1))
+            spec.append(torch.fft.rfft2(box(hk, a1, a2, q1, q2)).reshape(-1))
+        gs, spec = torch.cat(gs), torch.cat(spec)
+    return y, gu, gs, spec - STEP[c["kind"]] * gs
+
+
+def _dwt64(x, lp, levels):
+    """Periodic DWT over the last axis, coarsest first."""
+    hi = [(-1) ** k * lp[len(lp) - 1 - k] for k in range(len(lp))]
+    details = []
+    for _ in range(levels):
+        rolled = [torch.roll(x, -k, -1)[..., ::2] for k in range(len(lp))]
+        details.append(sum(h * v for h, v in zip(hi, rolled)))
+        x = sum(h * v for h, v in zip(lp, rolled))
+    return torch.cat([x] + details[::-1], -1)
+
+
+def exact(case, seed):
+    c, kind = case, case["kind"]
+    if kind in ("signals", "images"):
+        u = _signal(c, _gen(seed), kind == "signals").double()
+        t = _Terms(c, "cuda")
+        h = (lambda: (_flip(x) for x in t.responses())) if c["pconv"] else t.responses
+        y = _apply64(u, t.windows(), h(), adjoint=c["pconv"])
+        return y, _apply64(y, t.windows(), h(), adjoint=not c["pconv"])
+    if kind in ("train_signals", "train_images"):
+        return _train64(c, seed)
+    if kind == "uneven":
+        # many sizes of a few samples each: quicker on the host
+        ops = _uneven(c["count"], c["draw"])
+        flat = torch.rand(sum(o[0] * o[1] for o in ops), generator=_gen(seed), device="cuda").double().cpu()
+        ys, xs, at = [], [], 0
+        for n1, n2, a, b, h in ops:
+            u = flat[at:at + n1 * n2].view(1, n1, n2)
+            at += n1 * n2
+            a, b = torch.from_numpy(a).double(), torch.from_numpy(b).double()
+            w = (a[:, None, :, None] * b[None, :, None, :]).reshape(-1, n1, n2)
+            H = torch.fft.rfft2(torch.from_numpy(h).double())
+            y = torch.fft.irfft2((H * torch.fft.rfft2(w * u)).sum(0), s=(n1, n2))
+            ys.append(y.reshape(-1))
+            xs.append((w * torch.fft.irfft2(H.conj() * torch.fft.rfft2(y), s=(n1, n2))).sum(0).reshape(-1))
+        return torch.cat(ys), torch.cat(xs)
+    if kind == "project":
+        t, lags = _band(c, seed)
+        w = torch.from_numpy(_bspline(c["n"], c["m"], c["degree"])).cuda().double()
+        rhs = torch.cat([w @ t[i:i + 2048].double().t() for i in range(0, t.shape[0], 2048)], 1)
+        h = torch.zeros((c["m"], c["n"]), dtype=torch.float64, device="cuda")
+        h[:, torch.from_numpy(lags).cuda()] = torch.linalg.solve(w @ w.t(), rhs) / c["n"]
+        return h
+    t = _matrix(c, seed).double()
+    lp = [float(v) for v in (DB2 if c["taps"] == 4 else HAAR)]
+    coef = _dwt64(_dwt64(t, lp, c["levels"]).t(), lp, c["levels"]).t().contiguous()
+    return coef, t  # float32 taps are orthonormal to about 1e-8
