@@ -102,7 +102,7 @@ def draw(rng):
     if kind == "project":
         n = rng.choice([4096, 6144, 8192, 16384, 32768])
         return dict(kind=kind, n=n, m=rng.randint(8, 32), degree=rng.choice([1, 3]), lo=lo, hi=2.0 * lo)
-    return dict(kind=kind, n1=rng.choice(LENGTHS[4:11]), n2=rng.choice(LENGTHS[4:11]), levels=rng.randint(3, 6),
+    return dict(kind=kind, n1=256 << rng.randrange(5), n2=256 << rng.randrange(5), levels=rng.randint(3, 7),
                 taps=rng.choice([2, 4]))
 
 
