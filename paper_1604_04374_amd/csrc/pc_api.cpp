@@ -2519,11 +2519,11 @@ pc_status pc_wavelet_transform(int32_t inverse, int64_t n, int32_t levels, int32
   if (count < 1 || stride < 1 || dist < 1) return fail(PC_ERROR_INVALID_VALUE, "count, stride, dist must be >= 1");
   if (!in || !out || in == out) return fail(PC_ERROR_INVALID_VALUE, "null or identical in/out");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  CallTemps t;
   float *s1 = nullptr, *s2 = nullptr;
-  if ((st = t.alloc(&s1, (size_t)(count * (n / 2 + 1)))) || (st = t.alloc(&s2, (size_t)(count * (n / 2 + 1)))) ||
-      (st = t.commit(s)))
-    return st;
+  const size_t ws = (size_t)pc::wavelet_scratch(n, levels, count, stride, dist);
+  CallTemps t;
+  // (without scratch nothing is shared with other calls: no lock, one wait)
+  if (ws > 0 && ((st = t.alloc(&s1, ws)) || (st = t.alloc(&s2, ws)) || (st = t.commit(s)))) return st;
   hipError_t e = pc::launch_wavelet(inverse != 0, n, levels, f, count, stride, dist, in, out, s1, s2, s);
   if (e != hipSuccess) return fail_hip(e, "pc_wavelet_transform launch");
   e = hipStreamSynchronize(s);

@@ -461,7 +461,9 @@ struct WaveletFilter {
 };
 // `levels` levels of the periodic DWT (synthesis: its inverse) of `count`
 // vectors of n samples, element i of vector b at b * dist + i * stride (in
-// and out alike); s1, s2: scratch of count * n / 2 floats each
+// and out alike); s1, s2: scratch of wavelet_scratch floats each (0 where
+// every level runs in one launch; at most count * n / 2)
+int64_t wavelet_scratch(int64_t n, int levels, int64_t count, int64_t stride, int64_t dist);
 LaunchStatus launch_wavelet(bool synthesis, int64_t n, int levels, const WaveletFilter& f, int64_t count,
                             int64_t stride, int64_t dist, const float* in, float* out, float* s1, float* s2,
                             hipStream_t s);

@@ -49,6 +49,56 @@ def test_transform_columns_and_2d_tvir_coefficients():
     assert rel_l2(C, wv.meyer_coefficients(T32.astype(np.float64), h, levels)) <= TOL
 
 
+@pytest.mark.parametrize("n,count,levels,N,axis", [
+    (2, 3, 1, 2, 1), (4, 1, 2, 4, 0), (16, 300, 4, 1, 1),           # vectors shorter than the filter, one, many per workgroup
+    (2048, 1031, 7, 2, 1), (16384, 3, 9, 3, 1), (32768, 2, 8, 2, 1),  # the longest rows that fit, one launch per level above
+    (64, 7, 6, 3, 0), (2048, 2050, 5, 2, 0), (4096, 37, 12, 5, 0),  # columns: ragged tiles, the longest that fit
+    (8192, 33, 6, 1, 0), (8192, 5, 1, 2, 0), (8192, 3, 2, 4, 0)])   # separate levels before / after the fused ones, and alone
+def test_levels_in_one_launch(n, count, levels, N, axis):
+    """Every split of the levels over launches, both directions.  A level's
+    output is a sum of 2 N products with the filter, whose rows have norm 1:
+    each rounding is at most 2^-24 of the sum of magnitudes, (2 N)^(1/2)
+    times the output's norm, 2 N of them per level."""
+    import torch
+    import paper_1604_04374_amd as pcm
+    h = wv.daubechies(N)
+    tol = levels * (2 * N) ** 1.5 * 2.0 ** -24 + 2.0 ** -24  # and the filter's own rounding to float32
+    x = np.random.default_rng(n + count).standard_normal((count, n)).astype(np.float32)
+    xd = torch.from_numpy(np.ascontiguousarray(x if axis == 1 else x.T)).cuda()
+    h32 = h.astype(np.float32).astype(np.float64)
+    c = pcm.wavelet_transform(xd, h, levels, axis=axis).cpu().numpy()
+    assert rel_l2(c if axis == 1 else c.T, wv.dwt(x.astype(np.float64), h32, levels)) <= tol
+    b = pcm.wavelet_transform(xd, h, levels, axis=axis, inverse=True).cpu().numpy()
+    assert rel_l2(b if axis == 1 else b.T, wv.idwt(x.astype(np.float64), h32, levels)) <= tol
+
+
+@pytest.mark.parametrize("stride,dist", [(3, 200), (1, 1 << 24), (5, 1)])
+def test_fused_levels_on_strided_vectors(stride, dist):
+    """Element strides other than the matrix ones, and a distance beyond 24
+    bits (64-bit offsets): the samples between the vectors stay untouched."""
+    import ctypes
+    import torch
+    import paper_1604_04374_amd as pcm
+    lib = pcm.load_library()
+    n, count, levels = 64, 3 if dist != 1 else 4, 5
+    lp = wv.daubechies(2).astype(np.float32)
+    idx = (np.arange(count)[:, None] * dist + np.arange(n)[None, :] * stride)
+    x = np.random.default_rng(stride).standard_normal((count, n)).astype(np.float32)
+    xi = torch.zeros(int(idx.max()) + 1, device="cuda")
+    xi[torch.from_numpy(idx).cuda()] = torch.from_numpy(x).cuda()
+    for inverse, ref in ((0, wv.dwt), (1, wv.idwt)):
+        out = torch.full_like(xi, 7.0)
+        st = lib.pc_wavelet_transform(inverse, n, levels, 4, lp.ctypes.data_as(ctypes.c_void_p), count, stride, dist,
+                                      ctypes.c_void_p(xi.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0
+        got = out[torch.from_numpy(idx).cuda()].cpu().numpy()
+        assert rel_l2(got, ref(x.astype(np.float64), lp.astype(np.float64), levels)) <= levels * 8 * 2.0 ** -24
+        assert int((out == 7.0).sum()) >= out.numel() - count * n
+        out[torch.from_numpy(idx).cuda()] = 7.0
+        assert bool((out == 7.0).all())
+
+
 def _meyer_problem(n, levels, N, keep, seed):
     h = wv.daubechies(N)
     if n <= 4096:  # the largest coefficients of a TVIR
