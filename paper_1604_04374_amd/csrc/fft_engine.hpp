@@ -430,9 +430,10 @@ struct FftPass {
   // this pass feeds the last one across lanes
   static constexpr bool XLANE = XL && S == sch.n - 2 && Xl<L, P>::tab.ok;
   // this pass's exchange uses the skewed layout (see SKEW_BLOCK)
-  static constexpr bool SKW = !LAST && !XLANE && R == 12 && Ns == 4;
+  // (where its reads cross one block boundary at most: transforms of up to
+  // 64 threads)
+  static constexpr bool SKW = !LAST && !XLANE && R == 12 && Ns == 4 && skew_reads_ok(T, P);
   static_assert(!SKW || L + SKEW * ((L - 1) / SKEW_BLOCK) <= lds_len<L, PW>(), "LDS room for the skewed exchange");
-  static_assert(!SKW || skew_reads_ok(T, P), "a skewed read of t + T e crosses one block boundary at most");
 
   __device__ __forceinline__ static void run(float2 (&v)[P], float2* lds, const float2* __restrict__ tw, int t) {
 #pragma unroll

@@ -7,10 +7,20 @@
 // since the DFT is linear, sum_k F(H_k . U_k) = F(sum_k H_k . U_k), so the
 // forward pass pays m forward transforms and one inverse transform, and the
 // adjoint pass one forward and m inverse transforms.
+#include <algorithm>
+
 #include "fft_engine.hpp"
 #include "pc_internal.hpp"
 
 namespace pc {
+
+// The thread index, opaque to the compiler, for transforms inside a runtime
+// loop: their per-element LDS addresses are recomputed instead of held in
+// registers for the whole loop.
+__device__ __forceinline__ int opaque1d(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 
 #define PC_FOR_EACH_L(X) \
   X(64) X(128) X(256) X(512) X(1024) X(2048) X(4096) X(8192) \
@@ -30,26 +40,6 @@ bool fft_size_supported(int64_t L) {
 // ===========================================================================
 // N <= 8192: one workgroup (or one slice of it) per signal pair
 // ===========================================================================
-
-// Small batches (fewer workgroups than compute units) run split: the NF
-// transform slots of a workgroup share one pair and take its terms in turn,
-// and their spectral sums are added in LDS before the slot-0 result is kept.
-// Sum of the slots' acc into slot 0's acc (every thread calls it).
-template <int L, int P, int NF>
-__device__ __forceinline__ void sum_slots(float2 (&acc)[P], float2* lds, int c, int t) {
-  constexpr int T = L / P;
-  __syncthreads();  // every slot's transforms are done with LDS
-#pragma unroll
-  for (int e = 0; e < P; ++e) lds[c * lds_len<L>() + lpad(t + T * e)] = acc[e];
-  __syncthreads();
-  if (c == 0) {
-    for (int sl = 1; sl < NF; ++sl) {
-#pragma unroll
-      for (int e = 0; e < P; ++e) acc[e] = cadd(acc[e], lds[sl * lds_len<L>() + lpad(t + T * e)]);
-    }
-  }
-  // the next transform's first LDS write follows a barrier of its own
-}
 
 // Plan-time spectra H_k = F^* h_k (full complex, natural order).
 template <int L>
@@ -72,19 +62,19 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_spec1d_f
   }
 }
 
-// y = H_m u for signal pairs.
+// y = H_m u for signal pairs, one pair per transform slot: batches with a
+// pair for every slot of the chip (k_small1d_split takes the others).
 template <int L>
 __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_fwd1d_small(
     const float* __restrict__ u, float* __restrict__ y, int64_t batch, int m, const float* __restrict__ w,
-    const float2* __restrict__ H, const float2* __restrict__ tw, int split) {
+    const float2* __restrict__ H, const float2* __restrict__ tw) {
   constexpr int P = points_per_thread(L), T = L / P, NF = ffts_per_block(L);
   __shared__ float2 lds[NF * lds_len<L>()];
   __shared__ float2 twl[L];
   stage_twiddles<L>(twl, tw);
   const int c = threadIdx.x / T, t = threadIdx.x % T;
-  const int64_t pair = split ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * NF + c;
+  const int64_t pair = (int64_t)blockIdx.x * NF + c;
   const int64_t sa = 2 * pair, sb = sa + 1;
-  const bool keep = !split || c == 0;
   const bool va = sa < batch, vb = sb < batch;
   float ua[P], ub[P];
 #pragma unroll
@@ -97,18 +87,12 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_fwd1d_sm
 #pragma unroll
   for (int e = 0; e < P; ++e) acc[e] = make_float2(0.f, 0.f);
   float2* my = lds + c * lds_len<L>();
-  // every slot makes the same number of transform calls (they hold barriers):
-  // a slot past the last term transforms a valid term with zero weight
-  const int nk = split ? (m + NF - 1) / NF : m;
-  for (int i = 0; i < nk; ++i) {
-    const int kt = split ? c + NF * i : i;
-    const int k = kt < m ? kt : m - 1;
-    const float live = kt < m ? 1.f : 0.f;
+  for (int k = 0; k < m; ++k) {
     float2 v[P];
     const float* wk = w + (int64_t)k * L;
 #pragma unroll
     for (int e = 0; e < P; ++e) {
-      const float ww = live * wk[t + T * e];
+      const float ww = wk[t + T * e];
       v[e] = make_float2(ww * ua[e], ww * ub[e]);
     }
     fft_wg<L, P, false>(v, my, twl, t);
@@ -116,33 +100,28 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_fwd1d_sm
 #pragma unroll
     for (int e = 0; e < P; ++e) acc[e] = cfma(acc[e], Hk[t + T * e], v[e]);
   }
-  if (split && NF > 1) sum_slots<L, P, NF>(acc, lds, c, t);
   fft_wg<L, P, true>(acc, my, twl, t);
   const float sc = 1.0f / (float)L;
-  if (keep) {
 #pragma unroll
-    for (int e = 0; e < P; ++e) {
-      const int n = t + T * e;
-      if (va) y[sa * L + n] = acc[e].x * sc;
-      if (vb) y[sb * L + n] = acc[e].y * sc;
-    }
+  for (int e = 0; e < P; ++e) {
+    const int n = t + T * e;
+    if (va) y[sa * L + n] = acc[e].x * sc;
+    if (vb) y[sb * L + n] = acc[e].y * sc;
   }
 }
 
-// x = H_m^* v for signal pairs.
+// x = H_m^* v for signal pairs, one pair per transform slot.
 template <int L>
 __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_adj1d_small(
     const float* __restrict__ vin, float* __restrict__ x, int64_t batch, int m, const float* __restrict__ w,
-    const float2* __restrict__ H, const float2* __restrict__ tw, int split) {
+    const float2* __restrict__ H, const float2* __restrict__ tw) {
   constexpr int P = points_per_thread(L), T = L / P, NF = ffts_per_block(L);
   __shared__ float2 lds[NF * lds_len<L>()];
   __shared__ float2 twl[L];
   stage_twiddles<L>(twl, tw);
   const int c = threadIdx.x / T, t = threadIdx.x % T;
-  // split: every slot transforms the pair's input, then takes its terms in turn
-  const int64_t pair = split ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * NF + c;
+  const int64_t pair = (int64_t)blockIdx.x * NF + c;
   const int64_t sa = 2 * pair, sb = sa + 1;
-  const bool keep = !split || c == 0;
   const bool va = sa < batch, vb = sb < batch;
   float2 V[P];
 #pragma unroll
@@ -155,11 +134,7 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) __attribute__((
   float2 acc[P];
 #pragma unroll
   for (int e = 0; e < P; ++e) acc[e] = make_float2(0.f, 0.f);
-  const int nk = split ? (m + NF - 1) / NF : m;  // same count in every slot (see the forward)
-  for (int i = 0; i < nk; ++i) {
-    const int kt = split ? c + NF * i : i;
-    const int k = kt < m ? kt : m - 1;
-    const float live = kt < m ? 1.f : 0.f;
+  for (int k = 0; k < m; ++k) {
     const float2* Hk = H + (int64_t)k * L;
     float2 g[P];
 #pragma unroll
@@ -168,21 +143,177 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) __attribute__((
     const float* wk = w + (int64_t)k * L;
 #pragma unroll
     for (int e = 0; e < P; ++e) {
-      const float ww = live * wk[t + T * e];
+      const float ww = wk[t + T * e];
       acc[e].x = fmaf(ww, g[e].x, acc[e].x);
       acc[e].y = fmaf(ww, g[e].y, acc[e].y);
     }
   }
-  if (split && NF > 1) sum_slots<L, P, NF>(acc, lds, c, t);
   const float sc = 1.0f / (float)L;
-  if (keep) {
+#pragma unroll
+  for (int e = 0; e < P; ++e) {
+    const int n = t + T * e;
+    if (va) x[sa * L + n] = acc[e].x * sc;
+    if (vb) x[sb * L + n] = acc[e].y * sc;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Small batches: both directions with a pair's terms spread over the chip.
+// The terms go to G workgroups per pair and, inside one, to its NF transform
+// slots; slot (g, c) takes terms g NF + c, g NF + c + G NF, ...  By linearity
+// every slot ends with its own share of the output samples (forward: its
+// spectral sum transformed back; adjoint: its windowed inverses); the slots'
+// shares are added in LDS, and with G > 1 the workgroups leave theirs in
+// `part`, which k_small1d_sum adds in the order of g.
+//
+// What bounds it is latency: one transform after another.  Hence fewer
+// points per thread than the throughput kernels (more wavefronts per
+// transform), loads of the next term issued before the current transform,
+// and wave-local exchanges where a transform fits a wavefront.  Measured (us
+// per call, forward / adjoint; one workgroup per pair at the throughput
+// kernels' points per thread -> here): 37 signals of 3072 samples, 12 terms,
+// 61.5 / 67.1 -> 13.6 / 13.4; 64 of 8192, 30 terms, 209 / 143 -> 37.5 / 37.6;
+// 1 of 8192, 8 terms, 60.9 / 44.0 -> 16.3 / 16.5.  A last-arriving workgroup
+// that adds the shares instead of a second launch took 46 us where this
+// takes 13.6: every workgroup's device-scope fence writes its XCD's L2 back.
+// ---------------------------------------------------------------------------
+constexpr int split_points(int L) { return L % 3 == 0 ? 12 : L >= 8192 ? 16 : 8; }
+constexpr int split_threads(int L) { return L / split_points(L); }
+// (512 threads up to 1024 points: 8 terms of 1024 points in two rounds of
+// four slots 8.5 us, in four rounds of two 10.0)
+constexpr int split_slots(int L) { return split_threads(L) >= 256 ? 1 : (L <= 1024 ? 512 : 256) / split_threads(L); }
+
+template <int L, bool ADJ>
+__global__ __launch_bounds__(split_slots(L) * split_threads(L)) void k_small1d_split(
+    const float* __restrict__ u, float* __restrict__ y, int64_t batch, int m, const float* __restrict__ w,
+    const float2* __restrict__ H, const float2* __restrict__ tw, int G, float2* __restrict__ part) {
+  constexpr int P = split_points(L), T = L / P, NF = split_slots(L), NT = NF * T;
+  // an exchange region per slot; at the end NF x L sums
+  __shared__ float2 lds[NF * lds_len<L>()];
+  __shared__ float2 twl[L];
+  const int tid = (int)threadIdx.x, c = tid / T, t = tid % T;
+  const int64_t pair = blockIdx.x / G;
+  const int g = (int)(blockIdx.x % G);
+  TwStage<L, NT> ts;
+  ts.load(tw, tid);
+  const float* ua = u + 2 * pair * L;
+  const bool vb = 2 * pair + 1 < batch;
+  const float* ub = vb ? ua + L : ua;  // an odd batch's last pair reads its signal twice, the second zeroed
+  float xa[P], xb[P];
+#pragma unroll
+  for (int e = 0; e < P; ++e) {
+    xa[e] = ua[t + T * e];
+    xb[e] = ub[t + T * e];
+  }
+  // a slot past the last term runs a valid one with zero weight (the
+  // transforms may hold barriers)
+  const int step = G * NF, nk = (m - g * NF + step - 1) / step;  // g NF < m: the same count in every slot
+  auto term = [&](int i) { return g * NF + c + step * i; };
+  float wv[P];
+  float2 hv[P];
+  auto load = [&](int i) {
+    const int k = term(i) < m ? term(i) : m - 1;
+    const float* wk = w + (int64_t)k * L;
+    const float2* Hk = H + (int64_t)k * L;
+#pragma unroll
+    for (int e = 0; e < P; ++e) wv[e] = wk[t + T * e];
+#pragma unroll
+    for (int e = 0; e < P; ++e) hv[e] = Hk[t + T * e];
+  };
+  load(0);
+  float2* my = lds + c * lds_len<L>();
+  ts.commit(twl, tid);
+  if (!vb) {
+#pragma unroll
+    for (int e = 0; e < P; ++e) xb[e] = 0.f;
+  }
+  float2 acc[P], V[ADJ ? P : 1];
+#pragma unroll
+  for (int e = 0; e < P; ++e) acc[e] = make_float2(0.f, 0.f);
+  if constexpr (ADJ) {
+#pragma unroll
+    for (int e = 0; e < P; ++e) V[e] = make_float2(xa[e], xb[e]);
+    fft_wv<L, P, false, SYNC_WAVE>(V, my, twl, t);
+  }
+  for (int i = 0; i < nk; ++i) {
+    const float live = term(i) < m ? 1.f : 0.f;
+    float2 v[P];
+    float wc[P];
+    float2 hc[P];
 #pragma unroll
     for (int e = 0; e < P; ++e) {
-      const int n = t + T * e;
-      if (va) x[sa * L + n] = acc[e].x * sc;
-      if (vb) x[sb * L + n] = acc[e].y * sc;
+      wc[e] = live * wv[e];
+      hc[e] = hv[e];
+    }
+    if (i + 1 < nk) load(i + 1);
+    if constexpr (ADJ) {
+#pragma unroll
+      for (int e = 0; e < P; ++e) v[e] = cmulc(V[e], hc[e]);
+      fft_wv<L, P, true, SYNC_WAVE>(v, my, twl, opaque1d(t));
+#pragma unroll
+      for (int e = 0; e < P; ++e) {
+        acc[e].x = fmaf(wc[e], v[e].x, acc[e].x);
+        acc[e].y = fmaf(wc[e], v[e].y, acc[e].y);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < P; ++e) v[e] = make_float2(wc[e] * xa[e], wc[e] * xb[e]);
+      fft_wv<L, P, false, SYNC_WAVE>(v, my, twl, opaque1d(t));
+#pragma unroll
+      for (int e = 0; e < P; ++e) acc[e] = cfma(acc[e], hc[e], v[e]);
     }
   }
+  if constexpr (!ADJ) fft_wv<L, P, true, SYNC_WAVE>(acc, my, twl, t);
+  const float sc = 1.0f / (float)L;
+  float* ya = y + 2 * pair * L;
+  float* yb = ya + L;
+  if constexpr (NF == 1) {
+    if (G == 1) {
+#pragma unroll
+      for (int e = 0; e < P; ++e) {
+        ya[t + T * e] = acc[e].x * sc;
+        if (vb) yb[t + T * e] = acc[e].y * sc;
+      }
+      return;
+    }
+    float2* mine = part + (pair * G + g) * L;
+#pragma unroll
+    for (int e = 0; e < P; ++e) mine[t + T * e] = acc[e];
+  } else {
+    __syncthreads();  // every slot is done with its exchange region
+#pragma unroll
+    for (int e = 0; e < P; ++e) lds[c * L + t + T * e] = acc[e];
+    __syncthreads();
+    float2* mine = part + (pair * G + g) * L;
+    for (int n = tid; n < L; n += NT) {
+      float2 a = lds[n];
+#pragma unroll
+      for (int q = 1; q < NF; ++q) a = cadd(a, lds[q * L + n]);
+      if (G == 1) {
+        ya[n] = a.x * sc;
+        if (vb) yb[n] = a.y * sc;
+      } else {
+        mine[n] = a;
+      }
+    }
+  }
+}
+
+// y = the sum of a pair's G shares, scaled, in the order of g.
+template <int L>
+__global__ __launch_bounds__(256) void k_small1d_sum(const float2* __restrict__ part, int G, float* __restrict__ y,
+                                                     int64_t batch) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t pair = i / L;
+  const int n = (int)(i % L);
+  if (2 * pair >= batch) return;
+  const float2* s = part + pair * G * L + n;
+  float2 a = s[0];
+#pragma unroll 8
+  for (int g = 1; g < G; ++g) a = cadd(a, s[(int64_t)g * L]);
+  const float sc = 1.0f / (float)L;
+  y[2 * pair * L + n] = a.x * sc;
+  if (2 * pair + 1 < batch) y[(2 * pair + 1) * L + n] = a.y * sc;
 }
 
 template <int L>
@@ -193,33 +324,62 @@ static LaunchStatus spec1d_full_t(const float* h, float2* H, int m, const float2
   return hipGetLastError();
 }
 
-// split the terms over a workgroup's slots when one pair per slot leaves
-// compute units idle
-static inline bool split_small(int64_t pairs, int NF) { return NF > 1 && (pairs + NF - 1) / NF < 256; }
-
+// Workgroups per pair (0: the kernels with a pair per transform slot, which
+// do no work twice and win once they have a workgroup for every compute
+// unit).  One while the terms of a slot are few and short: the second launch
+// costs 2.3 us and a launch on the host (1 signal of 1024 samples, 8 terms,
+// two per slot: 8.5 us, spread 9.7; 12 terms, three per slot: 11.2, spread
+// 9.9).  Else as many as make about one workgroup per compute unit (64
+// signals of 3072 samples, 30 terms: 4, 8, 16 and 30 groups 32, 22.8, 24.2
+// and 29.3 us).
 template <int L>
-static LaunchStatus fwd1d_small_t(const Small1D& p, const float* u, float* y, int64_t batch, hipStream_t s,
-                                  Tracer* tr) {
-  constexpr int NF = ffts_per_block(L), T = fft_threads(L);
-  const int64_t pairs = (batch + 1) / 2;
-  const bool split = split_small(pairs, NF);
-  const int64_t blocks = split ? pairs : (pairs + NF - 1) / NF;
-  TraceScope ts(tr, "fwd1d_small", s);
-  hipLaunchKernelGGL(k_fwd1d_small<L>, dim3((unsigned)blocks), dim3(NF * T), 0, s, u, y, batch, p.m, p.w, p.H,
-                     p.tw, split ? 1 : 0);
-  return hipGetLastError();
+static int split_groups_t(int m, int64_t pairs) {
+  constexpr int NF = ffts_per_block(L), SF = split_slots(L);
+  if ((pairs + NF - 1) / NF >= 256) return 0;
+  const int most = (m + SF - 1) / SF;  // terms per slot of a single workgroup
+  if ((int64_t)most * L <= 2048) return 1;
+  const int g = (int)std::min<int64_t>(most, std::max<int64_t>(1, 256 / pairs));
+  const int per = (most + g - 1) / g;  // terms per slot; the fewest workgroups with that many
+  return (most + per - 1) / per;
 }
 
-template <int L>
-static LaunchStatus adj1d_small_t(const Small1D& p, const float* v, float* x, int64_t batch, hipStream_t s,
-                                  Tracer* tr) {
-  constexpr int NF = ffts_per_block(L), T = fft_threads(L);
+int small1d_groups(int L, int m, int64_t pairs) {
+  switch (L) {
+#define PC_CASE(LL) \
+  case LL:          \
+    return split_groups_t<LL>(m, pairs);
+    PC_FOR_EACH_L(PC_CASE)
+#undef PC_CASE
+  }
+  return 0;
+}
+
+int small1d_split_points(int L) { return split_points(L); }
+
+template <int L, bool ADJ>
+static LaunchStatus small1d_t(const Small1D& p, const float* u, float* y, int64_t batch, hipStream_t s, Tracer* tr) {
   const int64_t pairs = (batch + 1) / 2;
-  const bool split = split_small(pairs, NF);
-  const int64_t blocks = split ? pairs : (pairs + NF - 1) / NF;
-  TraceScope ts(tr, "adj1d_small", s);
-  hipLaunchKernelGGL(k_adj1d_small<L>, dim3((unsigned)blocks), dim3(NF * T), 0, s, v, x, batch, p.m, p.w, p.H,
-                     p.tw, split ? 1 : 0);
+  const int G = split_groups_t<L>(p.m, pairs);
+  if (G > 0) {
+    {
+      TraceScope ts(tr, ADJ ? "adj1d_small" : "fwd1d_small", s);
+      hipLaunchKernelGGL((k_small1d_split<L, ADJ>), dim3((unsigned)(pairs * G)),
+                         dim3(split_slots(L) * split_threads(L)), 0, s, u, y, batch, p.m, p.w, p.H, p.tws, G, p.part);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || G == 1) return e;
+    TraceScope ts(tr, "sum1d_small", s);
+    hipLaunchKernelGGL(k_small1d_sum<L>, dim3((unsigned)((pairs * L + 255) / 256)), dim3(256), 0, s, p.part, G, y,
+                       batch);
+    return hipGetLastError();
+  }
+  TraceScope ts(tr, ADJ ? "adj1d_small" : "fwd1d_small", s);
+  constexpr int NF = ffts_per_block(L), T = fft_threads(L);
+  const dim3 grid((unsigned)((pairs + NF - 1) / NF)), block(NF * T);
+  if constexpr (ADJ)
+    hipLaunchKernelGGL(k_adj1d_small<L>, grid, block, 0, s, u, y, batch, p.m, p.w, p.H, p.tw);
+  else
+    hipLaunchKernelGGL(k_fwd1d_small<L>, grid, block, 0, s, u, y, batch, p.m, p.w, p.H, p.tw);
   return hipGetLastError();
 }
 
@@ -239,7 +399,7 @@ LaunchStatus launch_fwd1d_small(const Small1D& p, const float* u, float* y, int6
   switch (p.L) {
 #define PC_CASE(LL) \
   case LL:          \
-    return fwd1d_small_t<LL>(p, u, y, batch, s, tr);
+    return small1d_t<LL, false>(p, u, y, batch, s, tr);
     PC_FOR_EACH_L(PC_CASE)
 #undef PC_CASE
   }
@@ -251,7 +411,7 @@ LaunchStatus launch_adj1d_small(const Small1D& p, const float* v, float* x, int6
   switch (p.L) {
 #define PC_CASE(LL) \
   case LL:          \
-    return adj1d_small_t<LL>(p, v, x, batch, s, tr);
+    return small1d_t<LL, true>(p, v, x, batch, s, tr);
     PC_FOR_EACH_L(PC_CASE)
 #undef PC_CASE
   }
@@ -843,55 +1003,130 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_fft_pair
   }
 }
 
-// gspec[k][f] for f <= N/2, one term per FFT slot, looping over the pairs.
-template <int L>
-__global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_grad1d_small(
-    const float* __restrict__ u, int64_t batch, int m, const float* __restrict__ w, const float2* __restrict__ Gc,
-    float2* __restrict__ gspec, const float2* __restrict__ tw) {
-  constexpr int P = points_per_thread(L), T = L / P, NF = ffts_per_block(L), NH = L / 2 + 1;
+// Backward of the small sizes.  Slot c of workgroup (kg, pg) owns term
+// k = kg NF + c and takes pairs pg, pg + PG, ...: from one transform of the
+// pair's output gradient, V, it accumulates E_k += conj(F^*(w_k u)) . V over
+// its pairs and, with GU, forms w_k . F(conj(H_k) V), whose sum over the
+// workgroup's slots is the workgroup's share of dL/du.  k_bwd1d_small_sum
+// adds the shares (dL/du over kg, E over pg) and writes both results.  The
+// transform of the gradient is done again by every term group: these sizes
+// are bound by latency, and a launch for it costs more; PRE reads it from Gc
+// (k_fft_pairs_small), for term counts that fill the chip by themselves.
+// Measured (both gradients, us; the pairs one after another in one workgroup
+// per term group and a separate adjoint -> here): 16 signals of 3072 samples,
+// 12 terms, 158 -> 16.5; 64 of 8192, 16 terms, 378 -> 48; 1 of 1024, 8 terms,
+// 20.4 -> 14.6.
+template <int L, bool GU, bool PRE>
+__global__ __launch_bounds__(split_slots(L) * split_threads(L)) void k_bwd1d_small(
+    const float* __restrict__ u, const float* __restrict__ gy, int64_t pairs, int64_t batch, int m,
+    const float* __restrict__ w, const float2* __restrict__ H, const float2* __restrict__ tw, int KG, int PG,
+    const float2* __restrict__ Gc, float2* __restrict__ gu_part, float2* __restrict__ e_part) {
+  constexpr int P = split_points(L), T = L / P, NF = split_slots(L), NT = NF * T;
   __shared__ float2 lds[NF * lds_len<L>()];
   __shared__ float2 twl[L];
-  stage_twiddles<L>(twl, tw);
-  const int c = threadIdx.x / T, t = threadIdx.x % T;
-  const int kraw = blockIdx.x * NF + c;
-  const bool ok = kraw < m;
-  const int k = ok ? kraw : m - 1;
-  float2* my = lds + c * lds_len<L>();
+  const int tid = (int)threadIdx.x, c = tid / T, t = tid % T;
+  const int kg = (int)(blockIdx.x % KG), pg = (int)(blockIdx.x / KG);
+  TwStage<L, NT> ts;
+  ts.load(tw, tid);
+  const int kraw = kg * NF + c, k = kraw < m ? kraw : m - 1;
+  const float live = kraw < m ? 1.f : 0.f;  // a slot past the last term adds nothing to dL/du
   const float* wk = w + (int64_t)k * L;
+  float wv[P];
+  float2 hv[GU ? P : 1];
+#pragma unroll
+  for (int e = 0; e < P; ++e) wv[e] = wk[t + T * e];
+  if constexpr (GU) {
+#pragma unroll
+    for (int e = 0; e < P; ++e) hv[e] = H[(int64_t)k * L + t + T * e];
+  }
   float2 acc[P];
 #pragma unroll
   for (int e = 0; e < P; ++e) acc[e] = make_float2(0.f, 0.f);
-  const int64_t pairs = (batch + 1) / 2;
-  for (int64_t pr = 0; pr < pairs; ++pr) {
-    const int64_t sa = 2 * pr, sb = sa + 1;
-    const bool vb = sb < batch;
-    float2 v[P];
+  float2* my = lds + c * lds_len<L>();
+  ts.commit(twl, tid);
+  for (int64_t pr = pg; pr < pairs; pr += PG) {
+    const bool vb = 2 * pr + 1 < batch;
+    const int64_t o = 2 * pr * L, ob = vb ? L : 0;  // an odd batch's last pair: the signal again, zeroed
+    float2 z[P], V[P];
+#pragma unroll
+    for (int e = 0; e < P; ++e) z[e] = make_float2(u[o + t + T * e], u[o + ob + t + T * e]);
+#pragma unroll
+    for (int e = 0; e < P; ++e)
+      V[e] = PRE ? Gc[pr * L + t + T * e] : make_float2(gy[o + t + T * e], gy[o + ob + t + T * e]);
 #pragma unroll
     for (int e = 0; e < P; ++e) {
-      const int n = t + T * e;
-      const float ww = wk[n];
-      v[e] = make_float2(ww * u[sa * L + n], vb ? ww * u[sb * L + n] : 0.f);
+      z[e] = make_float2(wv[e] * z[e].x, vb ? wv[e] * z[e].y : 0.f);
+      if (!PRE && !vb) V[e].y = 0.f;
     }
-    fft_wg<L, P, false>(v, my, twl, t);
+    if constexpr (!PRE) fft_wv<L, P, false, SYNC_WAVE>(V, my, twl, opaque1d(t));
+    fft_wv<L, P, false, SYNC_WAVE>(z, my, twl, opaque1d(t));
 #pragma unroll
-    for (int e = 0; e < P; ++e) acc[e] = cfma_conj(acc[e], v[e], Gc[pr * L + t + T * e]);
-  }
-  __syncthreads();
+    for (int e = 0; e < P; ++e) acc[e] = cfma_conj(acc[e], z[e], V[e]);
+    if constexpr (GU) {
 #pragma unroll
-  for (int e = 0; e < P; ++e) my[lpad(t + T * e)] = acc[e];
-  __syncthreads();
-  if (ok) {
+      for (int e = 0; e < P; ++e) V[e] = cmulc(V[e], hv[e]);
+      fft_wv<L, P, true, SYNC_WAVE>(V, my, twl, opaque1d(t));
+      float2* mine = gu_part + (pr * KG + kg) * L;
+      if constexpr (NF == 1) {
 #pragma unroll
-    for (int e = 0; e < P; ++e) {
-      const int f = t + T * e;
-      if (f < NH) {
-        const float2 a = my[lpad(f)];
-        const float2 b = my[lpad(f == 0 ? 0 : L - f)];
-        const float sc = 0.5f * half_weight(f, L) / (float)L;
-        gspec[(int64_t)k * NH + f] = make_float2(sc * (a.x + b.x), sc * (a.y - b.y));
+        for (int e = 0; e < P; ++e) mine[t + T * e] = cscale(V[e], wv[e]);
+      } else {
+        __syncthreads();  // every slot is done with its exchange region
+#pragma unroll
+        for (int e = 0; e < P; ++e) lds[c * L + t + T * e] = cscale(V[e], live * wv[e]);
+        __syncthreads();
+        for (int n = tid; n < L; n += NT) {
+          float2 a = lds[n];
+#pragma unroll
+          for (int q = 1; q < NF; ++q) a = cadd(a, lds[q * L + n]);
+          mine[n] = a;
+        }
+        __syncthreads();  // the sums are read before the next pair's exchanges
       }
     }
   }
+  if (kraw < m) {
+    float2* ek = e_part + ((int64_t)k * PG + pg) * L;
+#pragma unroll
+    for (int e = 0; e < P; ++e) ek[t + T * e] = acc[e];
+  }
+}
+
+// The sums of k_bwd1d_small's shares: blocks below gu_blocks write dL/du
+// (scaled, both signals of a pair), the rest the spectra gradient
+// gspec[k][f], f <= N/2, from E[f] and E[-f].
+template <int L>
+__global__ __launch_bounds__(256) void k_bwd1d_small_sum(const float2* __restrict__ gu_part,
+                                                         const float2* __restrict__ e_part, int KG, int PG, int m,
+                                                         int64_t batch, unsigned gu_blocks, float* __restrict__ gu,
+                                                         float2* __restrict__ gspec) {
+  constexpr int NH = L / 2 + 1;
+  const float sc = 1.0f / (float)L;
+  if (blockIdx.x < gu_blocks) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t pair = i / L;
+    const int n = (int)(i % L);
+    if (2 * pair >= batch) return;
+    const float2* s = gu_part + pair * KG * L + n;
+    float2 a = s[0];
+#pragma unroll 8
+    for (int g = 1; g < KG; ++g) a = cadd(a, s[(int64_t)g * L]);
+    gu[2 * pair * L + n] = a.x * sc;
+    if (2 * pair + 1 < batch) gu[(2 * pair + 1) * L + n] = a.y * sc;
+    return;
+  }
+  const int64_t i = (int64_t)(blockIdx.x - gu_blocks) * 256 + threadIdx.x;
+  if (i >= (int64_t)m * NH) return;
+  const int k = (int)(i / NH), f = (int)(i % NH), fm = f == 0 ? 0 : L - f;
+  const float2* e = e_part + (int64_t)k * PG * L;
+  float2 a = e[f], b = e[fm];
+#pragma unroll 4
+  for (int g = 1; g < PG; ++g) {
+    a = cadd(a, e[(int64_t)g * L + f]);
+    b = cadd(b, e[(int64_t)g * L + fm]);
+  }
+  const float s = 0.5f * half_weight(f, L) / (float)L;
+  gspec[i] = make_float2(s * (a.x + b.x), s * (a.y - b.y));
 }
 
 // ---- four-step layout -------------------------------------------------------
@@ -1066,27 +1301,91 @@ LaunchStatus launch_origin_phase1d(const Large1D& p, float2* Hd, hipStream_t s) 
   return hipErrorInvalidValue;
 }
 
+// Term groups (one term per slot) and pair groups (about one workgroup per
+// compute unit) of a small backward; PRE (see the kernel) from 256 term
+// groups on, where the second transform per term and pair would cost
+// throughput.
+struct Bwd1D {
+  int KG, PG;
+  bool pre, gu;  // gu: dL/du fits (shares of at most 64 MB)
+};
 template <int L>
-static LaunchStatus grad1d_small_t(const Small1D& p, const float* u, const float* gy, float2* gspec, int64_t batch,
-                                   float2* work, hipStream_t s) {
-  constexpr int NF = ffts_per_block(L), T = fft_threads(L);
+static Bwd1D bwd1d_t(int m, int64_t pairs) {
+  constexpr int SF = split_slots(L);
+  Bwd1D q;
+  q.KG = (m + SF - 1) / SF;
+  q.PG = (int)std::min<int64_t>(pairs, std::max<int64_t>(1, 256 / q.KG));
+  q.pre = q.KG >= 256;
+  q.gu = !q.pre && pairs * q.KG * L <= ((int64_t)1 << 23);
+  return q;
+}
+
+template <int L>
+static int64_t bwd1d_small_work_t(int m, int64_t pairs) {
+  const Bwd1D q = bwd1d_t<L>(m, pairs);
+  return ((int64_t)m * q.PG + (q.pre ? pairs : q.gu ? pairs * q.KG : 0)) * L;
+}
+
+int64_t bwd1d_small_work(int L, int m, int64_t pairs) {
+  switch (L) {
+#define PC_CASE(LL) \
+  case LL:          \
+    return bwd1d_small_work_t<LL>(m, pairs);
+    PC_FOR_EACH_L(PC_CASE)
+#undef PC_CASE
+  }
+  return 0;
+}
+
+bool bwd1d_small_gu(int L, int m, int64_t pairs) {
+  switch (L) {
+#define PC_CASE(LL) \
+  case LL:          \
+    return bwd1d_t<LL>(m, pairs).gu;
+    PC_FOR_EACH_L(PC_CASE)
+#undef PC_CASE
+  }
+  return false;
+}
+
+template <int L>
+static LaunchStatus bwd1d_small_t(const Small1D& p, const float* u, const float* gy, float* gu, float2* gspec,
+                                  int64_t batch, float2* work, hipStream_t s) {
   const int64_t pairs = (batch + 1) / 2;
-  hipLaunchKernelGGL(k_fft_pairs_small<L>, dim3((unsigned)((pairs + NF - 1) / NF)), dim3(NF * T), 0, s, gy, batch,
-                     work, p.tw);
-  hipError_t e = hipGetLastError();
+  const Bwd1D q = bwd1d_t<L>(p.m, pairs);
+  if (gu && !q.gu) return hipErrorInvalidValue;
+  float2* rest = work + (int64_t)p.m * q.PG * L;  // the shares of dL/du, or Gc
+  const dim3 grid((unsigned)(q.KG * q.PG)), block(split_slots(L) * split_threads(L));
+  if (q.pre) {
+    constexpr int NF = ffts_per_block(L), T = fft_threads(L);
+    hipLaunchKernelGGL(k_fft_pairs_small<L>, dim3((unsigned)((pairs + NF - 1) / NF)), dim3(NF * T), 0, s, gy, batch,
+                       rest, p.tw);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_bwd1d_small<L, false, true>), grid, block, 0, s, u, gy, pairs, batch, p.m, p.w, p.H, p.tws,
+                       q.KG, q.PG, rest, rest, work);
+  } else if (gu) {
+    hipLaunchKernelGGL((k_bwd1d_small<L, true, false>), grid, block, 0, s, u, gy, pairs, batch, p.m, p.w, p.H, p.tws,
+                       q.KG, q.PG, nullptr, rest, work);
+  } else {
+    hipLaunchKernelGGL((k_bwd1d_small<L, false, false>), grid, block, 0, s, u, gy, pairs, batch, p.m, p.w, p.H, p.tws,
+                       q.KG, q.PG, nullptr, rest, work);
+  }
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_grad1d_small<L>, dim3((unsigned)((p.m + NF - 1) / NF)), dim3(NF * T), 0, s, u, batch, p.m,
-                     p.w, work, gspec, p.tw);
+  const unsigned gub = gu ? blocks_for(pairs * L) : 0;
+  hipLaunchKernelGGL(k_bwd1d_small_sum<L>, dim3(gub + blocks_for((int64_t)p.m * (L / 2 + 1))), dim3(256), 0, s, rest,
+                     work, q.KG, q.PG, p.m, batch, gub, gu, gspec);
   return hipGetLastError();
 }
 
-LaunchStatus launch_grad1d_small(const Small1D& p, const float* u, const float* gy, float2* gspec, int64_t batch,
-                                 float2* work, hipStream_t s, Tracer* tr) {
-  TraceScope ts(tr, "grad1d_small", s);
+LaunchStatus launch_bwd1d_small(const Small1D& p, const float* u, const float* gy, float* gu, float2* gspec,
+                                int64_t batch, float2* work, hipStream_t s, Tracer* tr) {
+  TraceScope ts(tr, gu ? "bwd1d_small" : "grad1d_small", s);
   switch (p.L) {
 #define PC_CASE(LL) \
   case LL:          \
-    return grad1d_small_t<LL>(p, u, gy, gspec, batch, work, s);
+    return bwd1d_small_t<LL>(p, u, gy, gu, gspec, batch, work, s);
     PC_FOR_EACH_L(PC_CASE)
 #undef PC_CASE
   }

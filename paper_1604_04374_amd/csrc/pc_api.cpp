@@ -57,36 +57,51 @@ pc_status fail_hip(hipError_t e, const char* what) {
 std::mutex g_registry_mu;
 std::set<const void*> g_registry;  // live plans
 
+// exp(-2 i pi j / N), j < N (N a multiple of 8): float64 values on the first
+// eighth of the circle, the rest by symmetry (an eighth of the sines and
+// cosines, which were half of a small plan's creation), each rounded once.
+std::vector<float2> unit_roots(int64_t N) {
+  std::vector<float2> w((size_t)N);
+  const int64_t q = N / 4;
+  for (int64_t j = 0; 8 * j <= N; ++j) {
+    const double a = 2.0 * M_PI * (double)j / (double)N;
+    const float c = (float)std::cos(a), s = (float)std::sin(a);
+    // quarter k of the circle: (-i)^k times the first quarter's value
+    auto put = [&](int64_t i, float re, float im) {  // i in [0, q]
+      w[(size_t)i] = make_float2(re, im);
+      w[(size_t)(i + q)] = make_float2(im, -re);
+      w[(size_t)(i + 2 * q)] = make_float2(-re, -im);
+      if (i + 3 * q < N) w[(size_t)(i + 3 * q)] = make_float2(-im, re);
+    };
+    if (j < q) put(j, c, -s);
+    if (j > 0) put(q - j, s, -c);
+  }
+  w[0] = make_float2(1.f, 0.f);
+  w[(size_t)q] = make_float2(0.f, -1.f);
+  w[(size_t)(2 * q)] = make_float2(-1.f, 0.f);
+  w[(size_t)(3 * q)] = make_float2(0.f, 1.f);
+  return w;
+}
+
 // Twiddle table of the workgroup FFT engine for length L (see fft_engine.hpp):
 // for each pass (stride Ns, radix R), exp(-2 i pi q k / (Ns R)) for k < Ns,
-// 1 <= q < R, in float64 then rounded once.
+// 1 <= q < R (Ns R divides L, so each is one of the L unit roots).
 std::vector<float2> engine_twiddles(int L, int P = 0) {
   if (P == 0) P = pc::points_per_thread(L);
   const pc::Sched s = pc::make_sched(L, P);
+  const std::vector<float2> root = unit_roots(L);
   std::vector<float2> tw;
   tw.reserve(L);
   long Ns = 1;
   for (int i = 0; i < s.n; ++i) {
     const int R = s.r[i];
+    const long step = L / (Ns * R);
     for (long k = 0; k < Ns; ++k)
-      for (int q = 1; q < R; ++q) {
-        const double a = -2.0 * M_PI * (double)(q * k) / (double)(Ns * R);
-        tw.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
-      }
+      for (int q = 1; q < R; ++q) tw.push_back(root[(size_t)(q * k * step)]);
     Ns *= R;
   }
   tw.push_back(make_float2(0.f, 0.f));  // pad to L entries
   return tw;
-}
-
-// exp(-2 i pi j / N), j < N, exact phase reduction in integers.
-std::vector<float2> unit_roots(int64_t N) {
-  std::vector<float2> w(N);
-  for (int64_t j = 0; j < N; ++j) {
-    const double a = -2.0 * M_PI * (double)j / (double)N;
-    w[j] = make_float2((float)std::cos(a), (float)std::sin(a));
-  }
-  return w;
 }
 
 // Inner length L and class count R (N = R L, R in {2, 4, 8, 16}) of a
@@ -363,19 +378,38 @@ pc_status build_small1d(pc_plan p, const float* windows, const float* h, hipStre
   float* w = nullptr;
   st = p->upload(&w, std::vector<float>(windows, windows + (size_t)m * L), s, &p->window_bytes);
   if (st) return st;
+  // the twiddles, and those of the small batches' kernels behind them where
+  // these take another number of points per thread
+  const int sp = pc::small1d_split_points(L);
+  std::vector<float2> tables = engine_twiddles(L);
+  const size_t split_at = sp == pc::points_per_thread(L) ? 0 : tables.size();
+  if (split_at) {
+    const std::vector<float2> t2 = engine_twiddles(L, sp);
+    tables.insert(tables.end(), t2.begin(), t2.end());
+  }
   float2* tw = nullptr;
-  st = p->upload(&tw, engine_twiddles(L), s);
+  st = p->upload(&tw, tables, s);
   if (st) return st;
+  // room for the workgroups' shares at every call size up to the plan's that
+  // spreads a pair's terms (behind the spectra)
+  int64_t shares = 0;
+  for (int64_t pairs = 1; pairs <= (p->d.batch + 1) / 2; ++pairs) {
+    const int g = pc::small1d_groups(L, m, pairs);
+    if (g == 0) break;
+    if (g > 1) shares = std::max(shares, pairs * g);
+  }
   DeviceTemp hd;
   if ((st = hd.upload(h, (size_t)m * L))) return st;
   float2* H = nullptr;
-  st = p->alloc(&H, (size_t)m * L, &p->spectra_bytes);
+  st = p->alloc(&H, (size_t)(m + shares) * L);
   if (st) return st;
+  p->spectra_bytes += (int64_t)m * L * (int64_t)sizeof(float2);
+  p->workspace_bytes += shares * L * (int64_t)sizeof(float2);
   hipError_t e = pc::launch_spec1d_full(L, hd.get(), H, m, tw, s);
   if (e != hipSuccess) return fail_hip(e, "spectra kernel");
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(e, "spectra kernel");
-  p->s1 = pc::Small1D{L, m, w, H, tw};
+  p->s1 = pc::Small1D{L, m, w, H, tw, tw + split_at, shares > 0 ? H + (size_t)m * L : nullptr};
   return PC_SUCCESS;
 }
 
@@ -1790,9 +1824,13 @@ pc_status create_plan(const pc_plan_desc& d, const float* windows, const float* 
   }
   if (st == PC_SUCCESS && path != 3) {  // sections hold their gradient planes in their sub-plans
     if (d.flags & PC_PLAN_GRADIENTS) {
-      // 1D: pair spectra (pairs x N) or the per-class accumulators (m x N); 2D: m planes
+      // 1D: the backward's shares at the largest call, or the per-class accumulators (m x N); 2D: m planes
       const int64_t pairs = (d.batch + 1) / 2;
-      const int64_t n = path == 0 ? pairs * d.n0 : path == 1 ? (int64_t)d.m * d.n0 : d.m * d.n0 * (d.n1 / 2 + 1);
+      int64_t small = 0;
+      if (path == 0)  // (the shares of dL/du are capped: calls below the largest may need the most)
+        for (int64_t q = pairs; q > 0; q = pc::bwd1d_small_gu(p->s1.L, d.m, q) ? 0 : q - 1)
+          small = std::max(small, pc::bwd1d_small_work(p->s1.L, d.m, q));
+      const int64_t n = path == 0 ? small : path == 1 ? (int64_t)d.m * d.n0 : d.m * d.n0 * (d.n1 / 2 + 1);
       st = p->alloc(&p->grad_ws, (size_t)n, &p->workspace_bytes);
     }
   }
@@ -2318,7 +2356,7 @@ static hipError_t run_grad_spectra(pc_plan p, const float* u, const float* gy, f
   const float* b = p->pconv ? u : gy;
   hipError_t e;
   if (p->path == 0)
-    e = pc::launch_grad1d_small(p->s1, a, b, out, batch, p->grad_ws, s, p->tr());
+    e = pc::launch_bwd1d_small(p->s1, a, b, nullptr, out, batch, p->grad_ws, s, p->tr());
   else if (p->path == 1)
     e = pc::launch_grad1d_large(p->l1, a, b, out, batch, p->grad_ws, s, p->tr());
   else if (p->path == 2)
@@ -2359,6 +2397,8 @@ pc_status pc_backward(pc_plan p, const float* u, const float* gy, float* gu, voi
     e = pc::launch_grad2d(p->p2, u, gy, gs, batch, p->grad_ws, s, p->tr(), state == 0,
                           state == 2 ? p->p2.keep : nullptr);
     if (e == hipSuccess && gu) e = pc::launch_adj2d_tail(p->p2, gu, batch, s, p->tr());
+  } else if (p->path == 0 && !p->pconv && gspec && gu && pc::bwd1d_small_gu(p->s1.L, p->d.m, (batch + 1) / 2)) {
+    e = pc::launch_bwd1d_small(p->s1, u, gy, gu, gs, batch, p->grad_ws, s, p->tr());
   } else {
     if (gspec) e = run_grad_spectra(p, u, gy, gs, batch, true, nullptr, s);
     if (e == hipSuccess && gu) e = p->pconv ? run_forward(p, gy, gu, batch, s) : run_adjoint(p, gy, gu, batch, s);

@@ -66,7 +66,13 @@ struct Small1D {
   const float* w;            // m x L windows
   const float2* H;           // m x L full complex spectra, natural order
   const float2* tw;          // engine twiddles for L
+  // small batches (small1d_groups):
+  const float2* tws;         // engine twiddles for L at small1d_split_points(L) points per thread
+  float2* part;              // workgroups' shares of the output, groups x L per pair (null: one group)
 };
+// workgroups per pair for a call of `pairs` pairs (0: one pair per transform slot)
+int small1d_groups(int L, int m, int64_t pairs);
+int small1d_split_points(int L);
 LaunchStatus launch_spec1d_full(int L, const float* h, float2* H, int m, const float2* tw, hipStream_t s);
 LaunchStatus launch_fwd1d_small(const Small1D& p, const float* u, float* y, int64_t batch, hipStream_t s,
                                 Tracer* tr = nullptr);
@@ -377,8 +383,13 @@ LaunchStatus launch_transpose_set(const TransposeSet& ts, float2* ext, bool to_i
 // Spectra as parameters (natural real-FFT layout) and their gradients.
 LaunchStatus launch_spectra1d(const Small1D* ps, const Large1D* pl, const float2* in, float2* out, bool import,
                               hipStream_t s);
-LaunchStatus launch_grad1d_small(const Small1D& p, const float* u, const float* gy, float2* gspec, int64_t batch,
-                                 float2* work, hipStream_t s, Tracer* tr = nullptr);
+// Spectra gradient of the small sizes and, with gu non-null (only where
+// bwd1d_small_gu says so), dL/du from the same transforms; work:
+// bwd1d_small_work complex values for a call of that many pairs.
+int64_t bwd1d_small_work(int L, int m, int64_t pairs);
+bool bwd1d_small_gu(int L, int m, int64_t pairs);
+LaunchStatus launch_bwd1d_small(const Small1D& p, const float* u, const float* gy, float* gu, float2* gspec,
+                                int64_t batch, float2* work, hipStream_t s, Tracer* tr = nullptr);
 LaunchStatus launch_grad1d_large(const Large1D& p, const float* u, const float* gy, float2* gspec, int64_t batch,
                                  float2* E, hipStream_t s, Tracer* tr = nullptr);
 LaunchStatus launch_spectra2d(const Plan2D& p, const float2* in, float2* out, bool import, hipStream_t s);

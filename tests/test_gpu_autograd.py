@@ -189,3 +189,28 @@ def test_c5_autograd_full_grid():
     r = y.detach().cpu().numpy().astype(np.float64) - f
     assert rel_l2(gu, ex.adjoint_fft(r, w, None, h_spec=spec)) <= TOL
     assert rel_l2(gs, grads.grad_spectra(p.u, r, w)) <= TOL
+
+
+@pytest.mark.parametrize("n,m,batch", [
+    (256, 3, 1), (96, 40, 4),          # slots without a term; several term groups of one workgroup's slots
+    (1024, 9, 5), (3072, 12, 37), (8192, 16, 64),   # pairs spread over workgroups, odd batches
+    (2048, 256, 3),                    # as many term groups as compute units: the gradient transformed beforehand
+    (8192, 16, 200),                   # shares of dL/du beyond their cap: gradient and adjoint apart
+])
+def test_small_backward_spreads_terms_and_pairs(n, m, batch):
+    import torch
+    import paper_1604_04374_amd as pcm
+    p = wl.small_1d(n, m, 1, batch, seed=n + m)
+    g = np.random.default_rng(n).standard_normal(p.u.shape).astype(np.float32)
+    plan = pcm.Plan(p.w, p.h, batch=batch, gradients=True)
+    u, gy = torch.from_numpy(p.u).cuda(), torch.from_numpy(g).cuda()
+    w, h = p.dense_windows(), p.h.astype(np.float64)
+    ru, rs = grads.grad_u(g.astype(np.float64), w, h), grads.grad_spectra(p.u.astype(np.float64), g.astype(np.float64), w)
+    for want_u in (True, False):
+        gu, gs = plan.backward(u, gy, want_u=want_u)
+        assert rel_l2(gs.cpu().numpy(), rs) <= TOL
+        assert (gu is None) == (not want_u) and (gu is None or rel_l2(gu.cpu().numpy(), ru) <= TOL)
+    if batch > 1:  # a smaller call than the plan's
+        gu, gs = plan.backward(u[:1], gy[:1])
+        assert rel_l2(gu.cpu().numpy(), ru[:1]) <= TOL
+        assert rel_l2(gs.cpu().numpy(), grads.grad_spectra(p.u[:1].astype(np.float64), g[:1].astype(np.float64), w)) <= TOL

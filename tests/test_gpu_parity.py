@@ -58,6 +58,19 @@ def test_1d_small_sizes(n, m, deg, batch):
     _check(p, direct=n <= 2048 and batch <= 64)
 
 
+@pytest.mark.parametrize("n,m,deg,batch", [
+    # one workgroup per pair (few short terms; slots left idle), the most it takes
+    (64, 1, 1, 1), (96, 33, 1, 3), (512, 16, 1, 5),
+    # spread over workgroups: one term each, ragged terms per slot, terms past the last
+    (1024, 7, 1, 1), (1536, 5, 1, 2), (3072, 12, 3, 37), (8192, 30, 3, 64), (6144, 9, 1, 9), (2048, 31, 3, 101),
+    # the last batch before one pair per slot, and the first with it
+    (4096, 4, 1, 509), (4096, 4, 1, 513),
+])
+def test_1d_small_batches_spread_their_terms(n, m, deg, batch):
+    p = wl.small_1d(n, m, deg, batch, seed=300 + n + m, sigma_fn=lambda y: 0.01 + 0.03 * y)
+    _check(p)
+
+
 # ---------------------------------------------------------------------------
 # 1D four-step (N = R * L)
 # ---------------------------------------------------------------------------
