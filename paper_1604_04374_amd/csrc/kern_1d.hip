@@ -640,8 +640,12 @@ __global__ __launch_bounds__(L / P) void k_fold_fft(const float* __restrict__ x,
 // then the class's inverse FFT_L, stored for the combine step.
 // C: chunks of the short-support path (1 or 2; the plan's cw table), 0 for
 // the long-support path.
-template <int L, int R, int P, int C>
-__global__ __launch_bounds__(L / P) void k_fwd1d_large(const float* __restrict__ u, int64_t batch, Large1D p) {
+// G term groups: workgroup (pair, f1, g) takes the terms [m g / G, m (g + 1) / G)
+// and leaves its own inverse transform in slice g of Bws (k_combine1d adds
+// the slices), so that a few signals still fill the chip.
+// (SPLIT: G > 1; without it the group arithmetic folds away)
+template <int L, int R, int P, int C, bool SPLIT>
+__global__ __launch_bounds__(L / P) void k_fwd1d_large(const float* __restrict__ u, int64_t batch, Large1D p, int G) {
   constexpr int N = L * R;
   __shared__ float2 lds[fs_lds_len<L, P>()];
   FsLds<L, P> xl(lds);
@@ -650,13 +654,16 @@ __global__ __launch_bounds__(L / P) void k_fwd1d_large(const float* __restrict__
   float2 twr[tw_reg_count<L, P>()];
   load_tw_reg<L, P>(twr, p.tw, t);
   const int f1 = blockIdx.x % R;
-  const int64_t pair = blockIdx.x / R;
+  const int64_t pg = blockIdx.x / R;  // pair G + g
+  const int64_t pair = SPLIT ? pg / G : pg;
+  const int g = SPLIT ? (int)(pg % G) : 0;
+  const int k0 = SPLIT ? p.m * g / G : 0, k1 = SPLIT ? p.m * (g + 1) / G : p.m;
   const float* xa = u + 2 * pair * N;
   const float* xb = 2 * pair + 1 < batch ? xa + N : p.zeros;  // odd batch: a zero second signal
   float2 acc[P];
 #pragma unroll
   for (int e = 0; e < P; ++e) acc[e] = make_float2(0.f, 0.f);
-  for (int k = 0; k < p.m; ++k) {
+  for (int k = k0; k < k1; ++k) {
     const int S = p.w_len[k];
     if (S == 0) continue;
     const int o = p.w_off[k];
@@ -676,16 +683,17 @@ __global__ __launch_bounds__(L / P) void k_fwd1d_large(const float* __restrict__
     for (int e = 0; e < P; ++e) acc[e] = cfma(acc[e], hv[e], v[e]);
   }
   xl.template fft<true>(acc, twr, t);
-  store_blk<L, P>(p.Bws + (pair * R + f1) * L, acc, t);
+  store_blk<L, P>(p.Bws + (pg * R + f1) * L, acc, t);
 }
 
-// y[n2 + L n1] = (1/N) sum_f1 W_R^{-f1 n1} (W_N^{-f1 n2} b^{f1}[n2]).
+// y[n2 + L n1] = (1/N) sum_f1 W_R^{-f1 n1} (W_N^{-f1 n2} b^{f1}[n2]), b the
+// sum of the G slices of the forward pass.
 // One thread per 16-byte pair of a block (block_pos: elements n2 = t + T e
 // and n2 + T, e even), so every class block is read with coalesced 16-byte
 // loads.
-template <int L, int R, int P>
+template <int L, int R, int P, bool SPLIT>
 __global__ __launch_bounds__(256) void k_combine1d(const float2* __restrict__ Bws, float* __restrict__ y, int64_t batch,
-                                                   const float2* __restrict__ twC) {
+                                                   const float2* __restrict__ twC, int G) {
   constexpr int N = L * R, T = L / P;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t pairs = (batch + 1) / 2;
@@ -697,7 +705,14 @@ __global__ __launch_bounds__(256) void k_combine1d(const float2* __restrict__ Bw
   float2 b[2][R];
 #pragma unroll
   for (int f1 = 0; f1 < R; ++f1) {
-    const float4 v = reinterpret_cast<const float4*>(Bws + (pair * R + f1) * L)[q];
+    const float4* s = reinterpret_cast<const float4*>(Bws + (pair * (SPLIT ? G : 1) * R + f1) * L) + q;
+    float4 v = s[0];
+    if constexpr (SPLIT) {
+      for (int g = 1; g < G; ++g) {
+        const float4 a = s[(int64_t)g * (R * L / 2)];
+        v = make_float4(v.x + a.x, v.y + a.y, v.z + a.z, v.w + a.w);
+      }
+    }
     b[0][f1] = cmulc(make_float2(v.x, v.y), twC[f1 * L + n2[0]]);
     b[1][f1] = cmulc(make_float2(v.z, v.w), twC[f1 * L + n2[1]]);
   }
@@ -722,8 +737,10 @@ __global__ __launch_bounds__(256) void k_combine1d(const float2* __restrict__ Bw
 // item per term, whose support is at most C L long: the R class transforms
 // serve all its chunks, and each chunk takes its window and class modulation
 // together from cw.
-template <int L, int R, int P, int C>
-__global__ __launch_bounds__(L / P) void k_adj1d_large(Large1D p) {
+// G class groups (G divides R): workgroup (pair, item, g) takes R / G classes
+// and leaves its sum in slice g of the pair's block (k_ola1d adds them).
+template <int L, int R, int P, int C, bool SPLIT>
+__global__ __launch_bounds__(L / P) void k_adj1d_large(Large1D p, int G) {
   constexpr int T = L / P;
   __shared__ float2 lds[fs_lds_len<L, P>()];
   FsLds<L, P> xl(lds);
@@ -732,7 +749,9 @@ __global__ __launch_bounds__(L / P) void k_adj1d_large(Large1D p) {
   float2 twr[tw_reg_count<L, P>()];
   load_tw_reg<L, P>(twr, p.tw, t);
   const int item = blockIdx.x % p.n_items;
-  const int64_t pair = blockIdx.x / p.n_items;
+  const int64_t pg = blockIdx.x / p.n_items;  // pair G + g
+  const int64_t pair = SPLIT ? pg / G : pg;
+  const int f1_0 = SPLIT ? (int)(pg % G) * (R / G) : 0, f1_1 = SPLIT ? f1_0 + R / G : R;
   const int k = p.item_k[item];
   const int c0 = p.item_d0[item];
   const int Sc = p.item_len[item];
@@ -783,13 +802,14 @@ __global__ __launch_bounds__(L / P) void k_adj1d_large(Large1D p) {
   };
   // (prefetching the next class into a second register set measured slower
   // than register-resident twiddles, which need those registers)
-  for (int f1 = 0; f1 < R; ++f1) {
+#pragma unroll 1
+  for (int f1 = f1_0; f1 < f1_1; ++f1) {
     float2 va[P], ha[P];
     load(va, ha, f1);
     prod(va, ha);
     step(va, f1);
   }
-  float2* out = p.Pws + pair * p.p_stride + p.item_out[item];
+  float2* out = p.Pws + pg * p.p_stride + p.item_out[item];
   const float sc = 1.0f / (float)(L * R);
   if constexpr (C > 0) {
 #pragma unroll
@@ -811,21 +831,28 @@ __global__ __launch_bounds__(L / P) void k_adj1d_large(Large1D p) {
 
 // x[n] = sum over the items covering n of their stored products; the items
 // that can cover a sample are listed per tile of 256 samples.
-template <int L, int R>
-__global__ __launch_bounds__(256) void k_ola1d(Large1D p, float* __restrict__ x, int64_t batch) {
+template <int L, int R, bool SPLIT>
+__global__ __launch_bounds__(256) void k_ola1d(Large1D p, float* __restrict__ x, int64_t batch, int G) {
   constexpr int N = L * R, TILES = N / 256;
   // one workgroup per (pair, tile): the tile's item list is uniform
   const int64_t pair = blockIdx.x / TILES;
   const int tile = (int)(blockIdx.x % TILES);
   const int n = tile * 256 + (int)threadIdx.x;
-  const float2* base = p.Pws + pair * p.p_stride;
+  const float2* base = p.Pws + pair * (SPLIT ? G : 1) * p.p_stride;
   float2 acc = make_float2(0.f, 0.f);
   const int j0 = p.tile_off[tile], j1 = p.tile_off[tile + 1];
   for (int j = j0; j < j1; ++j) {
     const int it = p.tile_items[j];
     int dd = n - p.item_oc[it];
     if (dd < 0) dd += N;
-    if (dd < p.item_len[it]) acc = cadd(acc, base[p.item_out[it] + dd]);
+    if (dd < p.item_len[it]) {
+      const float2* s = base + p.item_out[it] + dd;
+      acc = cadd(acc, s[0]);
+      if constexpr (SPLIT) {
+#pragma unroll 4
+        for (int g = 1; g < G; ++g) acc = cadd(acc, s[g * p.p_stride]);
+      }
+    }
   }
   const int64_t sa = 2 * pair, sb = sa + 1;
   x[sa * N + n] = acc.x;
@@ -836,7 +863,7 @@ __global__ __launch_bounds__(256) void k_ola1d(Large1D p, float* __restrict__ x,
 // is a plan-time choice.
 #define PC_FOR_EACH_LRP(X)                                                          \
   X(8192, 2, 16) X(8192, 4, 16) X(8192, 8, 16) X(8192, 16, 16)                     \
-  X(6144, 2, 24) X(6144, 4, 24) X(6144, 8, 24) X(6144, 16, 24)                     \
+  X(6144, 2, 12) X(6144, 4, 12) X(6144, 8, 12) X(6144, 16, 12)                     \
   X(4096, 2, 16) X(4096, 4, 16) X(4096, 8, 16) X(4096, 16, 16)
 
 bool fourstep_variant_supported(int L, int R, int P) {
@@ -845,6 +872,30 @@ bool fourstep_variant_supported(int L, int R, int P) {
   PC_FOR_EACH_LRP(PC_CASE)
 #undef PC_CASE
   return false;
+}
+
+// Workgroups that the four-step kernels keep resident (two of 256 threads
+// per compute unit at their 237 to 256 VGPRs, one of 512): with fewer, the
+// terms, classes or pairs are split further.  Measured (5 signals of 24576
+// samples, 9 terms; us per launch at 24 points per thread and one group,
+// split, and split at 12 points): forward 119, 25, 13.4; adjoint 60, 21,
+// 11.9; gradient 60, 29, 11.3 (12 to 36 workgroups before, 108 split).
+static int64_t large_target(const Large1D& p) { return p.L / p.P >= 512 ? 256 : 512; }
+
+int fwd1d_large_groups(const Large1D& p, int64_t pairs) {
+  const int g = (int)std::min<int64_t>(p.m, std::max<int64_t>(1, large_target(p) / (pairs * p.R)));
+  const int per = (p.m + g - 1) / g;  // terms per group; the fewest groups with that many
+  return (p.m + per - 1) / per;
+}
+
+int adj1d_large_groups(const Large1D& p, int64_t pairs) {
+  int g = 1;
+  while (g < p.R && pairs * std::max(p.n_items, 1) * g * 2 <= large_target(p)) g *= 2;
+  return g;
+}
+
+int grad1d_large_groups(const Large1D& p, int64_t pairs) {
+  return (int)std::min<int64_t>(pairs, std::max<int64_t>(1, large_target(p) / ((int64_t)p.m * p.R)));
 }
 
 template <int L, int R, int P>
@@ -857,26 +908,40 @@ static LaunchStatus fold_fft_t(const Large1D& p, const float* x, int64_t n_sig, 
   return hipGetLastError();
 }
 
+#define PC_SPLIT_LAUNCH(K, C, ...)                                              \
+  do {                                                                          \
+    if (G > 1)                                                                  \
+      hipLaunchKernelGGL((K<L, R, P, C, true>), grid, block, 0, s, __VA_ARGS__);  \
+    else                                                                        \
+      hipLaunchKernelGGL((K<L, R, P, C, false>), grid, block, 0, s, __VA_ARGS__); \
+  } while (0)
+
 template <int L, int R, int P>
 static LaunchStatus fwd1d_large_t(const Large1D& p, const float* u, float* y, int64_t batch, hipStream_t s,
                                   Tracer* tr) {
   const int64_t pairs = (batch + 1) / 2;
+  const int G = fwd1d_large_groups(p, pairs);
   {
     TraceScope ts(tr, "fwd1d_large", s);
-    const dim3 grid((unsigned)(pairs * R)), block(L / P);
+    const dim3 grid((unsigned)(pairs * R * G)), block(L / P);
     if (p.chunks == 2)
-      hipLaunchKernelGGL((k_fwd1d_large<L, R, P, 2>), grid, block, 0, s, u, batch, p);
+      PC_SPLIT_LAUNCH(k_fwd1d_large, 2, u, batch, p, G);
     else if (p.chunks == 1)
-      hipLaunchKernelGGL((k_fwd1d_large<L, R, P, 1>), grid, block, 0, s, u, batch, p);
+      PC_SPLIT_LAUNCH(k_fwd1d_large, 1, u, batch, p, G);
     else
-      hipLaunchKernelGGL((k_fwd1d_large<L, R, P, 0>), grid, block, 0, s, u, batch, p);
+      PC_SPLIT_LAUNCH(k_fwd1d_large, 0, u, batch, p, G);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  // few pairs: smaller workgroups, so that every compute unit gets one
   const int64_t nthr = pairs * (L / 2);
+  const unsigned nt = nthr < 256 * 256 ? 64 : 256;
+  const dim3 grid((unsigned)((nthr + nt - 1) / nt)), block(nt);
   TraceScope ts(tr, "combine1d", s);
-  hipLaunchKernelGGL((k_combine1d<L, R, P>), dim3((unsigned)((nthr + 255) / 256)), dim3(256), 0, s, p.Bws, y, batch,
-                     p.twC);
+  if (G > 1)
+    hipLaunchKernelGGL((k_combine1d<L, R, P, true>), grid, block, 0, s, p.Bws, y, batch, p.twC, G);
+  else
+    hipLaunchKernelGGL((k_combine1d<L, R, P, false>), grid, block, 0, s, p.Bws, y, batch, p.twC, G);
   return hipGetLastError();
 }
 
@@ -884,22 +949,27 @@ template <int L, int R, int P>
 static LaunchStatus adj1d_large_t(const Large1D& p, const float* v, float* x, int64_t batch, hipStream_t s,
                                   Tracer* tr) {
   const int64_t pairs = (batch + 1) / 2;
-  LaunchStatus e = fold_fft_t<L, R, P>(p, v, batch, p.Vws, true, s, tr);
+  LaunchStatus e = v ? fold_fft_t<L, R, P>(p, v, batch, p.Vws, true, s, tr) : hipSuccess;
   if (e != hipSuccess) return e;
+  const int G = adj1d_large_groups(p, pairs);
   if (p.n_items > 0) {
     TraceScope ts(tr, "adj1d_large", s);
-    const dim3 grid((unsigned)(pairs * p.n_items)), block(L / P);
+    const dim3 grid((unsigned)(pairs * p.n_items * G)), block(L / P);
     if (p.chunks == 2)
-      hipLaunchKernelGGL((k_adj1d_large<L, R, P, 2>), grid, block, 0, s, p);
+      PC_SPLIT_LAUNCH(k_adj1d_large, 2, p, G);
     else if (p.chunks == 1)
-      hipLaunchKernelGGL((k_adj1d_large<L, R, P, 1>), grid, block, 0, s, p);
+      PC_SPLIT_LAUNCH(k_adj1d_large, 1, p, G);
     else
-      hipLaunchKernelGGL((k_adj1d_large<L, R, P, 0>), grid, block, 0, s, p);
+      PC_SPLIT_LAUNCH(k_adj1d_large, 0, p, G);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   TraceScope ts(tr, "ola1d", s);
-  hipLaunchKernelGGL((k_ola1d<L, R>), dim3((unsigned)(pairs * (L * R / 256))), dim3(256), 0, s, p, x, batch);
+  const dim3 grid((unsigned)(pairs * (L * R / 256))), block(256);
+  if (G > 1)
+    hipLaunchKernelGGL((k_ola1d<L, R, true>), grid, block, 0, s, p, x, batch, G);
+  else
+    hipLaunchKernelGGL((k_ola1d<L, R, false>), grid, block, 0, s, p, x, batch, G);
   return hipGetLastError();
 }
 
@@ -1179,10 +1249,11 @@ __global__ __launch_bounds__(256) void k_origin_phase1d(float2* __restrict__ Hd,
 }
 
 // E_k^{f1} = sum over pairs of conj(FFT_L(fold(w_k u))) . Gdec^{f1}, one
-// (term, class) per workgroup.
+// (term, class, pair group) per workgroup: group g of G takes pairs g, g + G,
+// ... and writes slice g of E (k_grad_export1d_large adds the slices).
 template <int L, int R, int P, int C>
 __global__ __launch_bounds__(L / P) void k_grad1d_large(const float* __restrict__ u, int64_t batch, Large1D p,
-                                                        float2* __restrict__ E) {
+                                                        float2* __restrict__ E, int G) {
   constexpr int N = L * R;
   __shared__ float2 lds[fs_lds_len<L, P>()];
   FsLds<L, P> xl(lds);
@@ -1190,7 +1261,7 @@ __global__ __launch_bounds__(L / P) void k_grad1d_large(const float* __restrict_
   float2 twr[tw_reg_count<L, P>()];
   load_tw_reg<L, P>(twr, p.tw, t);
   const int f1 = blockIdx.x % R;
-  const int k = blockIdx.x / R;
+  const int k = (blockIdx.x / R) % p.m, g = blockIdx.x / R / p.m;
   const int S = p.w_len[k];
   const int o = p.w_off[k];
   const float* wc = p.wc + p.w_base[k];
@@ -1200,28 +1271,34 @@ __global__ __launch_bounds__(L / P) void k_grad1d_large(const float* __restrict_
   for (int e = 0; e < P; ++e) acc[e] = make_float2(0.f, 0.f);
   const int64_t pairs = (batch + 1) / 2;
   if (S > 0) {
-    for (int64_t pr = 0; pr < pairs; ++pr) {
+    for (int64_t pr = g; pr < pairs; pr += G) {
       const float* xa = u + 2 * pr * N;
       const float* xb = 2 * pr + 1 < batch ? xa + N : p.zeros;
+      // an opaque index: the compiler otherwise keeps the window table's
+      // values (the same for every pair) and the addresses in registers for
+      // the whole loop (362 registers at 4096 points, 384 bytes of spills at
+      // 6144); the gradient's spectrum is read after the transform, which
+      // leaves more waves
+      const int tt = opaque1d(t);
       float2 v[P];
       if constexpr (C > 0)
-        fold_short<L, R, P, C>(v, t, xa, xb, o, p.cw + ((int64_t)k * R + f1) * C * L);
+        fold_short<L, R, P, C>(v, tt, xa, xb, o, p.cw + ((int64_t)k * R + f1) * C * L);
       else
-        fold_long<L, R, P>(v, t, f1, xa, xb, wc, o, S, p.twC, p.twN);
-      float2 gv[P];
-      load_blk<L, P>(p.Vws + (pr * R + f1) * L, gv, t);
+        fold_long<L, R, P>(v, tt, f1, xa, xb, wc, o, S, p.twC, p.twN);
       xl.template fft<false>(v, twr, t);
+      float2 gv[P];
+      load_blk<L, P>(p.Vws + (pr * R + f1) * L, gv, tt);
 #pragma unroll
       for (int e = 0; e < P; ++e) acc[e] = cfma_conj(acc[e], v[e], gv[e]);
     }
   }
-  store_blk<L, P>(E + ((int64_t)k * R + f1) * L, acc, t);
+  store_blk<L, P>(E + (((int64_t)g * p.m + k) * R + f1) * L, acc, t);
 }
 
 template <int L, int R, int P>
 __global__ __launch_bounds__(256) void k_grad_export1d_large(const float2* __restrict__ E, float2* __restrict__ gspec,
                                                              int m, const int* __restrict__ w_off,
-                                                             const float2* __restrict__ twN) {
+                                                             const float2* __restrict__ twN, int G) {
   constexpr int N = L * R, NH = N / 2 + 1;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= (int64_t)m * NH) return;
@@ -1230,10 +1307,16 @@ __global__ __launch_bounds__(256) void k_grad_export1d_large(const float2* __res
   // E was accumulated with the windowed transforms in the window-origin
   // frame; the natural-frame product carries conj(W_N^{f o_k})
   constexpr int T = L / P;
-  const float2 a =
-      cmulc(E[((int64_t)k * R + f % R) * L + block_pos(f / R, T)], origin_phase<L, R>(twN, f, w_off[k]));
-  const float2 b =
-      cmulc(E[((int64_t)k * R + fm % R) * L + block_pos(fm / R, T)], origin_phase<L, R>(twN, fm, w_off[k]));
+  const float2* ea = E + ((int64_t)k * R + f % R) * L + block_pos(f / R, T);
+  const float2* eb = E + ((int64_t)k * R + fm % R) * L + block_pos(fm / R, T);
+  float2 sa = ea[0], sb = eb[0];
+#pragma unroll 4
+  for (int g = 1; g < G; ++g) {
+    sa = cadd(sa, ea[(int64_t)g * m * N]);
+    sb = cadd(sb, eb[(int64_t)g * m * N]);
+  }
+  const float2 a = cmulc(sa, origin_phase<L, R>(twN, f, w_off[k]));
+  const float2 b = cmulc(sb, origin_phase<L, R>(twN, fm, w_off[k]));
   const float sc = 0.5f * half_weight(f, N) / (float)N;
   gspec[gid] = make_float2(sc * (a.x + b.x), sc * (a.y - b.y));
 }
@@ -1397,20 +1480,21 @@ static LaunchStatus grad1d_large_t(const Large1D& p, const float* u, const float
                                    float2* E, hipStream_t s, Tracer* tr) {
   LaunchStatus e = fold_fft_t<L, R, P>(p, gy, batch, p.Vws, true, s, tr);
   if (e != hipSuccess) return e;
+  const int G = grad1d_large_groups(p, (batch + 1) / 2);
   {
     TraceScope ts(tr, "grad1d_large", s);
-    const dim3 grid((unsigned)(p.m * R)), block(L / P);
+    const dim3 grid((unsigned)(p.m * R * G)), block(L / P);
     if (p.chunks == 2)
-      hipLaunchKernelGGL((k_grad1d_large<L, R, P, 2>), grid, block, 0, s, u, batch, p, E);
+      hipLaunchKernelGGL((k_grad1d_large<L, R, P, 2>), grid, block, 0, s, u, batch, p, E, G);
     else if (p.chunks == 1)
-      hipLaunchKernelGGL((k_grad1d_large<L, R, P, 1>), grid, block, 0, s, u, batch, p, E);
+      hipLaunchKernelGGL((k_grad1d_large<L, R, P, 1>), grid, block, 0, s, u, batch, p, E, G);
     else
-      hipLaunchKernelGGL((k_grad1d_large<L, R, P, 0>), grid, block, 0, s, u, batch, p, E);
+      hipLaunchKernelGGL((k_grad1d_large<L, R, P, 0>), grid, block, 0, s, u, batch, p, E, G);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((k_grad_export1d_large<L, R, P>), dim3(blocks_for((int64_t)p.m * (L * R / 2 + 1))), dim3(256), 0,
-                     s, E, gspec, p.m, p.w_off, p.twN);
+                     s, E, gspec, p.m, p.w_off, p.twN, G);
   return hipGetLastError();
 }
 

@@ -474,18 +474,25 @@ pc_status build_large1d(pc_plan p, int L, int R, const float* windows, const flo
     }
     tile_off[n_tiles] = (int)tile_items.size();
   }
+  // exp(-2 i pi j / N) in float64, for the tables below (each entry is one of
+  // the N roots, which spares a sine and a cosine per entry)
+  std::vector<double> rc((size_t)N), rs((size_t)N);
+  for (int64_t j = 0; j < N; ++j) {
+    const double a = -2.0 * M_PI * (double)j / (double)N;
+    rc[(size_t)j] = std::cos(a);
+    rs[(size_t)j] = std::sin(a);
+  }
   // class modulation table twC[f1 * L + n2] = exp(-2 i pi f1 n2 / N)
   std::vector<float2> twC((size_t)N);
   for (int f1 = 0; f1 < R; ++f1)
     for (int n2 = 0; n2 < L; ++n2) {
-      const int64_t j = ((int64_t)f1 * n2) % N;
-      const double a = -2.0 * M_PI * (double)j / (double)N;
-      twC[(size_t)f1 * L + n2] = make_float2((float)std::cos(a), (float)std::sin(a));
+      const size_t j = (size_t)(((int64_t)f1 * n2) % N);
+      twC[(size_t)f1 * L + n2] = make_float2((float)rc[j], (float)rs[j]);
     }
   pc::Large1D& q = p->l1;
   q.L = L;
   q.R = R;
-  q.P = pc::points_per_thread(L);
+  q.P = pc::fourstep_points(L);
   if (!pc::fourstep_variant_supported(L, R, q.P)) return fail(PC_ERROR_UNSUPPORTED, "four-step variant not built");
   q.m = m;
   q.chunks = chunks;
@@ -521,8 +528,8 @@ pc_status build_large1d(pc_plan p, int L, int R, const float* windows, const flo
           for (int d = 0; d < L; ++d) {
             const int64_t dd = (int64_t)c * L + d;
             const double wv = wc[(size_t)base[k] + dd];
-            const double a = -2.0 * M_PI * (double)(((int64_t)f1 * dd) % N) / (double)N;
-            dst[pc::block_pos(d, T)] = make_float2((float)(wv * std::cos(a)), (float)(wv * std::sin(a)));
+            const size_t j = (size_t)(((int64_t)f1 * dd) % N);
+            dst[pc::block_pos(d, T)] = make_float2((float)(wv * rc[j]), (float)(wv * rs[j]));
           }
         }
     float2* dcw = nullptr;
@@ -551,9 +558,15 @@ pc_status build_large1d(pc_plan p, int L, int R, const float* windows, const flo
   float2* Hd = nullptr;
   if ((st = p->alloc(&Hd, (size_t)m * N, &p->spectra_bytes))) return st;
   q.Hd = Hd;
-  if ((st = p->alloc(&q.Bws, (size_t)pairs * N, &p->workspace_bytes))) return st;
+  // slices for every call size up to the plan's (above 256 pairs there is one)
+  int64_t bs = pairs, ps = pairs;
+  for (int64_t c = std::min<int64_t>(pairs, 256); c > 0; --c) {
+    bs = std::max(bs, c * pc::fwd1d_large_groups(q, c));
+    ps = std::max(ps, c * pc::adj1d_large_groups(q, c));
+  }
+  if ((st = p->alloc(&q.Bws, (size_t)bs * N, &p->workspace_bytes))) return st;
   if ((st = p->alloc(&q.Vws, (size_t)pairs * N, &p->workspace_bytes))) return st;
-  if ((st = p->alloc(&q.Pws, (size_t)pairs * std::max<int64_t>(pstride, 1), &p->workspace_bytes))) return st;
+  if ((st = p->alloc(&q.Pws, (size_t)ps * std::max<int64_t>(pstride, 1), &p->workspace_bytes))) return st;
   DeviceTemp hd;
   if ((st = hd.upload(h, (size_t)m * N))) return st;
   hipError_t e = pc::launch_fold_fft(q, hd.get(), m, Hd, false, s);
@@ -1824,13 +1837,13 @@ pc_status create_plan(const pc_plan_desc& d, const float* windows, const float* 
   }
   if (st == PC_SUCCESS && path != 3) {  // sections hold their gradient planes in their sub-plans
     if (d.flags & PC_PLAN_GRADIENTS) {
-      // 1D: the backward's shares at the largest call, or the per-class accumulators (m x N); 2D: m planes
+      // 1D: the backward's shares, or the slices of the per-class accumulators (m x N each); 2D: m planes
       const int64_t pairs = (d.batch + 1) / 2;
       int64_t small = 0;
       if (path == 0)  // (the shares of dL/du are capped: calls below the largest may need the most)
         for (int64_t q = pairs; q > 0; q = pc::bwd1d_small_gu(p->s1.L, d.m, q) ? 0 : q - 1)
           small = std::max(small, pc::bwd1d_small_work(p->s1.L, d.m, q));
-      const int64_t n = path == 0 ? small : path == 1 ? (int64_t)d.m * d.n0 : d.m * d.n0 * (d.n1 / 2 + 1);
+      const int64_t n = path == 0 ? small : path == 1 ? (int64_t)pc::grad1d_large_groups(p->l1, pairs) * d.m * d.n0 : d.m * d.n0 * (d.n1 / 2 + 1);
       st = p->alloc(&p->grad_ws, (size_t)n, &p->workspace_bytes);
     }
   }
@@ -2401,7 +2414,10 @@ pc_status pc_backward(pc_plan p, const float* u, const float* gy, float* gu, voi
     e = pc::launch_bwd1d_small(p->s1, u, gy, gu, gs, batch, p->grad_ws, s, p->tr());
   } else {
     if (gspec) e = run_grad_spectra(p, u, gy, gs, batch, true, nullptr, s);
-    if (e == hipSuccess && gu) e = p->pconv ? run_forward(p, gy, gu, batch, s) : run_adjoint(p, gy, gu, batch, s);
+    if (e == hipSuccess && gu)
+      e = p->pconv                 ? run_forward(p, gy, gu, batch, s)
+          : p->path == 1 && gspec ? pc::launch_adj1d_large(p->l1, nullptr, gu, batch, s, p->tr())
+                                  : run_adjoint(p, gy, gu, batch, s);
   }
   if (gu || p->path < 2 || p->pconv)
     p->saved_state = 0;

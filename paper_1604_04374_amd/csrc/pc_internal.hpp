@@ -119,10 +119,20 @@ struct Large1D {
   const int* tile_off;       // N/256 + 1 entries
   const int* tile_items;
   // workspaces
-  float2* Bws;               // pairs x R x L (block layout)
+  float2* Bws;               // pairs x fwd1d_large_groups x R x L (block layout)
   float2* Vws;               // pairs x R x L (block layout)
-  float2* Pws;               // pairs x p_stride
+  float2* Pws;               // pairs x adj1d_large_groups x p_stride
 };
+// Term groups of the forward, class groups of the adjoint and pair groups of
+// the spectra gradient for a call of `pairs` pairs (slices of Bws, Pws and E).
+int fwd1d_large_groups(const Large1D& p, int64_t pairs);
+int adj1d_large_groups(const Large1D& p, int64_t pairs);
+int grad1d_large_groups(const Large1D& p, int64_t pairs);
+// points per thread of the inner transforms (6144: 12 rather than 24, twice
+// the wavefronts; us at 24 and 12: forward of 64 signals of 49152 samples, 16
+// terms, 105.7 and 83.8, of 98304 samples 444 and 190; 4096 and 8192 stay at
+// 16, where 8 is slower: one more exchange)
+constexpr int fourstep_points(int L) { return L == 6144 ? 12 : points_per_thread(L); }
 bool fourstep_variant_supported(int L, int R, int P);
 LaunchStatus launch_fold_fft(const Large1D& p, const float* xa, int64_t n_sig, float2* out, bool pairs, hipStream_t s,
                              Tracer* tr = nullptr);
@@ -132,6 +142,7 @@ LaunchStatus launch_conj(const float2* in, float2* out, int64_t n, hipStream_t s
 LaunchStatus launch_origin_phase1d(const Large1D& p, float2* Hd, hipStream_t s);
 LaunchStatus launch_fwd1d_large(const Large1D& p, const float* u, float* y, int64_t batch, hipStream_t s,
                                 Tracer* tr = nullptr);
+// v null: Vws holds the transform of v already (left by launch_grad1d_large)
 LaunchStatus launch_adj1d_large(const Large1D& p, const float* v, float* x, int64_t batch, hipStream_t s,
                                 Tracer* tr = nullptr);
 
@@ -390,6 +401,7 @@ int64_t bwd1d_small_work(int L, int m, int64_t pairs);
 bool bwd1d_small_gu(int L, int m, int64_t pairs);
 LaunchStatus launch_bwd1d_small(const Small1D& p, const float* u, const float* gy, float* gu, float2* gspec,
                                 int64_t batch, float2* work, hipStream_t s, Tracer* tr = nullptr);
+// E: grad1d_large_groups x m x N complex values; leaves the transform of gy in Vws
 LaunchStatus launch_grad1d_large(const Large1D& p, const float* u, const float* gy, float2* gspec, int64_t batch,
                                  float2* E, hipStream_t s, Tracer* tr = nullptr);
 LaunchStatus launch_spectra2d(const Plan2D& p, const float2* in, float2* out, bool import, hipStream_t s);

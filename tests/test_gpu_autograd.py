@@ -214,3 +214,26 @@ def test_small_backward_spreads_terms_and_pairs(n, m, batch):
         gu, gs = plan.backward(u[:1], gy[:1])
         assert rel_l2(gu.cpu().numpy(), ru[:1]) <= TOL
         assert rel_l2(gs.cpu().numpy(), grads.grad_spectra(p.u[:1].astype(np.float64), g[:1].astype(np.float64), w)) <= TOL
+
+
+@pytest.mark.parametrize("n,m,batch", [
+    (24576, 9, 5), (12288, 6, 1),      # terms, classes and pairs split over workgroups
+    (65536, 24, 3), (131072, 20, 2),   # two-chunk windows at 4096 and 8192 points per transform
+    (49152, 8, 40),                    # enough pairs that the forward is not split, the adjoint's classes are not
+    (98304, 4, 2),                     # windows longer than two inner lengths: several items per term
+])
+def test_fourstep_splits_over_workgroups(n, m, batch):
+    import torch
+    import paper_1604_04374_amd as pcm
+    p = wl.small_1d(n, m, 3 if m > 6 else 1, batch, seed=n + m, sigma_fn=wl.gen.c2_sigma)
+    g = np.random.default_rng(n).standard_normal(p.u.shape).astype(np.float32)
+    plan = pcm.Plan(p.w, p.h, batch=batch, gradients=True)
+    w, h = p.dense_windows(), p.h.astype(np.float64)
+    for b in sorted({batch, (batch + 1) // 2}):  # and a call smaller than the plan's batch
+        u64, g64 = p.u[:b].astype(np.float64), g[:b].astype(np.float64)
+        u, gy = torch.from_numpy(p.u[:b]).cuda(), torch.from_numpy(g[:b]).cuda()
+        assert rel_l2(plan.apply(u).cpu().numpy(), ex.apply_fft(u64, w, h)) <= TOL
+        gu, gs = plan.backward(u, gy)
+        assert rel_l2(gu.cpu().numpy(), grads.grad_u(g64, w, h)) <= TOL
+        assert rel_l2(gs.cpu().numpy(), grads.grad_spectra(u64, g64, w)) <= TOL
+        assert torch.equal(plan.apply_adjoint(gy), gu)
