@@ -9,139 +9,235 @@
 // The contraction W T^T (rows x n times n x m) is the one dense product of
 // the path: it runs on the matrix cores in FP32 (v_mfma_f32_16x16x4f32), split
 // along n into chunks whose partial sums are added in float64; the m x m
-// factorisations and the per-row solves are float64.
+// inverse or factorisation and the per-row solves are float64.
+#include <algorithm>
+
 #include "pc_internal.hpp"
 
 namespace pc {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// part[split][r][c] = sum over the split's chunk of j of A[r][j] B[c][j].
-// A: rows x K, B: cols x K, both row-major with K contiguous, K % 16 == 0,
-// 16-byte aligned rows.  Workgroup: 4 waves x GEMM_WAVE_ROWS rows, 32
-// columns; a wave holds GEMM_WAVE_ROWS / 16 row blocks x 2 column blocks of
-// 16 x 16 outputs, so each 16-byte load of B serves that many row blocks
-// (B, the windows, is re-read by every workgroup; A, the TVIR band, is
-// streamed once).  Each lane loads 4 consecutive k of its rows (and of its
-// two columns) and feeds them to 4 consecutive MFMA steps, so one 16-k step
-// of the loop covers k0 + 4g + s for lane group g < 4 and step s < 4 on both
-// operands alike.
+// part[seg][r][c] = sum over the segment's j of A[r][j] B[c][j], in float64
+// from FP32 sums of at most GEMM_CHUNK terms.  A: the rows x K TVIR band
+// followed by the cols x K windows themselves (their Gram matrix), B: the
+// windows; row-major with K contiguous, K % 16 == 0, 16-byte aligned rows.
+//
+// Bound by streaming the band from HBM once.  A workgroup (4 waves) takes
+// GEMM_ROWS rows and 32 columns and walks its segment in stages of GEMM_KT
+// samples: every row's stage is 256 contiguous bytes (16 lanes of 16 bytes;
+// loads of 64 bytes per row, straight into MFMA operands, reached 4.1 TB/s),
+// held in registers two stages ahead, then in one of two LDS buffers, where
+// 16-byte chunk c of row r sits at c ^ (r mod 16), so that the 16 rows of an
+// MFMA operand hit different banks.  48 KB of LDS: three workgroups per CU.
+// Lane (i, g) feeds 4 consecutive k of its row and columns to 4 MFMA steps,
+// the same k on both operands.  Workgroups of one segment are numbered
+// together, so that the windows' segment stays in every L2.  Measured (23595
+// lags x 65536 positions, 32 windows): 1517 us and 93 us for the Gram matrix
+// with 64-byte row loads, 1146 us (5.4 TB/s, the rate of a large copy) here
+// for both.
+constexpr int GEMM_CPR = GEMM_KT / 4;  // 16-byte chunks per row and stage
 __global__ __launch_bounds__(256) void k_gemm_nt_f32(const float* __restrict__ A, int64_t rows,
                                                      const float* __restrict__ B, int cols, int64_t K,
-                                                     float* __restrict__ part) {
-  constexpr int RT = GEMM_WAVE_ROWS / 16;  // row blocks per wave
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                                     int seg_stages, double* __restrict__ part) {
+  constexpr int AQ = GEMM_ROWS * GEMM_CPR / 256, BQ = GEMM_COLS * GEMM_CPR / 256;  // chunks per thread
+  static_assert(GEMM_CPR == 16 && GEMM_ROWS == 64 && GEMM_COLS == 32, "tile of the lane mapping below");
+  __shared__ floatx4 As[2][GEMM_ROWS * GEMM_CPR], Bs[2][GEMM_COLS * GEMM_CPR];
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = tid & 15, r = tid >> 4;  // load mapping: chunk c of rows r + 16 j
+  const int64_t band_tiles = (rows + GEMM_ROWS - 1) / GEMM_ROWS;
+  const bool gram = (int64_t)blockIdx.x >= band_tiles;
+  const int64_t t0 = (gram ? blockIdx.x - band_tiles : blockIdx.x) * GEMM_ROWS;  // first row of the tile
+  const int64_t have = gram ? cols : rows;
+  const int c0 = (int)blockIdx.y * GEMM_COLS;
+  const int64_t k_begin = (int64_t)blockIdx.z * seg_stages * GEMM_KT;
+  const int64_t k_left = K - k_begin;
+  const int ns = (int)(k_left < (int64_t)seg_stages * GEMM_KT ? (k_left + GEMM_KT - 1) / GEMM_KT : seg_stages);
+  // rows and columns past the last read the last one; their sums are not stored
+  const float* ap[AQ];
+  const float* bp[BQ];
+#pragma unroll
+  for (int j = 0; j < AQ; ++j) {
+    const int64_t row = t0 + r + 16 * j < have ? t0 + r + 16 * j : have - 1;
+    ap[j] = (gram ? B : A) + row * K + k_begin + 4 * c;
+  }
+#pragma unroll
+  for (int j = 0; j < BQ; ++j) {
+    const int col = c0 + r + 16 * j < cols ? c0 + r + 16 * j : cols - 1;
+    bp[j] = B + (int64_t)col * K + k_begin + 4 * c;
+  }
+  floatx4 ra0[AQ], rb0[BQ], ra1[AQ], rb1[BQ];
+  auto load = [&](floatx4(&a)[AQ], floatx4(&b)[BQ], int s) {
+    // K need not be whole stages: chunks past its end count as zero (and
+    // stages past the segment's last are loaded and not used)
+    const bool in = (int64_t)s * GEMM_KT + 4 * c < k_left;
+    const int64_t o = in ? (int64_t)s * GEMM_KT : 0;
+#pragma unroll
+    for (int j = 0; j < AQ; ++j) a[j] = *reinterpret_cast<const floatx4*>(ap[j] + o);
+#pragma unroll
+    for (int j = 0; j < BQ; ++j) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(bp[j] + o);
+      b[j] = in ? v : floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  auto put = [&](int buf, const floatx4(&a)[AQ], const floatx4(&b)[BQ]) {
+#pragma unroll
+    for (int j = 0; j < AQ; ++j) As[buf][(r + 16 * j) * GEMM_CPR + (c ^ r)] = a[j];  // (r + 16 j) mod 16 = r
+#pragma unroll
+    for (int j = 0; j < BQ; ++j) Bs[buf][(r + 16 * j) * GEMM_CPR + (c ^ r)] = b[j];
+  };
   const int g = lane >> 4, li = lane & 15;
-  const int64_t r0 = (int64_t)blockIdx.x * GEMM_ROWS + (int64_t)wave * GEMM_WAVE_ROWS;
-  const int ca = blockIdx.y * GEMM_COLS + li, cb = ca + 16;
-  const bool aok = ca < cols, bok = cb < cols;
-  const int64_t k_begin = (int64_t)blockIdx.z * GEMM_CHUNK;
-  const int64_t k_end = k_begin + GEMM_CHUNK < K ? k_begin + GEMM_CHUNK : K;
-  // out-of-range rows and columns read row 0 (valid memory) and are zeroed
-  // by a factor, so that every load is one unconditional 16-byte access
-  const float4* Ar[RT];
-  float fa[RT];
+  floatx4 acc0{0.f, 0.f, 0.f, 0.f}, acc1{0.f, 0.f, 0.f, 0.f};
+  double sum0[4] = {0., 0., 0., 0.}, sum1[4] = {0., 0., 0., 0.};
+  auto compute = [&](int buf) {
+    const floatx4* as = As[buf] + (16 * wave + li) * GEMM_CPR;
+    const floatx4* b0 = Bs[buf] + li * GEMM_CPR;
+    const floatx4* b1 = b0 + 16 * GEMM_CPR;
 #pragma unroll
-  for (int b = 0; b < RT; ++b) {
-    const int64_t r = r0 + 16 * b + li;
-    const bool rok = r < rows;
-    Ar[b] = reinterpret_cast<const float4*>(A + (rok ? r : 0) * K);
-    fa[b] = rok ? 1.f : 0.f;
-  }
-  const float4* Ba = reinterpret_cast<const float4*>(B + (int64_t)(aok ? ca : 0) * K);
-  const float4* Bb = reinterpret_cast<const float4*>(B + (int64_t)(bok ? cb : 0) * K);
-  const float fx = aok ? 1.f : 0.f, fy = bok ? 1.f : 0.f;
-  auto scale = [](float4 v, float f) { return make_float4(v.x * f, v.y * f, v.z * f, v.w * f); };
-  floatx4 acc0[RT], acc1[RT];
-#pragma unroll
-  for (int b = 0; b < RT; ++b) {
-    acc0[b] = floatx4{0.f, 0.f, 0.f, 0.f};
-    acc1[b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  }
-  // operands of step k0 + 16 load while the MFMAs of step k0 issue
-  int64_t q = (k_begin >> 2) + g;  // float4 index of k0 + 4g
-  float4 an[RT];
-#pragma unroll
-  for (int b = 0; b < RT; ++b) an[b] = Ar[b][q];
-  float4 xn = Ba[q], yn = Bb[q];
-  for (int64_t k0 = k_begin; k0 < k_end; k0 += 16) {
-    float4 a[RT];
-#pragma unroll
-    for (int b = 0; b < RT; ++b) a[b] = scale(an[b], fa[b]);
-    const float4 x = scale(xn, fx), y = scale(yn, fy);
-    q += 4;
-    if (k0 + 16 < k_end) {
-#pragma unroll
-      for (int b = 0; b < RT; ++b) an[b] = Ar[b][q];
-      xn = Ba[q];
-      yn = Bb[q];
+    for (int q = 0; q < GEMM_CPR / 4; ++q) {
+      const int pos = (4 * q + g) ^ li;
+      const floatx4 a = as[pos], x = b0[pos], y = b1[pos];
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, x.x, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, y.x, acc1, 0, 0, 0);
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, x.y, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, y.y, acc1, 0, 0, 0);
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, x.z, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, y.z, acc1, 0, 0, 0);
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, x.w, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, y.w, acc1, 0, 0, 0);
     }
+  };
+  auto flush = [&]() {
 #pragma unroll
-    for (int b = 0; b < RT; ++b) {
-      acc0[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b].x, x.x, acc0[b], 0, 0, 0);
-      acc1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b].x, y.x, acc1[b], 0, 0, 0);
-      acc0[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b].y, x.y, acc0[b], 0, 0, 0);
-      acc1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b].y, y.y, acc1[b], 0, 0, 0);
-      acc0[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b].z, x.z, acc0[b], 0, 0, 0);
-      acc1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b].z, y.z, acc1[b], 0, 0, 0);
-      acc0[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b].w, x.w, acc0[b], 0, 0, 0);
-      acc1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b].w, y.w, acc1[b], 0, 0, 0);
+    for (int i = 0; i < 4; ++i) {
+      sum0[i] += (double)acc0[i];
+      sum1[i] += (double)acc1[i];
+      acc0[i] = acc1[i] = 0.f;
     }
-  }
-  // output block element (i, j) sits in lane j + 16 (i / 4), item i % 4
-  float* P = part + (int64_t)blockIdx.z * rows * cols;
-#pragma unroll
-  for (int b = 0; b < RT; ++b)
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int64_t row = r0 + 16 * b + 4 * g + it;
-      if (row < rows) {
-        if (aok) P[row * cols + ca] = acc0[b][it];
-        if (bok) P[row * cols + cb] = acc1[b][it];
-      }
-    }
-}
-
-// out[i] = sum_s part[s][i] in float64
-__global__ __launch_bounds__(256) void k_sum_splits(const float* __restrict__ part, int splits, int64_t n,
-                                                    double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double s = 0.0;
-  for (int t = 0; t < splits; ++t) s += (double)part[(int64_t)t * n + i];
-  out[i] = s;
-}
-
-// In-place Cholesky G = L L^T (lower triangle, m <= CONSTRUCT_MAX_M), one
-// workgroup; *fail = 1 if a pivot is not above 1e-12 of its diagonal entry
-// (the windows are numerically dependent).
-__global__ __launch_bounds__(256) void k_cholesky(double* __restrict__ G, int m, int* __restrict__ fail) {
-  __shared__ double S[CONSTRUCT_MAX_M * CONSTRUCT_MAX_M];
-  __shared__ int bad;
-  for (int i = threadIdx.x; i < m * m; i += blockDim.x) S[i] = G[i];
-  if (threadIdx.x == 0) bad = 0;
+  };
+  // stage s: stage s + 1 goes from its registers to the other buffer, whose
+  // readers passed the barrier before; stage s + 3 is loaded in their place
+  auto stage = [&](int s, floatx4(&a)[AQ], floatx4(&b)[BQ], int buf) {
+    put(buf ^ 1, a, b);
+    load(a, b, s + 3);
+    compute(buf);
+    if ((s + 1) % (GEMM_CHUNK / GEMM_KT) == 0) flush();
+    __syncthreads();
+  };
+  load(ra0, rb0, 0);
+  load(ra1, rb1, 1);
+  put(0, ra0, rb0);
+  load(ra0, rb0, 2);
   __syncthreads();
-  for (int j = 0; j < m; ++j) {
-    if (threadIdx.x == 0) {
-      const double g = S[j * m + j];
-      double d = g;
-      for (int p = 0; p < j; ++p) d -= S[j * m + p] * S[j * m + p];
-      if (!(d > 1e-12 * g)) {
-        bad = 1;
-        d = 1.0;
-      }
-      S[j * m + j] = sqrt(d);
+  for (int s = 0; s < ns; s += 2) {
+    stage(s, ra1, rb1, 0);
+    if (s + 1 < ns) stage(s + 1, ra0, rb0, 1);
+  }
+  flush();
+  // output block element (i, j) sits in lane j + 16 (i / 4), item i % 4
+  double* P = part + ((int64_t)blockIdx.z * (rows + cols) + (gram ? rows : 0)) * cols;
+  const int ca = c0 + li, cb = ca + 16;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t row = t0 + 16 * wave + 4 * g + i;
+    if (row < have) {
+      if (ca < cols) P[row * cols + ca] = sum0[i];
+      if (cb < cols) P[row * cols + cb] = sum1[i];
+    }
+  }
+}
+
+// Inverse of the Gram matrix (m x m, m <= CONSTRUCT_MAX_M; the last m rows of
+// the contraction, summed over its segments) by Gauss-Jordan elimination in
+// LDS, one workgroup: every step updates the whole matrix in parallel (the
+// triangular factorisation and solves it replaces were chains of dependent
+// LDS reads: 40 us at m = 32, 24 here; 38 with 256 threads).  Without exchanges, as the matrix
+// is symmetric positive definite; step p's pivot is the one of its Cholesky
+// factorisation.  *fail = 1 if a pivot is not above 1e-12 of its diagonal
+// entry (the windows are numerically dependent).
+__global__ __launch_bounds__(1024) void k_gram_inverse(const double* __restrict__ part, int segs, int64_t rows, int m,
+                                                       double* __restrict__ inv, int* __restrict__ fail) {
+  __shared__ double S[CONSTRUCT_MAX_M * CONSTRUCT_MAX_M];
+  __shared__ double diag[CONSTRUCT_MAX_M];
+  const int nt = (int)blockDim.x, rs = nt >> 5;
+  const int ti = (int)threadIdx.x >> 5, tj = (int)threadIdx.x & 31;  // element (ti + rs a, tj + 32 b)
+  for (int i = ti; i < m; i += rs)
+    for (int j = tj; j < m; j += 32) {
+      const double* g = part + (rows * m + (int64_t)i * m + j);
+      double v = 0.0;
+#pragma unroll 4
+      for (int q = 0; q < segs; ++q) v += g[(int64_t)q * (rows + m) * m];
+      S[i * m + j] = v;
+      if (i == j) diag[i] = v;
+    }
+  int bad = 0;
+  __syncthreads();
+  for (int p = 0; p < m; ++p) {
+    double d = S[p * m + p];
+    if (!(d > 1e-12 * diag[p])) {
+      bad = 1;
+      d = 1.0;
+    }
+    const double rd = 1.0 / d;
+    for (int i = ti; i < m; i += rs) {
+      const double f = S[i * m + p] * rd;
+      for (int j = tj; j < m; j += 32)
+        if (i != p && j != p) S[i * m + j] -= f * S[p * m + j];
     }
     __syncthreads();
-    for (int i = j + 1 + threadIdx.x; i < m; i += blockDim.x) {
-      double v = S[i * m + j];
-      for (int p = 0; p < j; ++p) v -= S[i * m + p] * S[j * m + p];
-      S[i * m + j] = v / S[j * m + j];
+    for (int i = (int)threadIdx.x; i < m; i += nt) {
+      if (i == p) {
+        S[p * m + p] = rd;
+      } else {
+        S[i * m + p] *= -rd;
+        S[p * m + i] *= rd;
+      }
     }
     __syncthreads();
   }
-  for (int i = threadIdx.x; i < m * m; i += blockDim.x) G[i] = S[i];
+  for (int i = (int)threadIdx.x; i < m * m; i += nt) inv[i] = S[i];
   if (threadIdx.x == 0) *fail = bad;
+}
+
+// h[k][lags[r]] = sum_j inv[k][j] b_r[j] / n, b_r the contraction's row r
+// summed over its segments (float64): PROJECT_ROWS rows per workgroup, their
+// right-hand sides in LDS, a wave per k with a row per lane (consecutive lags
+// mostly, so the stores are contiguous; inv is read uniformly).  One thread
+// per row with its vector in memory took 105 us (23595 rows, m = 32) after
+// 33 us of summing; 15 us here, sums included.
+constexpr int PROJECT_ROWS = 64;
+__global__ __launch_bounds__(256) void k_project_solve(const double* __restrict__ part, int segs, int64_t rows, int m,
+                                                       const double* __restrict__ inv,
+                                                       const int64_t* __restrict__ lags, int64_t n,
+                                                       float* __restrict__ h) {
+  __shared__ double b[CONSTRUCT_MAX_M * (PROJECT_ROWS + 1)];
+  const int64_t r0 = (int64_t)blockIdx.x * PROJECT_ROWS;
+  for (int j = (int)threadIdx.x & 31; j < m; j += 32) {
+    constexpr int PER = PROJECT_ROWS / 8;
+    double v[PER];
+#pragma unroll
+    for (int a = 0; a < PER; ++a) v[a] = 0.0;
+    for (int q = 0; q < segs; ++q) {
+#pragma unroll
+      for (int a = 0; a < PER; ++a) {  // rows past the last read the last one
+        const int64_t r = r0 + (threadIdx.x >> 5) + 8 * a;
+        v[a] += part[((int64_t)q * (rows + m) + (r < rows ? r : rows - 1)) * m + j];
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < PER; ++a) b[j * (PROJECT_ROWS + 1) + (threadIdx.x >> 5) + 8 * a] = v[a];
+  }
+  __syncthreads();
+  const int lane = (int)threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (r0 + lane >= rows) return;
+  const int64_t l = lags[r0 + lane];
+  const double inv_n = 1.0 / (double)n;
+  for (int k = wave; k < m; k += 4) {
+    double v = 0.0;
+    for (int j = 0; j < m; ++j) v = fma(inv[k * m + j], b[j * (PROJECT_ROWS + 1) + lane], v);
+    h[(int64_t)k * n + l] = (float)(v * inv_n);
+  }
 }
 
 // In-place LU with partial pivoting of E (m x m): L unit lower, U upper,
@@ -201,12 +297,10 @@ __global__ __launch_bounds__(256) void k_lu(double* __restrict__ E, int m, int* 
   if (threadIdx.x == 0) *fail = bad;
 }
 
-// One thread per TVIR row r: solve for c(x_r) in float64 in the row's slot of
+// One thread per TVIR row r: solve E c = t in float64 in the row's slot of
 // `work` (m values), starting from the row of `src`, and write
-// h[k][lags[r]] = c_k / n.
-//   LU = false: F is the Cholesky factor L of the Gram matrix (L, then L^T).
-//   LU = true:  F holds unit-lower L and U with the row permutation perm.
-template <bool LU>
+// h[k][lags[r]] = c_k / n.  F holds unit-lower L and U with the row
+// permutation perm.
 __global__ __launch_bounds__(256) void k_row_solve(const double* __restrict__ F, const int* __restrict__ perm, int m,
                                                    const double* __restrict__ src, double* __restrict__ work,
                                                    int64_t rows, const int64_t* __restrict__ lags, int64_t n,
@@ -218,29 +312,16 @@ __global__ __launch_bounds__(256) void k_row_solve(const double* __restrict__ F,
   if (r >= rows) return;
   const double* a = src + r * m;
   double* b = work + r * m;
-  if (LU) {
-    for (int i = 0; i < m; ++i) b[i] = a[perm[i]];
-    for (int i = 0; i < m; ++i) {  // L y = P t, L unit lower
-      double v = b[i];
-      for (int p = 0; p < i; ++p) v -= S[i * m + p] * b[p];
-      b[i] = v;
-    }
-    for (int i = m - 1; i >= 0; --i) {  // U c = y
-      double v = b[i];
-      for (int p = i + 1; p < m; ++p) v -= S[i * m + p] * b[p];
-      b[i] = v / S[i * m + i];
-    }
-  } else {
-    for (int i = 0; i < m; ++i) {  // L y = b
-      double v = a[i];
-      for (int p = 0; p < i; ++p) v -= S[i * m + p] * b[p];
-      b[i] = v / S[i * m + i];
-    }
-    for (int i = m - 1; i >= 0; --i) {  // L^T c = y
-      double v = b[i];
-      for (int p = i + 1; p < m; ++p) v -= S[p * m + i] * b[p];
-      b[i] = v / S[i * m + i];
-    }
+  for (int i = 0; i < m; ++i) b[i] = a[perm[i]];
+  for (int i = 0; i < m; ++i) {  // L y = P t, L unit lower
+    double v = b[i];
+    for (int p = 0; p < i; ++p) v -= S[i * m + p] * b[p];
+    b[i] = v;
+  }
+  for (int i = m - 1; i >= 0; --i) {  // U c = y
+    double v = b[i];
+    for (int p = i + 1; p < m; ++p) v -= S[i * m + p] * b[p];
+    b[i] = v / S[i * m + i];
   }
   const int64_t l = lags[r];
   const double inv_n = 1.0 / (double)n;
@@ -278,21 +359,36 @@ __global__ __launch_bounds__(256) void k_flip(const float* __restrict__ in, floa
 
 static inline unsigned blocks_of(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-LaunchStatus launch_gemm_nt(const float* A, int64_t rows, const float* B, int cols, int64_t K, float* part,
-                            hipStream_t s) {
-  const dim3 grid((unsigned)((rows + GEMM_ROWS - 1) / GEMM_ROWS), (unsigned)((cols + GEMM_COLS - 1) / GEMM_COLS),
-                  (unsigned)gemm_splits(K));
-  hipLaunchKernelGGL(k_gemm_nt_f32, grid, dim3(256), 0, s, A, rows, B, cols, K, part);
-  return hipGetLastError();
+// Stages per segment and segments of the contraction: about five workgroups
+// per CU (enough that the last round costs little), as few segments as that
+// needs.
+static int gemm_seg_stages(int64_t rows, int m, int64_t K) {
+  const int64_t tiles = ((rows + GEMM_ROWS - 1) / GEMM_ROWS + (m + GEMM_ROWS - 1) / GEMM_ROWS) *
+                        ((m + GEMM_COLS - 1) / GEMM_COLS);
+  const int64_t stages = (K + GEMM_KT - 1) / GEMM_KT;
+  const int64_t segs = std::min(stages, (1280 + tiles - 1) / tiles);
+  return (int)((stages + segs - 1) / segs);
 }
 
-LaunchStatus launch_sum_splits(const float* part, int splits, int64_t n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_splits, dim3(blocks_of(n)), dim3(256), 0, s, part, splits, n, out);
-  return hipGetLastError();
+int gemm_segments(int64_t rows, int m, int64_t K) {
+  const int64_t per = gemm_seg_stages(rows, m, K), stages = (K + GEMM_KT - 1) / GEMM_KT;
+  return (int)((stages + per - 1) / per);
 }
 
-LaunchStatus launch_cholesky(double* G, int m, int* fail, hipStream_t s) {
-  hipLaunchKernelGGL(k_cholesky, dim3(1), dim3(256), 0, s, G, m, fail);
+LaunchStatus launch_project(const float* tvir, int64_t rows, const float* windows, int m, int64_t n, double* part,
+                            double* inv, int* fail, const int64_t* lags, float* h, hipStream_t s) {
+  const int segs = gemm_segments(rows, m, n);
+  const dim3 grid((unsigned)((rows + GEMM_ROWS - 1) / GEMM_ROWS + (m + GEMM_ROWS - 1) / GEMM_ROWS),
+                  (unsigned)((m + GEMM_COLS - 1) / GEMM_COLS), (unsigned)segs);
+  hipLaunchKernelGGL(k_gemm_nt_f32, grid, dim3(256), 0, s, tvir, rows, windows, m, n, gemm_seg_stages(rows, m, n),
+                     part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_gram_inverse, dim3(1), dim3(1024), 0, s, part, segs, rows, m, inv, fail);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_project_solve, dim3((unsigned)((rows + PROJECT_ROWS - 1) / PROJECT_ROWS)), dim3(256), 0, s, part,
+                     segs, rows, m, inv, lags, n, h);
   return hipGetLastError();
 }
 
@@ -301,14 +397,9 @@ LaunchStatus launch_lu(double* E, int m, int* perm, int* fail, hipStream_t s) {
   return hipGetLastError();
 }
 
-LaunchStatus launch_row_solve(bool lu, const double* F, const int* perm, int m, const double* src, double* work,
-                              int64_t rows, const int64_t* lags, int64_t n, float* h, hipStream_t s) {
-  if (lu)
-    hipLaunchKernelGGL(k_row_solve<true>, dim3(blocks_of(rows)), dim3(256), 0, s, F, perm, m, src, work, rows, lags,
-                       n, h);
-  else
-    hipLaunchKernelGGL(k_row_solve<false>, dim3(blocks_of(rows)), dim3(256), 0, s, F, perm, m, src, work, rows,
-                       lags, n, h);
+LaunchStatus launch_row_solve(const double* F, const int* perm, int m, const double* src, double* work, int64_t rows,
+                              const int64_t* lags, int64_t n, float* h, hipStream_t s) {
+  hipLaunchKernelGGL(k_row_solve, dim3(blocks_of(rows)), dim3(256), 0, s, F, perm, m, src, work, rows, lags, n, h);
   return hipGetLastError();
 }
 

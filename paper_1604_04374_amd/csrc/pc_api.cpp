@@ -2510,25 +2510,16 @@ pc_status pc_construct_project(int64_t n, int32_t m, int64_t rows, const float* 
   if ((reinterpret_cast<uintptr_t>(tvir) | reinterpret_cast<uintptr_t>(windows)) % 16)
     return fail(PC_ERROR_INVALID_VALUE, "tvir and windows must be 16-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int splits = pc::gemm_splits(n);
   CallTemps t;
-  float *part = nullptr, *gpart = nullptr;
-  double *rhs = nullptr, *work = nullptr, *G = nullptr;
+  double *part = nullptr, *inv = nullptr;
   int64_t* dl = nullptr;
   int* dfail = nullptr;
-  if ((st = t.alloc(&part, (size_t)splits * rows * m)) || (st = t.alloc(&gpart, (size_t)splits * m * m)) ||
-      (st = t.alloc(&rhs, (size_t)rows * m)) || (st = t.alloc(&work, (size_t)rows * m)) ||
-      (st = t.alloc(&G, (size_t)m * m)) || (st = t.alloc(&dfail, 1)) || (st = t.upload(&dl, lags, (size_t)rows)) ||
+  if ((st = t.alloc(&part, (size_t)pc::gemm_segments(rows, m, n) * (size_t)((rows + m) * m))) ||
+      (st = t.alloc(&inv, (size_t)m * m)) || (st = t.alloc(&dfail, 1)) || (st = t.upload(&dl, lags, (size_t)rows)) ||
       (st = t.commit(s)))
     return st;
   hipError_t e = pc::launch_fill_zero(h, (int64_t)m * n, s);
-  // right-hand sides W T(x, .)^T for every row, and the Gram matrix W W^T
-  if (e == hipSuccess) e = pc::launch_gemm_nt(tvir, rows, windows, m, n, part, s);
-  if (e == hipSuccess) e = pc::launch_sum_splits(part, splits, rows * m, rhs, s);
-  if (e == hipSuccess) e = pc::launch_gemm_nt(windows, m, windows, m, n, gpart, s);
-  if (e == hipSuccess) e = pc::launch_sum_splits(gpart, splits, (int64_t)m * m, G, s);
-  if (e == hipSuccess) e = pc::launch_cholesky(G, m, dfail, s);
-  if (e == hipSuccess) e = pc::launch_row_solve(false, G, nullptr, m, rhs, work, rows, dl, n, h, s);
+  if (e == hipSuccess) e = pc::launch_project(tvir, rows, windows, m, n, part, inv, dfail, dl, h, s);
   if (e != hipSuccess) return fail_hip(e, "pc_construct_project launch");
   return finish_construct(s, dfail, "pc_construct_project");
 }
@@ -2559,7 +2550,7 @@ pc_status pc_construct_interpolate(int64_t n, int32_t m, int64_t rows, const flo
   if (e == hipSuccess) e = pc::launch_node_matrix(windows, m, n, dn, E, s);
   if (e == hipSuccess) e = pc::launch_lu(E, m, perm, dfail, s);
   if (e == hipSuccess) e = pc::launch_to_double(samples, rows * m, src, s);
-  if (e == hipSuccess) e = pc::launch_row_solve(true, E, perm, m, src, work, rows, dl, n, h, s);
+  if (e == hipSuccess) e = pc::launch_row_solve(E, perm, m, src, work, rows, dl, n, h, s);
   if (e != hipSuccess) return fail_hip(e, "pc_construct_interpolate launch");
   return finish_construct(s, dfail, "pc_construct_interpolate");
 }

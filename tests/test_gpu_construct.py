@@ -60,6 +60,29 @@ def test_projection_matches_oracle(n, m, deg):
     assert np.all(h[:, unlisted] == 0)
 
 
+@pytest.mark.parametrize("n,m,rows", [
+    (16, 1, 1), (80, 3, 65), (2064, 33, 64), (4112, 49, 127),   # one row, ragged tiles of rows, columns and samples
+    (8192, 128, 300), (65536, 5, 1500)])                        # the most windows; sums longer than one FP32 chunk per segment
+def test_projection_tiles(n, m, rows):
+    """Random rows and windows (a well-conditioned Gram matrix).  An FP32 sum
+    of 2048 products of independent signs errs by about 2048^(1/2) 2^-24 of
+    its size, the solve by the condition number times that."""
+    import torch
+    import paper_1604_04374_amd as pcm
+    rng = np.random.default_rng(n + m)
+    T = rng.standard_normal((rows, n)).astype(np.float32)
+    W = rng.standard_normal((m, n)).astype(np.float32)
+    lags = rng.permutation(n)[:rows] if rows <= n else None
+    h = pcm.construct_project(torch.from_numpy(T).cuda(), lags, torch.from_numpy(W).cuda()).cpu().numpy()
+    G = W.astype(np.float64) @ W.astype(np.float64).T
+    ref = np.zeros((m, n))
+    ref[:, lags] = np.linalg.solve(G, W.astype(np.float64) @ T.astype(np.float64).T) / n
+    assert rel_l2(h, ref) <= 2 * 2048 ** 0.5 * 2.0 ** -24 * max(np.linalg.cond(G), 1.0)
+    rest = np.ones(n, bool)
+    rest[lags] = False
+    assert not h[:, rest].any()
+
+
 @pytest.mark.parametrize("n,m,deg", [(1024, 8, 1), (4096, 16, 3), (16384, 32, 3)])
 def test_interpolation_matches_oracle(n, m, deg):
     import torch
