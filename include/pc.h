@@ -465,7 +465,7 @@ enum {
   PC_BATCH_NO_GRAPH = 1u,
   /* Persistent passes: one launch per pass (rows in, forward column passes
    * and column transforms, adjoint column passes, rows out) and length group
-   * (points per thread 8: 64, 128; 12: 96, 192, 384; 16: 256, 512) instead
+   * (64, 128; 96, 192, 384; 256, 512 points) instead
    * of one launch per pass and transform length: every block of the pass
    * over all instances of the group's lengths is a work item of a list
    * (longest transforms first) that the launch's workgroups walk with a grid

@@ -107,9 +107,16 @@ __device__ __forceinline__ int opaque(int x) {
 // ---------------------------------------------------------------------------
 
 // Row pairs per workgroup: as many as LDS allows (transform buffers plus the
-// twiddle table within 156 KiB), at most 8 (tiles of 16 rows).
+// twiddle table within 156 KiB), at most 8 (tiles of 16 rows: whole 128-byte
+// lines of the spectral planes), at most 1024 threads.  From 1024 points on
+// smaller tiles, which keep two or more workgroups per CU, with neighbouring
+// tiles on one XCD (xcd_major_blocks), whose L2 joins their parts of a line
+// (us per forward / adjoint, 16-row tiles -> here: 1024 x 1024 51.0 / 53.8 ->
+// 50.5 / 45.6, 1536 x 1536 88.0 / 80.8 -> 77.5 / 71.4, 2048 x 2048 157.8 /
+// 156.3 -> 151.0 / 132.6).
 constexpr int row_pairs_per_block(int L2) {
-  int g = 8;
+  int g = L2 >= 2048 ? 2 : L2 >= 1024 ? 4 : 8;
+  while (g > 1 && g * fft_threads(L2) > 1024) g /= 2;
   while (g > 1 && (g * (L2 + L2 / PAD) + L2) * 8 > 156 * 1024) g /= 2;
   return g;
 }
@@ -127,6 +134,13 @@ constexpr int row_slot_len() {
 // Orders the accesses of one transform slot to its own LDS region: a
 // wavefront barrier when the slot's T threads lie in one wavefront (whose
 // LDS operations complete in program order), else a workgroup barrier.
+template <int T>
+__device__ __forceinline__ bool idle_wave(int f2raw, int c, int H2) {
+  // the wave's first slot is past the last column, so all its slots are
+  // (transforms that share a wavefront use no workgroup barrier)
+  if constexpr (T <= 64 && 64 % T == 0) return f2raw - c % (64 / T) >= H2;
+  return false;
+}
 template <int T>
 __device__ __forceinline__ void slot_sync() {
   if constexpr (T <= 64 && 64 % T == 0)
@@ -417,8 +431,10 @@ __device__ __forceinline__ void rows_inv_store(const RowJob& jb, float* __restri
 // transformed (latency hidden inside the workgroup, for a tile's share of
 // registers per thread; see rows_inv_pipe for when that pays).  ONE: every
 // job of the launch has one plane (nq = 1), so no sum is carried across a
-// transform (fewer registers, one more wave per SIMD at 384 points).
-template <int L2, int G, bool PIPE, bool ONE = false>
+// transform (fewer registers, one more wave per SIMD at 384 points).  SUM
+// (with ONE): no job has a window; its planes are added as the tile is
+// loaded, and their sum is transformed once.
+template <int L2, int G, bool PIPE, bool ONE = false, bool SUM = false>
 __device__ __forceinline__ void rows_inv_body(const RowJob* __restrict__ jobs, const BlockRef bm,
                                               float* __restrict__ y_arg, float2* __restrict__ lds,
                                               float2* __restrict__ twl, const float2* __restrict__ tw,
@@ -478,6 +494,32 @@ __device__ __forceinline__ void rows_inv_body(const RowJob* __restrict__ jobs, c
           if (ch < CH) nxt[i] = gld2(src, tile_src(ch));
         }
       }
+    } else if constexpr (SUM) {
+      constexpr int PS = (CH + NT - 1) / NT;
+      float4 sum[PS];
+#pragma unroll
+      for (int i = 0; i < PS; ++i) {
+        const int ch = tid + i * NT;
+        if (ch < CH) sum[i] = gld2(src0, tile_src(ch));
+      }
+      for (int g = 1; g < jb.nq; ++g) {
+        const float2* src = src0 + (int64_t)g * jb.q_stride;
+        float4 v[PS];
+#pragma unroll
+        for (int i = 0; i < PS; ++i) {
+          const int ch = tid + i * NT;
+          if (ch < CH) v[i] = gld2(src, tile_src(ch));
+        }
+#pragma unroll
+        for (int i = 0; i < PS; ++i)
+          sum[i] = make_float4(sum[i].x + v[i].x, sum[i].y + v[i].y, sum[i].z + v[i].z, sum[i].w + v[i].w);
+      }
+#pragma unroll
+      for (int i = 0; i < PS; ++i) {
+        const int ch = tid + i * NT;
+        if (ch < CH) tl[ch] = sum[i];
+      }
+      __syncthreads();
     } else {
       tile_to_lds<L2, G>(src0 + (int64_t)q * jb.q_stride, N1, lds, opaque(tid));
       __syncthreads();
@@ -488,7 +530,7 @@ __device__ __forceinline__ void rows_inv_body(const RowJob* __restrict__ jobs, c
   rows_inv_store<L2>(jb, yout, img, r, t, sa, sb, acc);
 }
 
-template <int L2, int G, bool PIPE, bool ONE = false>
+template <int L2, int G, bool PIPE, bool ONE = false, bool SUM = false>
 __global__ __launch_bounds__(G * fft_threads(L2)) void k_rows_inv(
     const RowJob* __restrict__ jobs, const BlockRef* __restrict__ bmap, float* __restrict__ y_arg,
     const float2* __restrict__ tw, int64_t img_limit) {
@@ -497,7 +539,7 @@ __global__ __launch_bounds__(G * fft_threads(L2)) void k_rows_inv(
   __shared__ float rfac[2 * G];
   const BlockRef bm = bmap[blockIdx.x];
   if (bm.img >= img_limit) return;  // uniform over the workgroup
-  rows_inv_body<L2, G, PIPE, ONE>(jobs, bm, y_arg, lds, twl, tw, rfac, threadIdx.x);
+  rows_inv_body<L2, G, PIPE, ONE, SUM>(jobs, bm, y_arg, lds, twl, tw, rfac, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -506,9 +548,12 @@ __global__ __launch_bounds__(G * fft_threads(L2)) void k_rows_inv(
 
 // Forward column pass for the term group bm.q: the group takes the column
 // factors q in [q0, q1) and, for each, every row factor k1 (the column of
-// src_q is loaded once and reused for all of them).  ngroups == 1: the
-// inverse column transform of the sum is written to dst; otherwise the
-// partial spectrum goes to part[group] for k_cols_sum_inv.
+// src_q is loaded once and reused for all of them).  The inverse column
+// transform of the group's sum is written to dst or, with several groups, to
+// part[group]: by linearity the row-inverse pass adds the groups' planes, and
+// no pass of its own adds their spectra (measured at 1024 x 1024, four
+// groups: that pass took 7.6 us).  With one column factor per group part may
+// be src itself: every thread writes the entries it has read.
 template <int L1, bool LATE, bool KEEP>
 __device__ __forceinline__ void cols_fwd_body(const ColJob* __restrict__ jobs, const BlockRef bm,
                                               float2* __restrict__ lds, float2* __restrict__ twl,
@@ -545,6 +590,7 @@ __device__ __forceinline__ void cols_fwd_body(const ColJob* __restrict__ jobs, c
   // the first column's loads go out before the twiddles are committed
   if (q0 < q1) load_col(q0);
   ts.commit(twl, tid);
+  if (idle_wave<T>(f2raw, c, H2)) return;
   for (int q = q0; q < q1; ++q) {
     if (q > q0) load_col(q);
     for (int k1 = 0; k1 < nk1; ++k1) {
@@ -580,21 +626,15 @@ __device__ __forceinline__ void cols_fwd_body(const ColJob* __restrict__ jobs, c
       for (int e = 0; e < P; ++e) acc[e] = cfma(acc[e], LATE ? gld(Hk, t + T * e) : hv[e], v[e]);
     }
   }
-  if (ngroups == 1) {
-    fft_wv<L1, P, true, SYNC_WAVE>(acc, my, twl, t);
-    if (valid) {
-      // rows t + T e < nvalid_out are stored (the rows the row-inverse pass reads)
-      const int nvo = jb.nvalid_out == 0 ? L1 : jb.nvalid_out;
-      const int no = nvo > t ? (nvo - t + T - 1) / T : 0;
-      float2* dst = jb.dst + img * plane + (int64_t)f2 * L1;
+  fft_wv<L1, P, true, SYNC_WAVE>(acc, my, twl, t);
+  if (valid) {
+    // rows t + T e < nvalid_out are stored (the rows the row-inverse pass reads)
+    const int nvo = jb.nvalid_out == 0 ? L1 : jb.nvalid_out;
+    const int no = nvo > t ? (nvo - t + T - 1) / T : 0;
+    float2* dst = (ngroups == 1 ? jb.dst : jb.part + g * jb.part_stride) + img * plane + (int64_t)f2 * L1;
 #pragma unroll
-      for (int e = 0; e < P; ++e)
-        if (e < no) gst(dst, t + T * e, acc[e]);
-    }
-  } else if (valid) {
-    float2* dst = jb.part + g * jb.part_stride + img * plane + (int64_t)f2 * L1;
-#pragma unroll
-    for (int e = 0; e < P; ++e) gst(dst, t + T * e, acc[e]);
+    for (int e = 0; e < P; ++e)
+      if (e < no) gst(dst, t + T * e, acc[e]);
   }
 }
 
@@ -607,38 +647,6 @@ __global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_f
   const BlockRef bm = bmap[blockIdx.x];
   if (bm.img >= img_limit) return;  // uniform over the workgroup
   cols_fwd_body<L1, LATE, KEEP>(jobs, bm, lds, twl, tw, threadIdx.x);
-}
-
-// dst[img][f2][:] = colIFFT(sum_g part[g][img][f2][:]).
-template <int L1>
-__global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_sum_inv(
-    const ColJob* __restrict__ jobs, const BlockRef* __restrict__ bmap, const float2* __restrict__ tw, int64_t img_limit) {
-  constexpr int P = points_per_thread(L1), T = L1 / P, NF = ffts_per_block(L1);
-  __shared__ float2 lds[NF * lds_len<L1>()];
-  __shared__ float2 twl[L1];
-  const BlockRef bm = bmap[blockIdx.x];
-  if (bm.img >= img_limit) return;  // uniform over the workgroup
-  stage_twiddles<L1>(twl, tw);
-  const ColJob& jb = jobs[bm.job];
-  const int H2 = jb.H2;
-  const int c = threadIdx.x / T, t = threadIdx.x % T;
-  const int64_t img = bm.img;
-  const int f2raw = bm.blk * NF + c;
-  const bool valid = f2raw < H2;
-  const int f2 = valid ? f2raw : H2 - 1;
-  const int64_t off = img * ((int64_t)L1 * H2) + (int64_t)f2 * L1;
-  float2 acc[P];
-#pragma unroll
-  for (int e = 0; e < P; ++e) acc[e] = gld(jb.part, off + t + T * e);
-  for (int g = 1; g < jb.ngroups; ++g) {
-#pragma unroll
-    for (int e = 0; e < P; ++e) acc[e] = cadd(acc[e], gld(jb.part, g * jb.part_stride + off + t + T * e));
-  }
-  fft_wv<L1, P, true, SYNC_WAVE>(acc, lds + c * lds_len<L1>(), twl, t);
-  if (valid) {
-#pragma unroll
-    for (int e = 0; e < P; ++e) gst(jb.dst, off + t + T * e, acc[e]);
-  }
 }
 
 // Adjoint column pass, one (column, q = bm.q) per FFT slot:
@@ -673,6 +681,7 @@ __device__ __forceinline__ void cols_adj_body(const ColJob* __restrict__ jobs, c
   const int nk1 = dense ? 1 : m1;
   float2* my = lds + c * lds_len<L1>();
   ts.commit(twl, tid);
+  if (idle_wave<T>(f2raw, c, H2)) return;
   if (jb.fft_src) fft_wv<L1, P, false, SYNC_WAVE>(vh, my, twl, t);  // uniform over the workgroup
   float2 acc[P];
 #pragma unroll
@@ -782,6 +791,7 @@ __global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_1
   }
   float2* my = lds + c * lds_len<L1>();
   ts.commit(twl, tid);
+  if (idle_wave<T>(f2raw, c, H2)) return;
   fft_wv<L1, P, false, SYNC_WAVE>(v, my, twl, opaque(t));
   if (KEEP && valid) {
     float2* kp = jb.keep + coff;
@@ -945,7 +955,7 @@ __global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_b
 // is the largest of them.
 // ---------------------------------------------------------------------------
 #define PC_FOR_EACH_PL(X) X(64) X(96) X(128) X(192) X(256) X(384) X(512)
-// lengths by points per thread (8, 12, 16): one persistent launch per group,
+// lengths by points per thread (4, 12, 8): one persistent launch per group,
 // so each holds the code of lengths with similar register needs
 #define PC_FOR_EACH_PG0(X) X(64) X(128)
 #define PC_FOR_EACH_PG1(X) X(96) X(192) X(384)
@@ -1020,7 +1030,7 @@ bool persist_length(int L) {
   return false;
 }
 
-int persist_group(int L) { return points_per_thread(L) == 8 ? 0 : points_per_thread(L) == 12 ? 1 : 2; }
+int persist_group(int L) { return points_per_thread(L) == 4 ? 0 : points_per_thread(L) == 12 ? 1 : 2; }
 
 int persist_block_rows(int L2) {
   switch (L2) {
@@ -1107,6 +1117,19 @@ void append_row_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int N
       for (int q = 0; q < nq; ++q) out.push_back(BlockRef{job, (int)img, b, q});
 }
 
+void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int L2, bool small) {
+  if (row_block_rows(L2, small) >= 16 || n_img < 1) return;  // whole lines
+  const int64_t per_img = (int64_t)(bm.size() - from) / n_img;
+  std::vector<BlockRef> img(per_img);
+  for (size_t i0 = from; i0 < bm.size(); i0 += per_img) {
+    // position p runs on XCD (i0 + p) mod 8: each XCD takes a run of blocks
+    int64_t next = 0;
+    for (int64_t x = 0; x < XCDS; ++x)
+      for (int64_t p = ((x - (int64_t)i0) % XCDS + XCDS) % XCDS; p < per_img; p += XCDS) img[p] = bm[i0 + next++];
+    std::copy(img.begin(), img.end(), bm.begin() + i0);
+  }
+}
+
 void append_col_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int H2, int L1, int nsub) {
   const int nb = (H2 + col_block_cols(L1) - 1) / col_block_cols(L1);
   for (int64_t img = 0; img < n_img; ++img)
@@ -1114,15 +1137,14 @@ void append_col_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int H
       for (int q = 0; q < nsub; ++q) out.push_back(BlockRef{job, (int)img, b, q});
 }
 
-// Late loads pay where the early variant is down to two waves per SIMD and
-// the late one has more (measured: the 1024 and 2048 column passes of single
-// images, 1.6x faster).  With three or more waves, early loads are worth
-// more when a launch's instances loop over several terms (each term's
-// spectrum loads during the previous term's transform; measured on 256
-// instances of 4 to 16 terms and 128 to 512 columns: late loads at 192, 256
-// and 384 points cost 12%), and less when every instance has a single term,
-// where there is no previous transform to hide behind (the 384-point
-// single-term sections of C5: late loads 2% faster).
+// Batches (single plans always take the late variant: 2 to 10% faster from 128
+// to 3072 points).  Late loads pay where the early variant is down to two
+// waves per SIMD and the late one has more.  With three or more waves, early
+// loads are worth more when a launch's instances loop over several terms
+// (each term's spectrum loads during the previous term's transform; measured
+// on 256 instances of 4 to 16 terms and 128 to 512 columns: 542 us early, 549
+// late), and less when every instance has a single term, where there is no
+// previous transform to hide behind.
 template <int L1>
 static bool late_pays(bool multi_term) {
   const int threads = col_threads(L1);
@@ -1222,18 +1244,30 @@ bool cols_adj_prefetch(int L1) {
   });
 }
 
-int col_groups_for(int H2, int64_t batch, int nq) {
-  // split the forward column pass over groups of column factors until about
-  // sixteen column transforms per compute unit are launched: with two or
-  // three resident workgroups per CU, fewer leave the last round of
-  // workgroups mostly empty (measured: 2048^2, 64 terms, 8 -> 16 per CU cut
-  // the pass by ~15%; 32 per CU was slower again from the partial sums)
-  const int64_t cols = (int64_t)H2 * batch;
-  const int64_t target = 256 * 16;
+int col_groups_for(int L1, int H2, int64_t batch, int nq) {
+  // split the forward column pass over groups of column factors until the
+  // chip has about three wavefronts per SIMD of column transforms; each group
+  // costs an inverse transform per column and a plane that the row-inverse
+  // pass reads (measured, us per forward at 1, 2 and 4 groups: 1024 x 1024,
+  // 16 terms 57, 46.9 and 46.0; 2048 x 2048 141.7, 140.1 and 148.8; 1536 x
+  // 1536 101, 92 and 97; four images of 512 x 512 47.8, 40.8 and 39.1).  A
+  // transform of 256 threads or more needs a third of that: 4096 x 512, 4
+  // terms, 42.1 at one group and 47.8 at two.
+  const int T = fft_threads(L1);
+  const int64_t waves = (int64_t)H2 * batch * T / 64, target = T >= 256 ? 1024 : 3000;
   int g = 1;
-  while (g < nq && cols * g < target) g *= 2;
+  while (g < nq && waves * g < target) g *= 2;
   return g < nq ? g : nq;
 }
+
+// A slot with several terms transforms its column of V once more than a pass
+// of its own would, 1 / m1 more work, which costs less than that pass's
+// launch and its round trip of the plane (measured, us per adjoint with the
+// pass and without: 256 x 256, 9 terms 20.1 and 17.5; 1024 x 1024, 16 terms
+// 47.2 and 44.1; 2048 x 2048 132.8 and 126.7).  With one term per slot (dense
+// windows) it doubles the transforms: only where they are too few to fill the
+// chip.
+bool adj_own_fft(int m1, int64_t slots) { return m1 >= 2 || slots <= 4096; }
 
 LaunchStatus launch_set(const LaunchSet& ls, int64_t nblocks, const float* x_arg, float* y_arg, hipStream_t s,
                         Tracer* tr, int64_t img_limit) {
@@ -1273,7 +1307,11 @@ LaunchStatus launch_set(const LaunchSet& ls, int64_t nblocks, const float* x_arg
       switch (ls.L) {
 #define PC_CASE(LL) \
   case LL:          \
-    if (ls.small_rows && ls.pipe)  \
+    if (ls.small_rows && ls.sum)  \
+      hipLaunchKernelGGL((k_rows_inv<LL, row_pairs_small(LL), false, true, true>), grid, block, 0, s, rj, ls.bmap, y_arg, ls.tw, img_limit); \
+    else if (ls.sum)  \
+      hipLaunchKernelGGL((k_rows_inv<LL, row_pairs_per_block(LL), false, true, true>), grid, block, 0, s, rj, ls.bmap, y_arg, ls.tw, img_limit); \
+    else if (ls.small_rows && ls.pipe)  \
       hipLaunchKernelGGL((k_rows_inv<LL, row_pairs_small(LL), true>), grid, block, 0, s, rj, ls.bmap, y_arg, ls.tw, img_limit); \
     else if (ls.small_rows && ls.one_plane)  \
       hipLaunchKernelGGL((k_rows_inv<LL, row_pairs_small(LL), false, true>), grid, block, 0, s, rj, ls.bmap, y_arg, ls.tw, img_limit); \
@@ -1306,16 +1344,6 @@ LaunchStatus launch_set(const LaunchSet& ls, int64_t nblocks, const float* x_arg
       hipLaunchKernelGGL((k_cols_fwd<LL, true, false>), grid, block, 0, s, cj, ls.bmap, ls.tw, img_limit); \
     else                       \
       hipLaunchKernelGGL((k_cols_fwd<LL, false, false>), grid, block, 0, s, cj, ls.bmap, ls.tw, img_limit); \
-    return hipGetLastError();
-        PC_FOR_EACH_L2(PC_CASE)
-#undef PC_CASE
-      }
-      break;
-    case KK_COLS_SUM:
-      switch (ls.L) {
-#define PC_CASE(LL) \
-  case LL:          \
-    hipLaunchKernelGGL(k_cols_sum_inv<LL>, grid, block, 0, s, cj, ls.bmap, ls.tw, img_limit); \
     return hipGetLastError();
         PC_FOR_EACH_L2(PC_CASE)
 #undef PC_CASE
@@ -1365,7 +1393,6 @@ const char* kernel_kind_name(int kind) {
     case KK_ROWS_FWD: return "rows_fwd";
     case KK_ROWS_INV: return "rows_inv";
     case KK_COLS_FWD: return "cols_fwd";
-    case KK_COLS_SUM: return "cols_sum";
     case KK_COLS_ADJ: return "cols_adj";
     case KK_COLS_FFT: return "cols_fft";
     case KK_COLS_BWD1: return "cols_bwd";
@@ -1390,7 +1417,6 @@ LaunchStatus launch_fwd2d(const Plan2D& p, const float* u, float* y, int64_t bat
                           bool keep) {
   LaunchStatus e = run(p.fwd_rows, batch, u, nullptr, s, tr);
   if (e == hipSuccess) e = run(keep && p.keep ? p.fwd_cols_keep : p.fwd_cols, batch, nullptr, nullptr, s, tr);
-  if (e == hipSuccess && p.col_groups > 1) e = run(p.fwd_sum, batch, nullptr, nullptr, s, tr);
   if (e == hipSuccess) e = run(p.fwd_rows_out, batch, nullptr, y, s, tr);
   return e;
 }
@@ -1405,8 +1431,8 @@ LaunchStatus launch_adj2d_tail(const Plan2D& p, float* x, int64_t batch, hipStre
 
 LaunchStatus launch_adj2d(const Plan2D& p, const float* v, float* x, int64_t batch, hipStream_t s, Tracer* tr) {
   LaunchStatus e = run(p.adj_rows, batch, v, nullptr, s, tr);
-  if (e == hipSuccess && !p.adj_fused) e = run(p.adj_fft, batch, nullptr, nullptr, s, tr);
-  if (e == hipSuccess) e = run(p.adj_cols, batch, nullptr, nullptr, s, tr);
+  if (e == hipSuccess && !p.adj_fused && !p.adj_own_fft) e = run(p.adj_fft, batch, nullptr, nullptr, s, tr);
+  if (e == hipSuccess) e = run(p.adj_own_fft ? p.adj_cols_fft : p.adj_cols, batch, nullptr, nullptr, s, tr);
   if (e == hipSuccess) e = run(p.adj_rows_out, batch, nullptr, x, s, tr);
   return e;
 }

@@ -20,6 +20,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <iterator>
+#include <map>
 #include <mutex>
 #include <new>
 #include <set>
@@ -602,6 +603,19 @@ int max_planes(const std::vector<J>& jobs) {
   return n;
 }
 
+// Whether a row-inverse list takes the SUM variant: no windows, and a job of
+// several planes.
+template <class J>
+bool sums_planes(const std::vector<J>& jobs) {
+  bool several = false;
+  if constexpr (std::is_same<J, pc::RowJob>::value)
+    for (const pc::RowJob& j : jobs) {
+      if (j.mode != 0) return false;
+      several = several || j.nq > 1;
+    }
+  return several;
+}
+
 template <class J>
 pc_status make_set(pc_plan p, pc::LaunchSet& ls, int kind, int L, const std::vector<J>& jobs,
                    const std::vector<pc::BlockRef>& bm, int64_t per_img, const float2* tw, hipStream_t s,
@@ -617,11 +631,12 @@ pc_status make_set(pc_plan p, pc::LaunchSet& ls, int kind, int L, const std::vec
   ls.threads = rows ? pc::row_threads(L, small_rows) : pc::col_threads(L);
   ls.small_rows = rows && small_rows;
   const uint64_t key = p->tune_key;
-  ls.late = kind == pc::KK_COLS_FWD && pc::tune_get(key, PC_TUNE_COLS_FWD_LATE, L, pc::cols_fwd_late(L, multi_term));
+  ls.late = kind == pc::KK_COLS_FWD && pc::tune_get(key, PC_TUNE_COLS_FWD_LATE, L, 1);
   ls.prefetch = kind == pc::KK_COLS_ADJ && pc::tune_get(key, PC_TUNE_COLS_ADJ_PREFETCH, L, pc::cols_adj_prefetch(L));
   ls.pipe = kind == pc::KK_ROWS_INV && pc::tune_get(key, PC_TUNE_ROWS_INV_PIPE, L, pc::rows_inv_pipe(L, ls.small_rows));
   ls.one = single_term_cols(kind, jobs);
   ls.one_plane = kind == pc::KK_ROWS_INV && max_planes(jobs) == 1;
+  ls.sum = kind == pc::KK_ROWS_INV && sums_planes(jobs);
   ls.jobs = dj;
   ls.bmap = db;
   ls.blocks = (int64_t)bm.size();
@@ -685,7 +700,7 @@ pc_status build_2d(pc_plan p, const float* windows, const float* h, hipStream_t 
   if ((st = p->alloc(&q.RA, (size_t)(nq * cap * plane), &p->workspace_bytes))) return st;
   if ((st = p->alloc(&q.Tws, (size_t)(cap * plane), &p->workspace_bytes))) return st;
   q.col_groups = std::max(1, std::min(nq, pc::tune_get(p->tune_key, PC_TUNE_COL_GROUPS, N1,
-                                                        pc::col_groups_for(H2, cap, nq))));
+                                                        pc::col_groups_for(N1, H2, cap, nq))));
   q.Part = nullptr;
   if (q.col_groups > 1 && (st = p->alloc(&q.Part, (size_t)(q.col_groups * cap * plane), &p->workspace_bytes)))
     return st;
@@ -712,6 +727,7 @@ pc_status build_2d(pc_plan p, const float* windows, const float* h, hipStream_t 
     pc::RowJob j{nullptr, nullptr, q.wcols, mode, N1, 0, 0.f, nullptr, q.RA, plane * cap};
     bm.clear();
     pc::append_row_blocks(bm, 0, cap, N1, N2, nq, sr_q);
+    pc::xcd_major_blocks(bm, 0, cap, N2, sr_q);
     if ((st = make_set(p, q.fwd_rows, pc::KK_ROWS_FWD, N2, std::vector<pc::RowJob>{j}, bm, (int64_t)rpi_q * nq, tw2, s,
                        sr_q)))
       return st;
@@ -723,13 +739,12 @@ pc_status build_2d(pc_plan p, const float* windows, const float* h, hipStream_t 
   if ((st = make_set(p, q.fwd_cols, pc::KK_COLS_FWD, N1, std::vector<pc::ColJob>{cf}, bm,
                      (int64_t)cpi * q.col_groups, tw1, s, false, m > 1)))
     return st;
-  bm.clear();
-  pc::append_col_blocks(bm, 0, cap, H2, N1, 1);
-  if ((st = make_set(p, q.fwd_sum, pc::KK_COLS_SUM, N1, std::vector<pc::ColJob>{cf}, bm, cpi, tw1, s))) return st;
-  {  // forward: rows of T -> y
-    pc::RowJob j{nullptr, nullptr, nullptr, 0, N1, 1, scale, q.Tws, nullptr, 0};
+  {  // forward: rows of T (or of the sum of the groups' planes) -> y
+    pc::RowJob j{nullptr, nullptr, nullptr, 0, N1, q.col_groups, scale, q.col_groups > 1 ? q.Part : q.Tws, nullptr,
+                 q.col_groups > 1 ? plane * cap : 0};
     bm.clear();
     pc::append_row_blocks(bm, 0, cap, N1, N2, 1, sr_i);
+    pc::xcd_major_blocks(bm, 0, cap, N2, sr_i);
     if ((st = make_set(p, q.fwd_rows_out, pc::KK_ROWS_INV, N2, std::vector<pc::RowJob>{j}, bm, rpi_i, tw2, s, sr_i)))
       return st;
   }
@@ -737,6 +752,7 @@ pc_status build_2d(pc_plan p, const float* windows, const float* h, hipStream_t 
     pc::RowJob j{nullptr, nullptr, nullptr, 0, N1, 0, 0.f, nullptr, q.Tws, plane * cap};
     bm.clear();
     pc::append_row_blocks(bm, 0, cap, N1, N2, 1, sr_f);
+    pc::xcd_major_blocks(bm, 0, cap, N2, sr_f);
     if ((st = make_set(p, q.adj_rows, pc::KK_ROWS_FWD, N2, std::vector<pc::RowJob>{j}, bm, rpi_f, tw2, s, sr_f)))
       return st;
   }
@@ -753,10 +769,18 @@ pc_status build_2d(pc_plan p, const float* windows, const float* h, hipStream_t 
   pc::append_col_blocks(bm, 0, cap, H2, N1, nq);
   if ((st = make_set(p, q.adj_cols, pc::KK_COLS_ADJ, N1, std::vector<pc::ColJob>{ca}, bm, (int64_t)cpi * nq, tw1, s)))
     return st;
+  q.adj_own_fft = !q.adj_fused && pc::adj_own_fft(q.dense ? 1 : q.m1, (int64_t)H2 * cap * nq);
+  if (q.adj_own_fft) {
+    ca.fft_src = 1;
+    if ((st = make_set(p, q.adj_cols_fft, pc::KK_COLS_ADJ, N1, std::vector<pc::ColJob>{ca}, bm, (int64_t)cpi * nq, tw1,
+                       s)))
+      return st;
+  }
   {  // adjoint: sum_q b_q . rows of Q_q -> x
     pc::RowJob j{nullptr, nullptr, q.wcols, mode, N1, nq, scale, q.RA, nullptr, plane * cap};
     bm.clear();
     pc::append_row_blocks(bm, 0, cap, N1, N2, 1, sr_i);
+    pc::xcd_major_blocks(bm, 0, cap, N2, sr_i);
     if ((st = make_set(p, q.adj_rows_out, pc::KK_ROWS_INV, N2, std::vector<pc::RowJob>{j}, bm, rpi_i, tw2, s, sr_i)))
       return st;
   }
@@ -904,6 +928,7 @@ pc_status batch_set(pc_batch b, std::vector<pc::LaunchSet>& seq, int kind, int L
   ls.pipe = kind == pc::KK_ROWS_INV && pc::tune_get(key, PC_TUNE_ROWS_INV_PIPE, L, pc::rows_inv_pipe(L, ls.small_rows));
   ls.one = single_term_cols(kind, jobs);
   ls.one_plane = kind == pc::KK_ROWS_INV && max_planes(jobs) == 1;
+  ls.sum = kind == pc::KK_ROWS_INV && sums_planes(jobs);
   ls.jobs = dj;
   ls.bmap = db;
   ls.blocks = (int64_t)bm.size();
@@ -1044,6 +1069,19 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
   auto out_slot = [&](size_t i, int c) -> float* const* {
     return table && !staged(i, c) ? b->dtab + (c * nb + inst[i].slot) * 2 + 1 : nullptr;
   };
+  // Forward-type instances whose column length has too few columns over the
+  // whole batch to fill the device run one term group per column factor, in
+  // place in RA (a batch call leaves nothing for a backward; 40 instances of
+  // 128 to 512 samples per side, us per forward: 251 without, 166 with).
+  std::map<int, int64_t> fwd_cols[2];  // columns of each length
+  for (int c = 0; c < 2; ++c)
+    for (size_t i = 0; i < inst.size(); ++i)
+      if (has(i, c) && fwd_type(i, c)) fwd_cols[c][inst[i].q->p2.N1] += inst[i].q->p2.H2 * inst[i].q->p2.batch_cap;
+  auto grouped = [&](size_t i, int c) {
+    const pc::Plan2D& q = inst[i].q->p2;
+    if ((q.dense ? q.m : q.m2) == 1 || keep || gather || b->persistent || !fwd_type(i, c)) return false;
+    return pc::col_groups_for(q.N1, (int)std::min<int64_t>(fwd_cols[c][q.N1], INT32_MAX), 1, 2) > 1;
+  };
   pc_status st;
   for (int c = 0; c < 2; ++c) {
     BatchLists& bl = lists[c];
@@ -1086,26 +1124,35 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
         const pc::SecTerm* st = inst[i].st;
         const int win_rows = st ? st->ea1 : 0, out_rows = st ? st->ef1 : 0;
         if (fwd_type(i, c)) {
+          const size_t bf0 = bf.size(), bfo0 = bfo.size();
           pc::append_row_blocks(bf, (int)jf.size(), cap, q.N1, L2, nq, sf, win_rows, pbr);
+          if (!pbr) pc::xcd_major_blocks(bf, bf0, cap, L2, sf);
           jf.push_back(gathered(pc::RowJob{inp, nullptr, q.wcols, mode, q.N1, 0, 0.f, nullptr, q.RA, plane * cap}));
           if (st) {  // samples outside the window box are zero and not read
             jf.back().mrows = st->ea1;
             jf.back().mcols = st->ea2;
           }
           pc::append_row_blocks(bfo, (int)jfo.size(), cap, q.N1, L2, 1, si, out_rows, pbr);
-          pc::RowJob jo{nullptr, out, nullptr, 0, q.N1, 1, scale, q.Tws, nullptr, 0};
+          if (!pbr) pc::xcd_major_blocks(bfo, bfo0, cap, L2, si);
+          // term groups, or one: the sum of the groups' planes (left in RA)
+          const bool split = grouped(i, c);
+          pc::RowJob jo{nullptr, out, nullptr, 0, q.N1, split ? nq : 1, scale, split ? q.RA : q.Tws, nullptr,
+                        split ? plane * cap : 0};
           jo.yp = out_slot(i, c);
           if (st) jo.ocols = st->ef2;  // the overlap-add reads the output box's columns only
           jfo.push_back(jo);
         } else {
           // sections: the rows of the forward output box only (the rest are zero)
+          const size_t ba0 = ba.size(), bao0 = bao.size();
           pc::append_row_blocks(ba, (int)ja.size(), cap, q.N1, L2, 1, sf, out_rows, pbr);
+          if (!pbr) pc::xcd_major_blocks(ba, ba0, cap, L2, sf);
           ja.push_back(gathered(pc::RowJob{inp, nullptr, nullptr, 0, q.N1, 0, 0.f, nullptr, q.Tws, plane * cap}));
           if (st) {  // only the output box of the forward section is read (the gradient needs the mask)
             ja.back().mrows = st->ef1;
             ja.back().mcols = st->ef2;
           }
           pc::append_row_blocks(bao, (int)jao.size(), cap, q.N1, L2, 1, si, win_rows, pbr);
+          if (!pbr) pc::xcd_major_blocks(bao, bao0, cap, L2, si);
           pc::RowJob jo{nullptr, out, q.wcols, mode, q.N1, nq, scale, q.RA, nullptr, plane * cap};
           jo.yp = out_slot(i, c);
           if (st && inst[i].direct_adj) {
@@ -1154,10 +1201,14 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
         const int64_t cap = q.batch_cap, plane = (int64_t)q.N1 * q.H2;
         const int nq = q.dense ? q.m : q.m2, dense = q.dense ? 1 : 0;
         const pc::SecTerm* st = inst[i].st;
-        if (fwd_type(i, c)) {  // one term group: the many instances already fill the device
-          pc::append_col_blocks(bf, (int)jf.size(), cap, q.H2, L1, 1);
+        if (fwd_type(i, c)) {
+          // one term group where the instances fill the device, else one per
+          // column factor, in place in RA
+          const int groups = grouped(i, c) ? nq : 1;
+          pc::append_col_blocks(bf, (int)jf.size(), cap, q.H2, L1, groups);
           f_multi = f_multi || q.m > 1;
-          jf.push_back(pc::ColJob{q.RA, q.Tws, nullptr, q.Hs, q.wrows, plane * cap, 0, q.H2, q.m1, q.m2, dense, 1});
+          jf.push_back(pc::ColJob{q.RA, q.Tws, q.RA, q.Hs, q.wrows, plane * cap, plane * cap, q.H2, q.m1, q.m2, dense,
+                                  groups});
           if (st) {
             jf.back().nvalid_in = st->ea1;  // the row pass transformed the window box rows only
             // the row-inverse pass reads whole row blocks of the output box rows

@@ -13,9 +13,17 @@ namespace pc {
 using LaunchStatus = hipError_t;
 
 // Points per thread used for an FFT of length L (3-smooth lengths need a
-// multiple of 3).
+// multiple of 3).  Few points: more wavefronts and fewer registers each, as
+// long as the passes stay as many (512 = 8 x 8 x 8 takes one exchange more
+// than 16 x 16 x 2 but less arithmetic, and a whole wavefront).  Measured (us
+// per forward / adjoint, at 16, or 24, points -> here): 512 x 512, 16 terms
+// 34.3 / 40.0 -> 27.0 / 29.3, 256 x 256, 9 terms 24.9 / 29.9 -> 18.6 / 20.7,
+// 128 x 128 (8 points before) 16.7 / 18.2 -> 14.5 / 15.4, 1536 x 1536 94.5 /
+// 94.8 -> 88.3 / 80.2, 3072 x 1024 83.5 / 84.6 -> 69.2 / 69.8; 2048 the same
+// at 8 and 16.
 constexpr int points_per_thread(int L) {
-  return (L % 3 == 0) ? (L >= 1536 ? 24 : 12) : (L >= 256 ? 16 : 8);
+  if (L % 3 == 0) return 12;
+  return L <= 128 ? 4 : L <= 1024 ? 8 : 16;
 }
 constexpr int fft_threads(int L) { return L / points_per_thread(L); }
 // FFTs per workgroup for the batched row / column kernels.
@@ -132,7 +140,7 @@ int grad1d_large_groups(const Large1D& p, int64_t pairs);
 // the wavefronts; us at 24 and 12: forward of 64 signals of 49152 samples, 16
 // terms, 105.7 and 83.8, of 98304 samples 444 and 190; 4096 and 8192 stay at
 // 16, where 8 is slower: one more exchange)
-constexpr int fourstep_points(int L) { return L == 6144 ? 12 : points_per_thread(L); }
+constexpr int fourstep_points(int L) { return L == 6144 ? 12 : 16; }
 bool fourstep_variant_supported(int L, int R, int P);
 LaunchStatus launch_fold_fft(const Large1D& p, const float* xa, int64_t n_sig, float2* out, bool pairs, hipStream_t s,
                              Tracer* tr = nullptr);
@@ -187,7 +195,7 @@ struct RowJob {
 struct ColJob {
   const float2* src;   // input planes
   float2* dst;         // output planes (in place for the transform-only pass)
-  float2* part;        // partial sums of the forward pass (ngroups > 1)
+  float2* part;        // the term groups' output planes of the forward pass (ngroups > 1)
   const float2* Hs;    // spectra, m planes [k][f2][f1]
   const float* wrows;  // row-axis window factors a_k1[n1] (separable)
   int64_t q_stride;    // between factor planes of src (forward) / dst (adjoint)
@@ -229,7 +237,7 @@ struct BlockRef {
   int job, img, blk, q;
 };
 
-enum KernelKind { KK_ROWS_FWD = 0, KK_ROWS_INV, KK_COLS_FWD, KK_COLS_SUM, KK_COLS_ADJ, KK_COLS_FFT, KK_COLS_BWD1, KK_SEC_SCATTER };
+enum KernelKind { KK_ROWS_FWD = 0, KK_ROWS_INV, KK_COLS_FWD, KK_COLS_ADJ, KK_COLS_FFT, KK_COLS_BWD1, KK_SEC_SCATTER };
 
 // Persistent batch passes: every row or column block of a pass, whatever
 // its transform length (within a length group), is one work item of one
@@ -249,7 +257,7 @@ bool persist_length(int L);
 int persist_block_rows(int L2);
 // dynamic LDS bytes of a persistent pass over the given lengths
 int persist_lds_bytes(int kind, const std::vector<int>& lengths);
-// length group of a persistent launch (points per thread 8, 12, 16)
+// length group of a persistent launch (points per thread 4, 12, 8)
 int persist_group(int L);
 int persist_grid(int kind, int pg, int lds_bytes, int64_t n_items);
 
@@ -270,6 +278,7 @@ struct LaunchSet {
   bool prefetch = false;           // adjoint column kernel: the prefetching variant (cols_adj_prefetch)
   bool pipe = false;               // row-inverse kernel: the pipelined variant (rows_inv_pipe)
   bool one_plane = false;          // row-inverse kernel: every job sums one plane (its ONE variant)
+  bool sum = false;                // row-inverse kernel: windowless jobs, some of several planes (its SUM variant)
   bool keep = false;               // forward column kernel: the variant storing U_k (jobs' keep pointers)
   bool one = false;                // column kernels: every job single-term (k_cols_1term)
   // persistent pass (persist >= 0: a PersistKind) of length group pgroup:
@@ -302,15 +311,19 @@ struct Plan2D {
   float2* Tws;               // batch_cap planes
   int col_groups;            // term groups of the forward column pass
   bool adj_fused;            // single term: adj_cols transforms its input itself (adj_fft unused by the adjoint)
-  float2* Part;              // col_groups x batch_cap planes of partial spectra (col_groups > 1)
-  LaunchSet fwd_rows, fwd_cols, fwd_sum, fwd_rows_out;
+  bool adj_own_fft;          // several terms: the adjoint runs adj_cols_fft, which transforms its input itself
+  float2* Part;              // col_groups x batch_cap planes of the groups' column transforms (col_groups > 1)
+  LaunchSet fwd_rows, fwd_cols, fwd_rows_out;
   LaunchSet fwd_cols_keep;   // fwd_cols storing U_k into keep (when the plan keeps them)
   float2* keep = nullptr;    // m x batch_cap planes of U_k, or null
-  LaunchSet adj_rows, adj_fft, adj_cols, adj_rows_out;
+  LaunchSet adj_rows, adj_fft, adj_cols, adj_cols_fft, adj_rows_out;
   LaunchSet spec_rows, spec_cols;
 };
 
-int col_groups_for(int H2, int64_t batch, int nq);
+int col_groups_for(int L1, int H2, int64_t batch, int nq);
+// Whether the adjoint column pass of a plan of several terms transforms its
+// input itself, in every column slot of m1 terms, instead of a pass before it.
+bool adj_own_fft(int m1, int64_t slots);
 
 // ---------------------------------------------------------------------------
 // Tuning table (tune.cpp): measured choices of the per-length variants for
@@ -353,6 +366,12 @@ int col_threads(int L1);
 // row_block_rows(L2, small))
 void append_row_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int N1, int L2, int nq,
                        bool small = false, int rows = 0, int block_rows = 0);
+// Reorders the blocks from `from` on, image by image (n_img of them), so that
+// neighbouring ones run on one XCD: row tiles of less than 16 rows share the
+// 128-byte lines of the spectral planes with their neighbours (with 4-row
+// tiles in order, four XCDs fetched every line: 17 us to read four planes of
+// 1024 x 513 entries, 13 here).
+void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int L2, bool small);
 void append_col_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int H2, int L1, int nsub);
 const char* kernel_kind_name(int kind);
 // img_limit: blocks of images >= img_limit return at once (their input and

@@ -125,6 +125,20 @@ def test_2d_separable(n1, n2, m1, m2, kind, batch):
     _check(p, direct=(n1 * n2 <= 64 * 96))
 
 
+@pytest.mark.parametrize("n1,n2,m1,m2,kind,batch", [
+    # row tiles of 8 and 4 rows (1024 points and more), their blocks dealt to the XCDs by neighbourhood
+    (64, 1024, 2, 2, "hat", 3), (96, 1536, 2, 3, "hat", 1), (64, 2048, 3, 2, "hat", 2), (128, 4096, 2, 2, "hat", 1),
+    # column transforms of one and of several wavefronts, groups of column factors of every count
+    (1024, 64, 2, 3, "hat", 1), (1536, 96, 3, 2, "hat", 2), (2048, 64, 2, 4, "hat", 1), (4096, 96, 2, 2, "hat", 1),
+    (256, 512, 4, 4, "hat", 7), (512, 128, 1, 4, "hat", 1), (128, 192, 4, 1, "hat", 5),
+    # 65 and 97 columns: workgroups whose last wavefronts have none
+    (512, 128, 3, 3, "hat", 2), (256, 192, 2, 2, "hat", 1), (768, 64, 2, 2, "hat", 1),
+])
+def test_2d_tiles_groups_and_idle_wavefronts(n1, n2, m1, m2, kind, batch):
+    p = wl.small_2d(n1, n2, m1, m2, batch, seed=700 + n1 + n2 + m1, kind=kind)
+    _check(p)
+
+
 def test_2d_dense_windows():
     p = wl.small_2d(64, 128, 2, 3, 3, seed=41, kind="hat")
     w = p.dense_windows()
