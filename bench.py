@@ -265,7 +265,7 @@ def main():
                     help="extra steps timed one by one after a 1 GiB write that evicts L2 and the "
                          "Infinity Cache (reported as cold_ms_per_step; 0 disables)")
     ap.add_argument("--persistent", action="store_true",
-                    help="c4: one persistent launch per pass (PC_BATCH_PERSISTENT)")
+                    help="c4: one launch per pass, whatever the tuning table says (PC_BATCH_PERSISTENT)")
     ap.add_argument("--no-tuning", action="store_true",
                     help="clear the tuning table: every variant from the library's rules")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="MIB",

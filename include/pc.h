@@ -453,8 +453,8 @@ pc_status pc_wavelet_transform_noalloc(int32_t inverse, int64_t n, int32_t level
  *           Convolution-product and product-convolution plans may share a
  *           batch.
  *   flags   PC_BATCH_NO_GRAPH: launch the passes directly instead of
- *           through the captured graphs; PC_BATCH_PERSISTENT: one persistent
- *           launch per pass (below).
+ *           through the captured graphs; PC_BATCH_PERSISTENT: one
+ *           launch per pass, whatever the tuning table says (below).
  *   stream  unused (creation is synchronous).
  * Errors: INVALID_VALUE (count < 1, null array, a repeated plan, a plan that
  * is not 2D, plans on different devices, unknown flags),
@@ -463,14 +463,12 @@ pc_status pc_wavelet_transform_noalloc(int32_t inverse, int64_t n, int32_t level
 typedef struct pc_batch_s* pc_batch;
 enum {
   PC_BATCH_NO_GRAPH = 1u,
-  /* Persistent passes: one launch per pass (rows in, forward column passes
-   * and column transforms, adjoint column passes, rows out) and length group
-   * (64, 128; 96, 192, 384; 256, 512 points) instead
-   * of one launch per pass and transform length: every block of the pass
-   * over all instances of the group's lengths is a work item of a list
-   * (longest transforms first) that the launch's workgroups walk with a grid
-   * stride.  Other lengths keep their own launches.  Without the flag, a
-   * tuning table entry for the batch (PC_TUNE_BATCH_PERSISTENT) decides. */
+  /* One launch per pass (rows in, forward column passes and column
+   * transforms, adjoint column passes, rows out) for every transform length
+   * up to 512 together, instead of one launch per pass and transform length.
+   * Longer lengths keep their own launches.  This is what a batch does in any
+   * case, unless a tuning table entry for it (PC_TUNE_BATCH_PERSISTENT 0) asks
+   * for launches per length; the flag overrides that entry. */
   PC_BATCH_PERSISTENT = 2u
 };
 pc_status pc_batch_create(pc_batch* out, int32_t count, const pc_plan* plans, uint32_t flags, void* stream);
@@ -529,7 +527,7 @@ enum {
   PC_TUNE_ROWS_INV_SMALL = 5,     /* row-inverse passes: 4-row tiles instead of 16-row ones */
   PC_TUNE_COL_GROUPS = 6,         /* full-grid forward column pass: term groups */
   PC_TUNE_FOURSTEP_L = 7,         /* 1D four-step: inner transform length */
-  PC_TUNE_BATCH_PERSISTENT = 8,   /* batches: persistent passes (length 0) */
+  PC_TUNE_BATCH_PERSISTENT = 8,   /* batches: one launch per pass (1, the rule) or per length (0) (length 0) */
   PC_TUNE_SEC_STREAMS = 9,        /* sectioned plans: two launch chains, on two streams (length 0) */
   PC_TUNE_KEEP = 10               /* plans with gradients: keep the windowed spectra within the budget (1, the
                                      rule) or recompute them in every backward (0) (length 0) */

@@ -155,8 +155,7 @@ constexpr int row_pairs_small(int L2) { return row_pairs_per_block(L2) < 2 ? row
 // Half-spectra of windowed rows, transposed: sout[q][img][f2][n1], f2 < H2.
 // The body of a row-forward block bm (G row pairs, G * T threads), with the
 // workgroup's LDS (G * row_slot_len<L2, G>() entries) and the staged
-// twiddles; the per-length kernel and the persistent batch kernel both run
-// it.
+// twiddles; the per-length kernel and the merged batch kernel both run it.
 template <int L2, int G>
 __device__ __forceinline__ void rows_fwd_body(const RowJob* __restrict__ jobs, const BlockRef bm,
                                               const float* __restrict__ x_arg, float2* __restrict__ lds,
@@ -944,158 +943,139 @@ __global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_b
 }
 
 // ---------------------------------------------------------------------------
-// Persistent batch passes.  One launch per pass and length group runs the
-// blocks of every transform length of the group; its workgroups
-// (PERSIST_THREADS threads, row passes with G = PERSIST_THREADS / T row
-// pairs) walk the item list with a grid stride, stage the item's twiddles and
-// run the pass body.  The
-// variants are fixed to the ones with the fewest registers (spectrum loaded
-// after the transform, no prefetch, no pipelined row-inverse tiles): a
-// launch holds the code of every length of its group, so its register count
-// is the largest of them.
+// Merged batch passes: one launch per pass for the blocks of every transform
+// length up to 512, each workgroup branching to its length's pass body.  A
+// batch of uneven instances has some hundred to a few thousand blocks of each
+// length; launched per length they fill the chip once or less, and every
+// launch waits for the one before to drain (us forward / adjoint, launches
+// per length -> merged: 12 instances of 128 to 512 samples per side 115 / 120
+// -> 44 / 47, 40 170 / 176 -> 97 / 89, 256 540 / 494 -> 445 / 405).
+// The job tables and twiddle pointers are kernel arguments: read through a
+// pointer from memory, the job fields are loaded per lane by flat
+// instructions, whose completion every LDS wait of the transforms then also
+// waits for (256 instances: 530 / 497).  Two launches, 12-point lengths apart,
+// keep more waves per SIMD but drain twice (563 / 497 against those), as does
+// a register limit (spills).
+// Row passes: MERGED_THREADS / T row pairs per block, at most 16 (threads
+// beyond them leave at once).
 // ---------------------------------------------------------------------------
-#define PC_FOR_EACH_PL(X) X(64) X(96) X(128) X(192) X(256) X(384) X(512)
-// lengths by points per thread (4, 12, 8): one persistent launch per group,
-// so each holds the code of lengths with similar register needs
-#define PC_FOR_EACH_PG0(X) X(64) X(128)
-#define PC_FOR_EACH_PG1(X) X(96) X(192) X(384)
-#define PC_FOR_EACH_PG2(X) X(256) X(512)
+#define PC_FOR_EACH_ML(X) X(64, 0) X(96, 1) X(128, 2) X(192, 3) X(256, 4) X(384, 5) X(512, 6)
 
 template <int L>
-constexpr int prow_pairs() { return PERSIST_THREADS / fft_threads(L); }
+constexpr int merged_row_pairs() {
+  return MERGED_THREADS / fft_threads(L) < 16 ? MERGED_THREADS / fft_threads(L) : 16;
+}
 
 template <int KIND, int L>
-constexpr int plds_entries() {
+constexpr int merged_lds() {
   // transform buffers, twiddles and (row-inverse) the 2G row factors
-  return (KIND == PK_ROWS_FWD   ? prow_pairs<L>() * row_slot_len<L, prow_pairs<L>()>()
-          : KIND == PK_ROWS_INV ? prow_pairs<L>() * lds_len<L>()
-                                : ffts_per_block(L) * lds_len<L>()) +
-         L + (KIND == PK_ROWS_INV ? prow_pairs<L>() : 0);
+  return ((KIND == MK_ROWS_FWD   ? merged_row_pairs<L>() * row_slot_len<L, merged_row_pairs<L>()>()
+           : KIND == MK_ROWS_INV ? merged_row_pairs<L>() * lds_len<L>()
+                                 : ffts_per_block(L) * lds_len<L>()) +
+          L + (KIND == MK_ROWS_INV ? merged_row_pairs<L>() : 0)) *
+         (int)sizeof(float2);
 }
 
-template <int KIND, int L>
-__device__ __forceinline__ void persist_item(const PItem& w, float2* smem, const float* x_arg, float* y_arg) {
-  float2* twl = smem;
-  float2* lds = smem + L;
-  // (each body stages the item's twiddles itself)
-  // an opaque copy of the thread index: the body's per-element addresses are
-  // recomputed per item instead of living across the item loop
-  const int tid = opaque((int)threadIdx.x);
-  if constexpr (KIND == PK_ROWS_FWD) {
-    rows_fwd_body<L, prow_pairs<L>()>(static_cast<const RowJob*>(w.jobs), w.bm, x_arg, lds, twl, w.tw, tid);
-  } else if constexpr (KIND == PK_ROWS_INV) {
-    rows_inv_body<L, prow_pairs<L>(), false>(static_cast<const RowJob*>(w.jobs), w.bm, y_arg, lds, twl, w.tw,
-                                             reinterpret_cast<float*>(lds + prow_pairs<L>() * lds_len<L>()), tid);
-  } else if constexpr (KIND == PK_COLS_A) {
+template <int KIND, int L, class Job>
+__device__ __forceinline__ void merged_block(const Job* __restrict__ jobs, const MergedBlock& w,
+                                             const float2* __restrict__ tw, float2* smem) {
+  constexpr int G = merged_row_pairs<L>();
+  constexpr int NT = (KIND == MK_ROWS_FWD || KIND == MK_ROWS_INV ? G : ffts_per_block(L)) * fft_threads(L);
+  static_assert(NT <= MERGED_THREADS && (NT == MERGED_THREADS || NT % 64 == 0), "merged blocks are whole waves");
+  const int tid = threadIdx.x;
+  if (NT < MERGED_THREADS && tid >= NT) return;  // whole waves, before any barrier
+  float2* twl = smem + (KIND == MK_ROWS_INV ? G : 0);
+  float2* lds = twl + L;
+  if constexpr (KIND == MK_ROWS_FWD) {
+    rows_fwd_body<L, G>(jobs, w.bm, nullptr, lds, twl, tw, tid);
+  } else if constexpr (KIND == MK_ROWS_INV) {
+    float* rfac = reinterpret_cast<float*>(smem);
     if (w.sub == 0)
-      cols_fwd_body<L, true, false>(static_cast<const ColJob*>(w.jobs), w.bm, lds, twl, w.tw, tid);
+      rows_inv_body<L, G, false>(jobs, w.bm, nullptr, lds, twl, tw, rfac, tid);
     else
-      cols_fft_body<L>(static_cast<const ColJob*>(w.jobs), w.bm, lds, twl, w.tw, tid);
+      rows_inv_body<L, G, false, true, true>(jobs, w.bm, nullptr, lds, twl, tw, rfac, tid);
+  } else if constexpr (KIND == MK_COLS_FWD) {
+    if (w.sub == 0)
+      cols_fwd_body<L, true, false>(jobs, w.bm, lds, twl, tw, tid);
+    else
+      cols_fft_body<L>(jobs, w.bm, lds, twl, tw, tid);
   } else {
-    cols_adj_body<L, false>(static_cast<const ColJob*>(w.jobs), w.bm, lds, twl, w.tw, tid);
+    cols_adj_body<L, false>(jobs, w.bm, lds, twl, tw, tid);
   }
 }
 
-template <int KIND, int PG>
-__global__ __launch_bounds__(PERSIST_THREADS) void k_persist(const PItem* __restrict__ items, int n_items,
-                                                            const float* __restrict__ x_arg, float* __restrict__ y_arg) {
+template <int KIND, class Job>
+__global__ __launch_bounds__(MERGED_THREADS) void k_merged(const Job* __restrict__ jobs,
+                                                           const MergedBlock* __restrict__ blocks, MergedTw tws) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
-  // workgroup b takes items b, b + grid, b + 2 grid, ... of the list (longest
-  // first): no shared counter, whose same-address atomics would serialise
-  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-    __syncthreads();  // the previous item is done with LDS
-    const PItem w = items[it];
-#define PC_CASE(LL)                                  \
-  case LL:                                           \
-    persist_item<KIND, LL>(w, smem, x_arg, y_arg);   \
+  const MergedBlock w = blocks[blockIdx.x];
+  switch (w.L) {
+#define PC_CASE(LL, I)                                            \
+  case LL:                                                        \
+    merged_block<KIND, LL, Job>(jobs, w, tws.tw[I], smem);        \
     break;
-    if constexpr (PG == 0) {
-      switch (w.L) { PC_FOR_EACH_PG0(PC_CASE) }
-    } else if constexpr (PG == 1) {
-      switch (w.L) { PC_FOR_EACH_PG1(PC_CASE) }
-    } else {
-      switch (w.L) { PC_FOR_EACH_PG2(PC_CASE) }
-    }
+    PC_FOR_EACH_ML(PC_CASE)
 #undef PC_CASE
   }
 }
 
-bool persist_length(int L) {
+int merged_index(int L) {
   switch (L) {
-#define PC_CASE(LL) case LL:
-    PC_FOR_EACH_PL(PC_CASE)
+#define PC_CASE(LL, I) \
+  case LL:             \
+    return I;
+    PC_FOR_EACH_ML(PC_CASE)
 #undef PC_CASE
-    return true;
   }
-  return false;
+  return -1;
 }
 
-int persist_group(int L) { return points_per_thread(L) == 4 ? 0 : points_per_thread(L) == 12 ? 1 : 2; }
-
-int persist_block_rows(int L2) {
+int merged_block_rows(int L2) {
   switch (L2) {
-#define PC_CASE(LL) \
-  case LL:          \
-    return 2 * prow_pairs<LL>();
-    PC_FOR_EACH_PL(PC_CASE)
+#define PC_CASE(LL, I) \
+  case LL:             \
+    return 2 * merged_row_pairs<LL>();
+    PC_FOR_EACH_ML(PC_CASE)
 #undef PC_CASE
   }
   return 0;
 }
 
-template <int KIND>
-static int plds_bytes_of(int L) {
+int merged_lds_bytes(int kind, int L) {
   switch (L) {
-#define PC_CASE(LL) \
-  case LL:          \
-    return plds_entries<KIND, LL>() * (int)sizeof(float2);
-    PC_FOR_EACH_PL(PC_CASE)
+#define PC_CASE(LL, I)                                         \
+  case LL:                                                     \
+    return kind == MK_ROWS_FWD   ? merged_lds<MK_ROWS_FWD, LL>() \
+           : kind == MK_ROWS_INV ? merged_lds<MK_ROWS_INV, LL>() \
+           : kind == MK_COLS_FWD ? merged_lds<MK_COLS_FWD, LL>() \
+                                 : merged_lds<MK_COLS_ADJ, LL>();
+    PC_FOR_EACH_ML(PC_CASE)
 #undef PC_CASE
   }
   return 0;
 }
 
-int persist_lds_bytes(int kind, const std::vector<int>& lengths) {
-  int b = 0;
-  for (int L : lengths) {
-    const int x = kind == PK_ROWS_FWD   ? plds_bytes_of<PK_ROWS_FWD>(L)
-                  : kind == PK_ROWS_INV ? plds_bytes_of<PK_ROWS_INV>(L)
-                  : kind == PK_COLS_A   ? plds_bytes_of<PK_COLS_A>(L)
-                                        : plds_bytes_of<PK_COLS_ADJ>(L);
-    b = std::max(b, x);
+static LaunchStatus launch_merged(const LaunchSet& ls, hipStream_t s, Tracer* tr) {
+  static const char* const names[] = {"merged_rows_fwd", "merged_cols_fwd", "merged_cols_adj", "merged_rows_inv"};
+  TraceScope ts(tr, names[ls.merged & 3], s);
+  const dim3 grid((unsigned)ls.blocks), block(MERGED_THREADS);
+  const size_t lds = (size_t)ls.lds_bytes;
+  const RowJob* rj = static_cast<const RowJob*>(ls.jobs);
+  const ColJob* cj = static_cast<const ColJob*>(ls.jobs);
+  switch (ls.merged) {
+    case MK_ROWS_FWD:
+      hipLaunchKernelGGL((k_merged<MK_ROWS_FWD, RowJob>), grid, block, lds, s, rj, ls.mblocks, ls.mtw);
+      break;
+    case MK_COLS_FWD:
+      hipLaunchKernelGGL((k_merged<MK_COLS_FWD, ColJob>), grid, block, lds, s, cj, ls.mblocks, ls.mtw);
+      break;
+    case MK_COLS_ADJ:
+      hipLaunchKernelGGL((k_merged<MK_COLS_ADJ, ColJob>), grid, block, lds, s, cj, ls.mblocks, ls.mtw);
+      break;
+    default:
+      hipLaunchKernelGGL((k_merged<MK_ROWS_INV, RowJob>), grid, block, lds, s, rj, ls.mblocks, ls.mtw);
   }
-  return b;
-}
-
-template <int KIND>
-static const void* persist_fn_k(int pg) {
-  if (pg == 0) return reinterpret_cast<const void*>(k_persist<KIND, 0>);
-  if (pg == 1) return reinterpret_cast<const void*>(k_persist<KIND, 1>);
-  return reinterpret_cast<const void*>(k_persist<KIND, 2>);
-}
-
-static const void* persist_fn(int kind, int pg) {
-  switch (kind) {
-    case PK_ROWS_FWD: return persist_fn_k<PK_ROWS_FWD>(pg);
-    case PK_COLS_A: return persist_fn_k<PK_COLS_A>(pg);
-    case PK_COLS_ADJ: return persist_fn_k<PK_COLS_ADJ>(pg);
-  }
-  return persist_fn_k<PK_ROWS_INV>(pg);
-}
-
-// workgroups of a persistent launch: as many as the device holds at once
-// (never more than the items)
-int persist_grid(int kind, int pg, int lds_bytes, int64_t n_items) {
-  int dev = 0, cus = 256, per_cu = 1;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
-  }
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persist_fn(kind, pg), PERSIST_THREADS, lds_bytes) !=
-          hipSuccess ||
-      per_cu < 1)
-    per_cu = 1;
-  return (int)std::min<int64_t>(n_items, (int64_t)cus * per_cu);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -1117,8 +1097,8 @@ void append_row_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int N
       for (int q = 0; q < nq; ++q) out.push_back(BlockRef{job, (int)img, b, q});
 }
 
-void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int L2, bool small) {
-  if (row_block_rows(L2, small) >= 16 || n_img < 1) return;  // whole lines
+void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int L2, bool small, int block_rows) {
+  if ((block_rows > 0 ? block_rows : row_block_rows(L2, small)) >= 16 || n_img < 1) return;  // whole lines
   const int64_t per_img = (int64_t)(bm.size() - from) / n_img;
   std::vector<BlockRef> img(per_img);
   for (size_t i0 = from; i0 < bm.size(); i0 += per_img) {
@@ -1272,16 +1252,7 @@ bool adj_own_fft(int m1, int64_t slots) { return m1 >= 2 || slots <= 4096; }
 LaunchStatus launch_set(const LaunchSet& ls, int64_t nblocks, const float* x_arg, float* y_arg, hipStream_t s,
                         Tracer* tr, int64_t img_limit) {
   if (nblocks <= 0) return hipSuccess;
-  if (ls.persist >= 0) {
-    static const char* const names[] = {"persist_rows_fwd", "persist_cols_a", "persist_cols_adj", "persist_rows_inv"};
-    TraceScope ts(tr, names[ls.persist & 3], s);
-    const dim3 pg((unsigned)nblocks), pb(PERSIST_THREADS);
-    const void* fn = persist_fn(ls.persist, ls.pgroup);
-    void* args[] = {(void*)&ls.items, (void*)&ls.n_items, (void*)&x_arg, (void*)&y_arg};
-    const hipError_t e = hipLaunchKernel(fn, pg, pb, args, (size_t)ls.lds_bytes, s);
-    if (e != hipSuccess) return e;
-    return hipGetLastError();
-  }
+  if (ls.merged >= 0) return launch_merged(ls, s, tr);
   if (ls.kind == KK_SEC_SCATTER)  // (traced as sec_scatter by the launcher)
     return launch_sec_scatter(*ls.sec, nullptr, ls.sec_adjoint, nblocks < ls.sec->cap ? nblocks : ls.sec->cap, s, tr,
                               ls.sec_out);

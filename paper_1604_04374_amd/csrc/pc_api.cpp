@@ -831,7 +831,7 @@ struct pc_batch_s {
   std::vector<void*> allocs;
   std::vector<pc::LaunchSet> fwd_seq, adj_seq;
   bool has_fwd = false, has_adj = false, use_graph = true;
-  bool persistent = false;  // one persistent launch per pass for the lengths it holds code for
+  bool merged = false;  // one launch per pass for all the lengths the merged kernels hold code for
   hipGraph_t gf = nullptr, ga = nullptr;
   hipGraphExec_t ef = nullptr, ea = nullptr;
   // Buffers of the calls: the jobs read each instance's input and output
@@ -891,30 +891,55 @@ std::set<const void*> g_batches;  // live batches (guarded by g_registry_mu)
 // convolution-product one.
 struct BatchLists {
   std::vector<pc::LaunchSet> f_rows_in, f_cols, f_rows_out, a_rows_in, a_fft, a_cols, a_rows_out;
-  // persistent passes (pc::PersistKind): their work items and lengths, and
-  // the launches made of them
-  std::vector<pc::PItem> items[4][3];  // [pass][length group]
-  std::vector<int> lens[4][3];
-  std::vector<pc::LaunchSet> persist[4];
+  // merged passes (pc::MergedKind): the blocks and jobs collected for each
+  struct Merged {
+    struct Item {
+      pc::MergedBlock blk;
+      int work;  // sort key: the block's share of the pass
+    };
+    std::vector<Item> items;
+    std::vector<pc::RowJob> rows;
+    std::vector<pc::ColJob> cols;
+    pc::MergedTw tw = {};
+    int lds = 0;
+    std::vector<pc::RowJob>& jobs(const pc::RowJob*) { return rows; }
+    std::vector<pc::ColJob>& jobs(const pc::ColJob*) { return cols; }
+  } merged[4];
 };
+
+// A merged block's share of its pass, the order of the list: the chip takes
+// blocks roughly in list order, so the short ones fill its last round.  Row
+// blocks: by length alone, which keeps the neighbours of xcd_major_blocks
+// together.
+int merged_work(const pc::RowJob&, int, int L) { return L; }
+int merged_work(const pc::ColJob& j, int kind, int L) {
+  const int terms = kind == pc::MK_COLS_ADJ ? j.m1 : j.m1 * j.m2 / j.ngroups;
+  return (terms + 1) * pc::points_per_thread(L);
+}
 
 template <class J>
 pc_status batch_set(pc_batch b, std::vector<pc::LaunchSet>& seq, int kind, int L, const std::vector<J>& jobs,
                     const std::vector<pc::BlockRef>& bm, const float2* tw, bool multi_term = true,
-                    bool small_rows = false, BatchLists* pl = nullptr, int pkind = -1, int psub = 0) {
+                    bool small_rows = false, BatchLists* pl = nullptr, int mkind = -1, int msub = 0) {
   if (jobs.empty()) return PC_SUCCESS;
+  if (pl && b->merged && pc::merged_index(L) >= 0) {
+    BatchLists::Merged& mg = pl->merged[mkind];
+    std::vector<J>& all = mg.jobs(jobs.data());
+    const int j0 = (int)all.size();
+    all.insert(all.end(), jobs.begin(), jobs.end());
+    for (pc::BlockRef r : bm) {
+      const int work = merged_work(jobs[(size_t)r.job], mkind, L);
+      r.job += j0;
+      mg.items.push_back({pc::MergedBlock{r, L, msub}, work});
+    }
+    mg.tw.tw[pc::merged_index(L)] = tw;
+    mg.lds = std::max(mg.lds, pc::merged_lds_bytes(mkind, L));
+    return PC_SUCCESS;
+  }
   J* dj = nullptr;
   pc::BlockRef* db = nullptr;
   pc_status st = b->upload(&dj, jobs);
   if (st) return st;
-  if (pl && pkind >= 0 && b->persistent && pc::persist_length(L)) {
-    // a length of the persistent pass: its blocks become work items
-    const int g = pc::persist_group(L);
-    for (const pc::BlockRef& r : bm) pl->items[pkind][g].push_back(pc::PItem{dj, r, tw, L, psub});
-    if (std::find(pl->lens[pkind][g].begin(), pl->lens[pkind][g].end(), L) == pl->lens[pkind][g].end())
-      pl->lens[pkind][g].push_back(L);
-    return PC_SUCCESS;
-  }
   if ((st = b->upload(&db, bm))) return st;
   pc::LaunchSet ls;
   const bool rows = kind == pc::KK_ROWS_FWD || kind == pc::KK_ROWS_INV;
@@ -1073,13 +1098,20 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
   // whole batch to fill the device run one term group per column factor, in
   // place in RA (a batch call leaves nothing for a backward; 40 instances of
   // 128 to 512 samples per side, us per forward: 251 without, 166 with).
-  std::map<int, int64_t> fwd_cols[2];  // columns of each length
+  std::map<int, int64_t> fwd_cols[2], adj_slots[2];  // columns (and adjoint slots) of each length
   for (int c = 0; c < 2; ++c)
-    for (size_t i = 0; i < inst.size(); ++i)
-      if (has(i, c) && fwd_type(i, c)) fwd_cols[c][inst[i].q->p2.N1] += inst[i].q->p2.H2 * inst[i].q->p2.batch_cap;
+    for (size_t i = 0; i < inst.size(); ++i) {
+      const pc::Plan2D& q = inst[i].q->p2;
+      const int64_t cols = q.H2 * q.batch_cap;
+      if (!has(i, c)) continue;
+      if (fwd_type(i, c))
+        fwd_cols[c][q.N1] += cols;
+      else
+        adj_slots[c][q.N1] += cols * (q.dense ? q.m : q.m2);
+    }
   auto grouped = [&](size_t i, int c) {
     const pc::Plan2D& q = inst[i].q->p2;
-    if ((q.dense ? q.m : q.m2) == 1 || keep || gather || b->persistent || !fwd_type(i, c)) return false;
+    if ((q.dense ? q.m : q.m2) == 1 || keep || gather || !fwd_type(i, c)) return false;
     return pc::col_groups_for(q.N1, (int)std::min<int64_t>(fwd_cols[c][q.N1], INT32_MAX), 1, 2) > 1;
   };
   pc_status st;
@@ -1088,12 +1120,8 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
     for (int L2 : n2s) {
       const bool sf = pc::tune_get(b->tune_key, PC_TUNE_ROWS_FWD_SMALL, L2, 0) != 0;  // row tiles
       const bool si = pc::tune_get(b->tune_key, PC_TUNE_ROWS_INV_SMALL, L2, 0) != 0;
-      // the persistent row passes take G = 256 / T row pairs per block, when
-      // that many rows divide every image of this row length
-      int pbr = b->persistent && pc::persist_length(L2) ? pc::persist_block_rows(L2) : 0;
-      for (const BInst& x : inst)
-        if (pbr && x.q->p2.N2 == L2 && x.q->p2.N1 % pbr) pbr = 0;
-      BatchLists* prow = pbr ? &bl : nullptr;
+      // the merged row passes have blocks of their own heights
+      const int pbr = b->merged ? pc::merged_block_rows(L2) : 0;
       std::vector<pc::RowJob> jf, jfo, ja, jao;
       std::vector<pc::BlockRef> bf, bfo, ba, bao;
       const float2* tw = nullptr;
@@ -1126,14 +1154,14 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
         if (fwd_type(i, c)) {
           const size_t bf0 = bf.size(), bfo0 = bfo.size();
           pc::append_row_blocks(bf, (int)jf.size(), cap, q.N1, L2, nq, sf, win_rows, pbr);
-          if (!pbr) pc::xcd_major_blocks(bf, bf0, cap, L2, sf);
+          pc::xcd_major_blocks(bf, bf0, cap, L2, sf, pbr);
           jf.push_back(gathered(pc::RowJob{inp, nullptr, q.wcols, mode, q.N1, 0, 0.f, nullptr, q.RA, plane * cap}));
           if (st) {  // samples outside the window box are zero and not read
             jf.back().mrows = st->ea1;
             jf.back().mcols = st->ea2;
           }
           pc::append_row_blocks(bfo, (int)jfo.size(), cap, q.N1, L2, 1, si, out_rows, pbr);
-          if (!pbr) pc::xcd_major_blocks(bfo, bfo0, cap, L2, si);
+          pc::xcd_major_blocks(bfo, bfo0, cap, L2, si, pbr);
           // term groups, or one: the sum of the groups' planes (left in RA)
           const bool split = grouped(i, c);
           pc::RowJob jo{nullptr, out, nullptr, 0, q.N1, split ? nq : 1, scale, split ? q.RA : q.Tws, nullptr,
@@ -1145,14 +1173,14 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
           // sections: the rows of the forward output box only (the rest are zero)
           const size_t ba0 = ba.size(), bao0 = bao.size();
           pc::append_row_blocks(ba, (int)ja.size(), cap, q.N1, L2, 1, sf, out_rows, pbr);
-          if (!pbr) pc::xcd_major_blocks(ba, ba0, cap, L2, sf);
+          pc::xcd_major_blocks(ba, ba0, cap, L2, sf, pbr);
           ja.push_back(gathered(pc::RowJob{inp, nullptr, nullptr, 0, q.N1, 0, 0.f, nullptr, q.Tws, plane * cap}));
           if (st) {  // only the output box of the forward section is read (the gradient needs the mask)
             ja.back().mrows = st->ef1;
             ja.back().mcols = st->ef2;
           }
           pc::append_row_blocks(bao, (int)jao.size(), cap, q.N1, L2, 1, si, win_rows, pbr);
-          if (!pbr) pc::xcd_major_blocks(bao, bao0, cap, L2, si);
+          pc::xcd_major_blocks(bao, bao0, cap, L2, si, pbr);
           pc::RowJob jo{nullptr, out, q.wcols, mode, q.N1, nq, scale, q.RA, nullptr, plane * cap};
           jo.yp = out_slot(i, c);
           if (st && inst[i].direct_adj) {
@@ -1167,11 +1195,11 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
           jao.push_back(jo);
         }
       }
-      if ((st = batch_set(b, bl.f_rows_in, pc::KK_ROWS_FWD, L2, jf, bf, tw, true, sf, prow, pc::PK_ROWS_FWD)))
+      if ((st = batch_set(b, bl.f_rows_in, pc::KK_ROWS_FWD, L2, jf, bf, tw, true, sf, &bl, pc::MK_ROWS_FWD)))
         return st;
-      if ((st = batch_set(b, bl.f_rows_out, pc::KK_ROWS_INV, L2, jfo, bfo, tw, true, si, prow, pc::PK_ROWS_INV)))
+      if ((st = batch_set(b, bl.f_rows_out, pc::KK_ROWS_INV, L2, jfo, bfo, tw, true, si, &bl, pc::MK_ROWS_INV, 1)))
         return st;
-      if (gather && !prow && !ba.empty()) {
+      if (gather && !ba.empty()) {
         // the sections' output boxes overlap: the adjoint's row-forward
         // blocks over the same image rows (same band of the row-block
         // height from the box origin) share their lines
@@ -1184,9 +1212,9 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
         }
         xcd_group_blocks(ba, band);
       }
-      if ((st = batch_set(b, bl.a_rows_in, pc::KK_ROWS_FWD, L2, ja, ba, tw, true, sf, prow, pc::PK_ROWS_FWD)))
+      if ((st = batch_set(b, bl.a_rows_in, pc::KK_ROWS_FWD, L2, ja, ba, tw, true, sf, &bl, pc::MK_ROWS_FWD)))
         return st;
-      if ((st = batch_set(b, bl.a_rows_out, pc::KK_ROWS_INV, L2, jao, bao, tw, true, si, prow, pc::PK_ROWS_INV)))
+      if ((st = batch_set(b, bl.a_rows_out, pc::KK_ROWS_INV, L2, jao, bao, tw, true, si, &bl, pc::MK_ROWS_INV)))
         return st;
     }
     for (int L1 : n1s) {
@@ -1220,13 +1248,14 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
             jf.back().keep_stride = plane * cap;
           }
         } else {
-          if (!q.adj_fused) {
+          const bool own = q.adj_fused || (!gather && pc::adj_own_fft(dense ? 1 : q.m1, adj_slots[c][L1]));
+          if (!own) {
             pc::append_col_blocks(bt, (int)jt.size(), cap, q.H2, L1, 1);
             jt.push_back(pc::ColJob{nullptr, q.Tws, nullptr, nullptr, nullptr, 0, 0, q.H2, q.m1, q.m2, dense, 1});
           }
           pc::append_col_blocks(ba, (int)ja.size(), cap, q.H2, L1, nq);
           pc::ColJob j{q.Tws, q.RA, nullptr, q.Hs, q.wrows, plane * cap, 0, q.H2, q.m1, q.m2, dense, 1};
-          j.fft_src = q.adj_fused ? 1 : 0;
+          j.fft_src = own ? 1 : 0;
           if (st) {  // the row-inverse pass reads whole row blocks of the window box rows
             const int br = pc::row_block_rows(q.N2, pc::tune_get(b->tune_key, PC_TUNE_ROWS_INV_SMALL, q.N2, 0) != 0);
             j.nvalid_out = std::min(q.N1, (st->ea1 + br - 1) / br * br);
@@ -1235,39 +1264,46 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
           ja.push_back(j);
         }
       }
-      const bool nokeep = keep == nullptr;  // the persistent forward column pass keeps nothing
-      if ((st = batch_set(b, bl.f_cols, pc::KK_COLS_FWD, L1, jf, bf, tw, f_multi, false, nokeep ? &bl : nullptr,
-                          pc::PK_COLS_A, 0)))
+      if ((st = batch_set(b, bl.f_cols, pc::KK_COLS_FWD, L1, jf, bf, tw, f_multi, false, &bl, pc::MK_COLS_FWD)))
         return st;
-      if ((st = batch_set(b, bl.a_fft, pc::KK_COLS_FFT, L1, jt, bt, tw, true, false, &bl, pc::PK_COLS_A, 1))) return st;
-      if ((st = batch_set(b, bl.a_cols, pc::KK_COLS_ADJ, L1, ja, ba, tw, true, false, &bl, pc::PK_COLS_ADJ))) return st;
+      if ((st = batch_set(b, bl.a_fft, pc::KK_COLS_FFT, L1, jt, bt, tw, true, false, &bl, pc::MK_COLS_FWD, 1)))
+        return st;
+      if ((st = batch_set(b, bl.a_cols, pc::KK_COLS_ADJ, L1, ja, ba, tw, true, false, &bl, pc::MK_COLS_ADJ))) return st;
     }
   }
   for (int c = 0; c < 2; ++c) {
     BatchLists& bl = lists[c];
-    for (int k = 0; k < 4; ++k)
-      for (int g = 2; g >= 0; --g) {  // the launches of longer transforms first
-      std::vector<pc::PItem>& it = bl.items[k][g];
-      if (it.empty()) continue;
-      // longer transforms first (within a length, the instances with the
-      // most terms first, as listed)
-      std::stable_sort(it.begin(), it.end(), [](const pc::PItem& x, const pc::PItem& y) { return x.L > y.L; });
-      pc::PItem* di = nullptr;
-      if ((st = b->upload(&di, it))) return st;
+    std::vector<pc::LaunchSet> merged[4];
+    for (int k = 0; k < 4; ++k) {
+      BatchLists::Merged& mg = bl.merged[k];
+      if (mg.items.empty()) continue;
+      std::stable_sort(mg.items.begin(), mg.items.end(),
+                       [](const BatchLists::Merged::Item& x, const BatchLists::Merged::Item& y) { return x.work > y.work; });
+      std::vector<pc::MergedBlock> blocks;
+      blocks.reserve(mg.items.size());
+      for (const BatchLists::Merged::Item& x : mg.items) blocks.push_back(x.blk);
+      const bool rows = k == pc::MK_ROWS_FWD || k == pc::MK_ROWS_INV;
+      pc::MergedBlock* db = nullptr;
+      pc::RowJob* dr = nullptr;
+      pc::ColJob* dc = nullptr;
+      if ((st = b->upload(&db, blocks)) || (st = rows ? b->upload(&dr, mg.rows) : b->upload(&dc, mg.cols))) return st;
       pc::LaunchSet ls;
-      ls.persist = k;
-      ls.pgroup = g;
-      ls.items = di;
-      ls.n_items = (int)it.size();
-      ls.lds_bytes = pc::persist_lds_bytes(k, bl.lens[k][g]);
-      ls.blocks = pc::persist_grid(k, g, ls.lds_bytes, ls.n_items);
-      ls.threads = pc::PERSIST_THREADS;
-      ls.kind = k == pc::PK_ROWS_FWD ? pc::KK_ROWS_FWD : k == pc::PK_ROWS_INV ? pc::KK_ROWS_INV : pc::KK_COLS_FWD;
-      bl.persist[k].push_back(ls);
-      }
+      ls.kind = k == pc::MK_ROWS_FWD   ? pc::KK_ROWS_FWD
+                : k == pc::MK_ROWS_INV ? pc::KK_ROWS_INV
+                : k == pc::MK_COLS_FWD ? pc::KK_COLS_FWD
+                                       : pc::KK_COLS_ADJ;
+      ls.merged = k;
+      ls.mblocks = db;
+      ls.jobs = rows ? static_cast<const void*>(dr) : dc;
+      ls.mtw = mg.tw;
+      ls.lds_bytes = mg.lds;
+      ls.blocks = (int64_t)blocks.size();
+      ls.threads = pc::MERGED_THREADS;
+      merged[k].push_back(ls);
+    }
     std::vector<pc::LaunchSet>& seq = c == 0 ? b->fwd_seq : b->adj_seq;
-    for (auto* v : {&bl.persist[pc::PK_ROWS_FWD], &bl.f_rows_in, &bl.a_rows_in, &bl.persist[pc::PK_COLS_A], &bl.f_cols,
-                    &bl.a_fft, &bl.persist[pc::PK_COLS_ADJ], &bl.a_cols, &bl.persist[pc::PK_ROWS_INV], &bl.f_rows_out,
+    for (auto* v : {&merged[pc::MK_ROWS_FWD], &bl.f_rows_in, &bl.a_rows_in, &merged[pc::MK_COLS_FWD], &bl.f_cols,
+                    &bl.a_fft, &merged[pc::MK_COLS_ADJ], &bl.a_cols, &merged[pc::MK_ROWS_INV], &bl.f_rows_out,
                     &bl.a_rows_out})
       seq.insert(seq.end(), v->begin(), v->end());
     // the overlap-add of each sectioned plan of a user batch, into the
@@ -2058,7 +2094,7 @@ pc_status pc_batch_create(pc_batch* out, int32_t count, const pc_plan* plans, ui
     for (pc_plan q : b->plans) ds.push_back(q->d);
     b->tune_key = pc::tune_batch_key(ds);
   }
-  b->persistent = (flags & PC_BATCH_PERSISTENT) || pc::tune_get(b->tune_key, PC_TUNE_BATCH_PERSISTENT, 0, 0) != 0;
+  b->merged = (flags & PC_BATCH_PERSISTENT) || pc::tune_get(b->tune_key, PC_TUNE_BATCH_PERSISTENT, 0, 1) != 0;
   b->use_graph = !(flags & PC_BATCH_NO_GRAPH);
   DeviceGuard g(device);
   const size_t tab_bytes = (size_t)4 * count * sizeof(float*);

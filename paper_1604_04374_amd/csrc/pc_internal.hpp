@@ -239,27 +239,24 @@ struct BlockRef {
 
 enum KernelKind { KK_ROWS_FWD = 0, KK_ROWS_INV, KK_COLS_FWD, KK_COLS_ADJ, KK_COLS_FFT, KK_COLS_BWD1, KK_SEC_SCATTER };
 
-// Persistent batch passes: every row or column block of a pass, whatever
-// its transform length (within a length group), is one work item of one
-// launch; the workgroups walk the list with a grid stride.
-enum PersistKind { PK_ROWS_FWD = 0, PK_COLS_A = 1, PK_COLS_ADJ = 2, PK_ROWS_INV = 3 };
-struct PItem {
-  const void* jobs;  // device RowJob[] or ColJob[] of the item's length
-  BlockRef bm;
-  const float2* tw;  // engine twiddles for L
-  int L;
-  int sub;           // PK_COLS_A: 0 forward column pass, 1 column transform of V
+// Merged batch passes: the blocks of a pass over every transform length up
+// to 512, in one launch.
+enum MergedKind { MK_ROWS_FWD = 0, MK_COLS_FWD = 1, MK_COLS_ADJ = 2, MK_ROWS_INV = 3 };
+struct MergedBlock {
+  BlockRef bm;  // (job: index into the launch's one job table)
+  int L;        // transform length
+  int sub;      // MK_COLS_FWD: 1 column transform of V; MK_ROWS_INV: 1 windowless planes, added first
 };
-constexpr int PERSIST_THREADS = 256;
-// transform lengths the persistent kernels hold code for
-bool persist_length(int L);
-// rows per block of the persistent row passes (G = PERSIST_THREADS / T row pairs)
-int persist_block_rows(int L2);
-// dynamic LDS bytes of a persistent pass over the given lengths
-int persist_lds_bytes(int kind, const std::vector<int>& lengths);
-// length group of a persistent launch (points per thread 4, 12, 8)
-int persist_group(int L);
-int persist_grid(int kind, int pg, int lds_bytes, int64_t n_items);
+constexpr int MERGED_THREADS = 256, MERGED_LENGTHS = 7;
+struct MergedTw {
+  const float2* tw[MERGED_LENGTHS];  // engine twiddles by merged_index
+};
+// index of a length the merged kernels hold code for, else -1
+int merged_index(int L);
+// rows per block of the merged row passes
+int merged_block_rows(int L2);
+// dynamic LDS bytes of a merged pass's blocks of length L
+int merged_lds_bytes(int kind, int L);
 
 // A prepared launch: kernel kind and length, device tables, block counts.
 struct Sec2D;
@@ -281,12 +278,11 @@ struct LaunchSet {
   bool sum = false;                // row-inverse kernel: windowless jobs, some of several planes (its SUM variant)
   bool keep = false;               // forward column kernel: the variant storing U_k (jobs' keep pointers)
   bool one = false;                // column kernels: every job single-term (k_cols_1term)
-  // persistent pass (persist >= 0: a PersistKind) of length group pgroup:
-  // items (device PItem[]), their count and the dynamic LDS bytes
-  int persist = -1;
-  int pgroup = 0;
-  const PItem* items = nullptr;
-  int n_items = 0;
+  // merged pass (merged >= 0: a MergedKind): its blocks (device), the
+  // lengths' twiddles and the dynamic LDS bytes
+  int merged = -1;
+  const MergedBlock* mblocks = nullptr;
+  MergedTw mtw = {};
   int lds_bytes = 0;
   // overlap-add of a sectioned plan in a batch (KK_SEC_SCATTER): its section
   // geometry, the direction, and the batch table entry holding the output
@@ -371,7 +367,7 @@ void append_row_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int N
 // 128-byte lines of the spectral planes with their neighbours (with 4-row
 // tiles in order, four XCDs fetched every line: 17 us to read four planes of
 // 1024 x 513 entries, 13 here).
-void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int L2, bool small);
+void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int L2, bool small, int block_rows = 0);
 void append_col_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int H2, int L1, int nsub);
 const char* kernel_kind_name(int kind);
 // img_limit: blocks of images >= img_limit return at once (their input and

@@ -187,3 +187,39 @@ def test_batch_rejects_misuse():
     assert lib.pc_batch_apply(None, None, None, None) == 1
     assert lib.pc_batch_destroy(None) == 1
     del y
+
+
+# every length of the merged passes as column and row length (blocks of 16 to
+# 32 rows, some with idle threads; 65 columns are one more than whole column
+# blocks), one longer length with launches of its own, one term to sixteen
+MERGED = [(64, 512, 2, 3, 1), (96, 384, 1, 1, 2), (128, 256, 3, 1, 1), (192, 192, 2, 2, 2), (256, 96, 1, 4, 1),
+          (384, 128, 4, 4, 1), (512, 64, 2, 1, 3), (768, 96, 2, 2, 1), (96, 768, 1, 3, 1)]
+
+
+@pytest.mark.parametrize("merged", [1, 0])
+def test_lengths_merged_into_one_launch_per_pass(merged):
+    # separable, dense and product-convolution plans in one batch.  TOL is the
+    # file's; 1e-6 between a batch and its single plans as above.
+    import torch
+    import paper_1604_04374_amd as pcm
+    probs = [wl.small_2d(n1, n2, m1, m2, batch, seed=40 + i, kind="hat")
+             for i, (n1, n2, m1, m2, batch) in enumerate(MERGED)]
+    plans = [pcm.Plan(p.dense_windows().astype(np.float32) if i % 4 == 3 else plan_args(p), p.h, batch=p.batch,
+                      full_grid=True, product_convolution=i % 3 == 2) for i, p in enumerate(probs)]
+    inputs = [torch.from_numpy(p.u).cuda() for p in probs]
+    pcm.tune_set([(pcm.tune_batch_key(plans), pcm.TUNE_KNOBS["batch_persistent"], 0, merged)])
+    try:
+        b = pcm.Batch(plans)
+    finally:
+        pcm.tune_set([])
+    print(f"[gpu] batch of every length (merged={merged})", flush=True)
+    y = [t.cpu().numpy() for t in b.apply(inputs)]
+    x = [t.cpu().numpy() for t in b.apply_adjoint(inputs)]
+    b.destroy()
+    for i, (p, pl) in enumerate(zip(probs, plans)):
+        assert per_instance_rel(y[i], pl.apply(inputs[i]).cpu().numpy()) <= 1e-6, p.name
+        assert per_instance_rel(x[i], pl.apply_adjoint(inputs[i]).cpu().numpy()) <= 1e-6, p.name
+        if i % 3 != 2:
+            ry, rx = oracle_fft(p)
+            assert per_instance_rel(y[i], ry) <= TOL and per_instance_rel(x[i], rx) <= TOL, p.name
+        pl.destroy()
