@@ -633,9 +633,14 @@ pc_status make_set(pc_plan p, pc::LaunchSet& ls, int kind, int L, const std::vec
   const uint64_t key = p->tune_key;
   ls.late = kind == pc::KK_COLS_FWD && pc::tune_get(key, PC_TUNE_COLS_FWD_LATE, L, 1);
   ls.prefetch = kind == pc::KK_COLS_ADJ && pc::tune_get(key, PC_TUNE_COLS_ADJ_PREFETCH, L, pc::cols_adj_prefetch(L));
-  ls.pipe = kind == pc::KK_ROWS_INV && pc::tune_get(key, PC_TUNE_ROWS_INV_PIPE, L, pc::rows_inv_pipe(L, ls.small_rows));
   ls.one = single_term_cols(kind, jobs);
   ls.one_plane = kind == pc::KK_ROWS_INV && max_planes(jobs) == 1;
+  // one plane leaves nothing to load ahead, for 160 registers instead of 88 at
+  // 384 points (us per adjoint and per training step, piped -> not: sections
+  // of 384 x 384 on 2048 x 2048 49.3 and 127.9 -> 46.4 and 122.8, of 512 x 512
+  // on 3072 x 3072 78.0 and 253 -> 71.7 and 242)
+  ls.pipe = kind == pc::KK_ROWS_INV &&
+            pc::tune_get(key, PC_TUNE_ROWS_INV_PIPE, L, !ls.one_plane && pc::rows_inv_pipe(L, ls.small_rows));
   ls.sum = kind == pc::KK_ROWS_INV && sums_planes(jobs);
   ls.jobs = dj;
   ls.bmap = db;
@@ -950,9 +955,10 @@ pc_status batch_set(pc_batch b, std::vector<pc::LaunchSet>& seq, int kind, int L
   const uint64_t key = b->tune_key;
   ls.late = kind == pc::KK_COLS_FWD && pc::tune_get(key, PC_TUNE_COLS_FWD_LATE, L, pc::cols_fwd_late(L, multi_term));
   ls.prefetch = kind == pc::KK_COLS_ADJ && pc::tune_get(key, PC_TUNE_COLS_ADJ_PREFETCH, L, pc::cols_adj_prefetch(L));
-  ls.pipe = kind == pc::KK_ROWS_INV && pc::tune_get(key, PC_TUNE_ROWS_INV_PIPE, L, pc::rows_inv_pipe(L, ls.small_rows));
   ls.one = single_term_cols(kind, jobs);
   ls.one_plane = kind == pc::KK_ROWS_INV && max_planes(jobs) == 1;
+  ls.pipe = kind == pc::KK_ROWS_INV &&
+            pc::tune_get(key, PC_TUNE_ROWS_INV_PIPE, L, !ls.one_plane && pc::rows_inv_pipe(L, ls.small_rows));
   ls.sum = kind == pc::KK_ROWS_INV && sums_planes(jobs);
   ls.jobs = dj;
   ls.bmap = db;
