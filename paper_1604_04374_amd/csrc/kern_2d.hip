@@ -757,15 +757,10 @@ __global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_a
 // transform.  KEEP (forward): the transformed windowed column U is also
 // stored at keep[img][f2][:] for the backward pass.
 template <int L1, bool ADJ, bool KEEP = false>
-__global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_1term(
-    const ColJob* __restrict__ jobs, const BlockRef* __restrict__ bmap, const float2* __restrict__ tw,
-    int64_t img_limit) {
+__device__ __forceinline__ void cols_1term_body(const ColJob* __restrict__ jobs, const BlockRef bm,
+                                                float2* __restrict__ lds, float2* __restrict__ twl,
+                                                const float2* __restrict__ tw, const int tid) {
   constexpr int P = points_per_thread(L1), T = L1 / P, NF = ffts_per_block(L1);
-  __shared__ float2 lds[NF * lds_len<L1>()];
-  __shared__ float2 twl[L1];
-  const BlockRef bm = bmap[blockIdx.x];
-  if (bm.img >= img_limit) return;  // uniform over the workgroup
-  const int tid = threadIdx.x;
   TwStage<L1, NF * T> ts;
   ts.load(tw, tid);
   const ColJob& jb = jobs[bm.job];
@@ -816,6 +811,17 @@ __global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_1
   }
 }
 
+template <int L1, bool ADJ, bool KEEP = false>
+__global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_1term(
+    const ColJob* __restrict__ jobs, const BlockRef* __restrict__ bmap, const float2* __restrict__ tw,
+    int64_t img_limit) {
+  __shared__ float2 lds[ffts_per_block(L1) * lds_len<L1>()];
+  __shared__ float2 twl[L1];
+  const BlockRef bm = bmap[blockIdx.x];
+  if (bm.img >= img_limit) return;  // uniform over the workgroup
+  cols_1term_body<L1, ADJ, KEEP>(jobs, bm, lds, twl, tw, threadIdx.x);
+}
+
 // In-place column FFTs of dst: dst[img][f2][:] = colFFT(dst[img][f2][:]).
 template <int L1>
 __device__ __forceinline__ void cols_fft_body(const ColJob* __restrict__ jobs, const BlockRef bm,
@@ -862,13 +868,11 @@ __global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_f
 // windowed input left by the forward pass) or U read from keep.  dst is read
 // before it is overwritten, column by column, by the same threads.
 template <int L1>
-__global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_bwd1(
-    const ColJob* __restrict__ jobs, const BlockRef* __restrict__ bmap, const float2* __restrict__ tw,
-    float2* __restrict__ gext, int64_t img_limit) {
+__device__ __forceinline__ void cols_bwd1_body(const ColJob* __restrict__ jobs, const BlockRef bm,
+                                               float2* __restrict__ lds, float2* __restrict__ twl,
+                                               const float2* __restrict__ tw, float2* __restrict__ gext,
+                                               const int64_t img_limit) {
   constexpr int P = points_per_thread(L1), T = L1 / P, NF = ffts_per_block(L1);
-  __shared__ float2 lds[NF * lds_len<L1>()];
-  __shared__ float2 twl[L1];
-  const BlockRef bm = bmap[blockIdx.x];
   stage_twiddles<L1>(twl, tw);
   const ColJob& jb = jobs[bm.job];
   const int H2 = jb.H2;
@@ -942,6 +946,15 @@ __global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_b
   }
 }
 
+template <int L1>
+__global__ __launch_bounds__(ffts_per_block(L1) * fft_threads(L1)) void k_cols_bwd1(
+    const ColJob* __restrict__ jobs, const BlockRef* __restrict__ bmap, const float2* __restrict__ tw,
+    float2* __restrict__ gext, int64_t img_limit) {
+  __shared__ float2 lds[ffts_per_block(L1) * lds_len<L1>()];
+  __shared__ float2 twl[L1];
+  cols_bwd1_body<L1>(jobs, bmap[blockIdx.x], lds, twl, tw, gext, img_limit);
+}
+
 // ---------------------------------------------------------------------------
 // Merged batch passes: one launch per pass for the blocks of every transform
 // length up to 512, each workgroup branching to its length's pass body.  A
@@ -969,50 +982,61 @@ constexpr int merged_row_pairs() {
 template <int KIND, int L>
 constexpr int merged_lds() {
   // transform buffers, twiddles and (row-inverse) the 2G row factors
-  return ((KIND == MK_ROWS_FWD   ? merged_row_pairs<L>() * row_slot_len<L, merged_row_pairs<L>()>()
-           : KIND == MK_ROWS_INV ? merged_row_pairs<L>() * lds_len<L>()
-                                 : ffts_per_block(L) * lds_len<L>()) +
-          L + (KIND == MK_ROWS_INV ? merged_row_pairs<L>() : 0)) *
+  constexpr int G = merged_row_pairs<L>();
+  constexpr bool inv = KIND == MK_ROWS_INV || KIND == MK_ROWS_INV1;
+  return ((KIND == MK_ROWS_FWD ? G * row_slot_len<L, G>() : inv ? G * lds_len<L>() : ffts_per_block(L) * lds_len<L>()) +
+          L + (inv ? G : 0)) *
          (int)sizeof(float2);
 }
 
 template <int KIND, int L, class Job>
 __device__ __forceinline__ void merged_block(const Job* __restrict__ jobs, const MergedBlock& w,
-                                             const float2* __restrict__ tw, float2* smem) {
+                                             const float2* __restrict__ tw, float2* smem, float* arg,
+                                             const int64_t img_limit) {
   constexpr int G = merged_row_pairs<L>();
-  constexpr int NT = (KIND == MK_ROWS_FWD || KIND == MK_ROWS_INV ? G : ffts_per_block(L)) * fft_threads(L);
-  static_assert(NT <= MERGED_THREADS && (NT == MERGED_THREADS || NT % 64 == 0), "merged blocks are whole waves");
+  constexpr bool inv = KIND == MK_ROWS_INV || KIND == MK_ROWS_INV1, rows = KIND == MK_ROWS_FWD || inv;
+  constexpr int NT = (rows ? G : ffts_per_block(L)) * fft_threads(L);
+  static_assert(NT == MERGED_THREADS || (rows && NT % 64 == 0 && NT < MERGED_THREADS), "merged blocks are whole waves");
   const int tid = threadIdx.x;
   if (NT < MERGED_THREADS && tid >= NT) return;  // whole waves, before any barrier
-  float2* twl = smem + (KIND == MK_ROWS_INV ? G : 0);
+  float2* twl = smem + (inv ? G : 0);
   float2* lds = twl + L;
   if constexpr (KIND == MK_ROWS_FWD) {
-    rows_fwd_body<L, G>(jobs, w.bm, nullptr, lds, twl, tw, tid);
-  } else if constexpr (KIND == MK_ROWS_INV) {
+    rows_fwd_body<L, G>(jobs, w.bm, arg, lds, twl, tw, tid);
+  } else if constexpr (inv) {
     float* rfac = reinterpret_cast<float*>(smem);
-    if (w.sub == 0)
-      rows_inv_body<L, G, false>(jobs, w.bm, nullptr, lds, twl, tw, rfac, tid);
+    if (KIND == MK_ROWS_INV1)
+      rows_inv_body<L, G, false, true>(jobs, w.bm, arg, lds, twl, tw, rfac, tid);
+    else if (w.sub == 0)
+      rows_inv_body<L, G, false>(jobs, w.bm, arg, lds, twl, tw, rfac, tid);
     else
-      rows_inv_body<L, G, false, true, true>(jobs, w.bm, nullptr, lds, twl, tw, rfac, tid);
+      rows_inv_body<L, G, false, true, true>(jobs, w.bm, arg, lds, twl, tw, rfac, tid);
   } else if constexpr (KIND == MK_COLS_FWD) {
     if (w.sub == 0)
       cols_fwd_body<L, true, false>(jobs, w.bm, lds, twl, tw, tid);
     else
       cols_fft_body<L>(jobs, w.bm, lds, twl, tw, tid);
-  } else {
+  } else if constexpr (KIND == MK_COLS_ADJ) {
     cols_adj_body<L, false>(jobs, w.bm, lds, twl, tw, tid);
+  } else if constexpr (KIND == MK_COLS_BWD1) {
+    cols_bwd1_body<L>(jobs, w.bm, lds, twl, tw, reinterpret_cast<float2*>(arg), img_limit);
+  } else {
+    cols_1term_body<L, KIND == MK_COLS_ADJ1, KIND == MK_COLS_KEEP1>(jobs, w.bm, lds, twl, tw, tid);
   }
 }
 
+// arg: the launch's input (rows in), output (rows out) or gradient buffer
 template <int KIND, class Job>
 __global__ __launch_bounds__(MERGED_THREADS) void k_merged(const Job* __restrict__ jobs,
-                                                           const MergedBlock* __restrict__ blocks, MergedTw tws) {
+                                                           const MergedBlock* __restrict__ blocks, MergedTw tws,
+                                                           float* __restrict__ arg, int64_t img_limit) {
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
   const MergedBlock w = blocks[blockIdx.x];
+  if (w.bm.img >= img_limit) return;  // uniform over the workgroup
   switch (w.L) {
-#define PC_CASE(LL, I)                                            \
-  case LL:                                                        \
-    merged_block<KIND, LL, Job>(jobs, w, tws.tw[I], smem);        \
+#define PC_CASE(LL, I)                                                          \
+  case LL:                                                                      \
+    merged_block<KIND, LL, Job>(jobs, w, tws.tw[I], smem, arg, img_limit);      \
     break;
     PC_FOR_EACH_ML(PC_CASE)
 #undef PC_CASE
@@ -1043,37 +1067,41 @@ int merged_block_rows(int L2) {
 
 int merged_lds_bytes(int kind, int L) {
   switch (L) {
-#define PC_CASE(LL, I)                                         \
-  case LL:                                                     \
-    return kind == MK_ROWS_FWD   ? merged_lds<MK_ROWS_FWD, LL>() \
-           : kind == MK_ROWS_INV ? merged_lds<MK_ROWS_INV, LL>() \
-           : kind == MK_COLS_FWD ? merged_lds<MK_COLS_FWD, LL>() \
-                                 : merged_lds<MK_COLS_ADJ, LL>();
+#define PC_CASE(LL, I)                                                                         \
+  case LL:                                                                                     \
+    return kind == MK_ROWS_FWD                              ? merged_lds<MK_ROWS_FWD, LL>()    \
+           : kind == MK_ROWS_INV || kind == MK_ROWS_INV1 ? merged_lds<MK_ROWS_INV, LL>()       \
+                                                            : merged_lds<MK_COLS_FWD, LL>();
     PC_FOR_EACH_ML(PC_CASE)
 #undef PC_CASE
   }
   return 0;
 }
 
-static LaunchStatus launch_merged(const LaunchSet& ls, hipStream_t s, Tracer* tr) {
-  static const char* const names[] = {"merged_rows_fwd", "merged_cols_fwd", "merged_cols_adj", "merged_rows_inv"};
-  TraceScope ts(tr, names[ls.merged & 3], s);
+static LaunchStatus launch_merged(const LaunchSet& ls, const float* x_arg, float* y_arg, hipStream_t s, Tracer* tr,
+                                  int64_t img_limit) {
+  TraceScope ts(tr, kernel_kind_name(ls.kind), s);
   const dim3 grid((unsigned)ls.blocks), block(MERGED_THREADS);
   const size_t lds = (size_t)ls.lds_bytes;
   const RowJob* rj = static_cast<const RowJob*>(ls.jobs);
   const ColJob* cj = static_cast<const ColJob*>(ls.jobs);
+  float* arg = ls.merged == MK_ROWS_FWD ? const_cast<float*>(x_arg) : y_arg;  // (the row-forward pass only reads it)
   switch (ls.merged) {
-    case MK_ROWS_FWD:
-      hipLaunchKernelGGL((k_merged<MK_ROWS_FWD, RowJob>), grid, block, lds, s, rj, ls.mblocks, ls.mtw);
-      break;
-    case MK_COLS_FWD:
-      hipLaunchKernelGGL((k_merged<MK_COLS_FWD, ColJob>), grid, block, lds, s, cj, ls.mblocks, ls.mtw);
-      break;
-    case MK_COLS_ADJ:
-      hipLaunchKernelGGL((k_merged<MK_COLS_ADJ, ColJob>), grid, block, lds, s, cj, ls.mblocks, ls.mtw);
-      break;
-    default:
-      hipLaunchKernelGGL((k_merged<MK_ROWS_INV, RowJob>), grid, block, lds, s, rj, ls.mblocks, ls.mtw);
+#define PC_CASE(K, J, j)                                                                                    \
+  case K:                                                                                                   \
+    hipLaunchKernelGGL((k_merged<K, J>), grid, block, lds, s, j, ls.mblocks, ls.mtw, arg, img_limit);       \
+    break;
+    PC_CASE(MK_ROWS_FWD, RowJob, rj)
+    PC_CASE(MK_ROWS_INV, RowJob, rj)
+    PC_CASE(MK_ROWS_INV1, RowJob, rj)
+    PC_CASE(MK_COLS_FWD, ColJob, cj)
+    PC_CASE(MK_COLS_ADJ, ColJob, cj)
+    PC_CASE(MK_COLS_FWD1, ColJob, cj)
+    PC_CASE(MK_COLS_KEEP1, ColJob, cj)
+    PC_CASE(MK_COLS_ADJ1, ColJob, cj)
+    PC_CASE(MK_COLS_BWD1, ColJob, cj)
+#undef PC_CASE
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -1252,7 +1280,7 @@ bool adj_own_fft(int m1, int64_t slots) { return m1 >= 2 || slots <= 4096; }
 LaunchStatus launch_set(const LaunchSet& ls, int64_t nblocks, const float* x_arg, float* y_arg, hipStream_t s,
                         Tracer* tr, int64_t img_limit) {
   if (nblocks <= 0) return hipSuccess;
-  if (ls.merged >= 0) return launch_merged(ls, s, tr);
+  if (ls.merged >= 0) return launch_merged(ls, x_arg, y_arg, s, tr, img_limit);
   if (ls.kind == KK_SEC_SCATTER)  // (traced as sec_scatter by the launcher)
     return launch_sec_scatter(*ls.sec, nullptr, ls.sec_adjoint, nblocks < ls.sec->cap ? nblocks : ls.sec->cap, s, tr,
                               ls.sec_out);

@@ -836,7 +836,9 @@ struct pc_batch_s {
   std::vector<void*> allocs;
   std::vector<pc::LaunchSet> fwd_seq, adj_seq;
   bool has_fwd = false, has_adj = false, use_graph = true;
-  bool merged = false;  // one launch per pass for all the lengths the merged kernels hold code for
+  // one launch per row pass (column pass) for all the lengths the merged
+  // kernels hold code for
+  bool merged_rows = false, merged_cols = false;
   hipGraph_t gf = nullptr, ga = nullptr;
   hipGraphExec_t ef = nullptr, ea = nullptr;
   // Buffers of the calls: the jobs read each instance's input and output
@@ -887,6 +889,104 @@ namespace {
 
 std::set<const void*> g_batches;  // live batches (guarded by g_registry_mu)
 
+// A merged pass (pc::MergedKind) in the making: its blocks and jobs.
+struct Merged {
+  struct Item {
+    pc::MergedBlock blk;
+    int work;  // sort key: the block's share of the pass
+  };
+  std::vector<Item> items;
+  std::vector<pc::RowJob> rows;
+  std::vector<pc::ColJob> cols;
+  pc::MergedTw tw = {};
+  int lds = 0;
+  std::vector<pc::RowJob>& jobs(const pc::RowJob*) { return rows; }
+  std::vector<pc::ColJob>& jobs(const pc::ColJob*) { return cols; }
+};
+
+// A merged block's share of its pass, the order of the list: the chip takes
+// blocks roughly in list order, so the short ones fill its last round.  Row
+// blocks: by length alone, which keeps the neighbours of xcd_major_blocks
+// together.
+int merged_work(const pc::RowJob&, int, int L) { return L; }
+int merged_work(const pc::ColJob& j, int kind, int L) {
+  const int terms = kind == pc::MK_COLS_ADJ || kind == pc::MK_COLS_ADJ1 ? j.m1 : j.m1 * j.m2 / j.ngroups;
+  return (terms + 1) * pc::points_per_thread(L);
+}
+
+template <class J>
+void collect_merged(Merged& mg, const std::vector<J>& jobs, const std::vector<pc::BlockRef>& bm, const float2* tw,
+                    int mkind, int L, int msub) {
+  std::vector<J>& all = mg.jobs(jobs.data());
+  const int j0 = (int)all.size();
+  all.insert(all.end(), jobs.begin(), jobs.end());
+  for (pc::BlockRef r : bm) {
+    const int work = merged_work(jobs[(size_t)r.job], mkind, L);
+    r.job += j0;
+    mg.items.push_back({pc::MergedBlock{r, L, msub}, work});
+  }
+  mg.tw.tw[pc::merged_index(L)] = tw;
+  mg.lds = std::max(mg.lds, pc::merged_lds_bytes(mkind, L));
+}
+
+// The launch of a merged pass; up(&device, host) uploads a table.
+template <class Upload>
+pc_status finish_merged(Merged& mg, int mkind, std::vector<pc::LaunchSet>& seq, Upload&& up) {
+  if (mg.items.empty()) return PC_SUCCESS;
+  std::stable_sort(mg.items.begin(), mg.items.end(),
+                   [](const Merged::Item& x, const Merged::Item& y) { return x.work > y.work; });
+  std::vector<pc::MergedBlock> blocks;
+  blocks.reserve(mg.items.size());
+  for (const Merged::Item& x : mg.items) blocks.push_back(x.blk);
+  pc::MergedBlock* db = nullptr;
+  pc::LaunchSet ls;
+  pc_status st = up(&db, blocks);
+  if (!st && !mg.rows.empty()) {
+    pc::RowJob* d = nullptr;
+    st = up(&d, mg.rows);
+    ls.jobs = d;
+  } else if (!st) {
+    pc::ColJob* d = nullptr;
+    st = up(&d, mg.cols);
+    ls.jobs = d;
+  }
+  if (st) return st;
+  switch (mkind) {
+    case pc::MK_ROWS_FWD: ls.kind = pc::KK_ROWS_FWD; break;
+    case pc::MK_ROWS_INV:
+    case pc::MK_ROWS_INV1: ls.kind = pc::KK_ROWS_INV; break;
+    case pc::MK_COLS_ADJ:
+    case pc::MK_COLS_ADJ1: ls.kind = pc::KK_COLS_ADJ; break;
+    case pc::MK_COLS_BWD1: ls.kind = pc::KK_COLS_BWD1; break;
+    default: ls.kind = pc::KK_COLS_FWD;
+  }
+  ls.merged = mkind;
+  ls.mblocks = db;
+  ls.mtw = mg.tw;
+  ls.lds_bytes = mg.lds;
+  ls.blocks = (int64_t)blocks.size();
+  ls.threads = pc::MERGED_THREADS;
+  seq.push_back(ls);
+  return PC_SUCCESS;
+}
+
+// Whether a sectioned plan's pass over these lengths is merged: where it
+// would otherwise take two launches or more (us per forward, adjoint and
+// training step, apart -> merged: 2048 x 2048 in sections of 384 and 512 74.5,
+// 61.5 and 161 -> 60.3, 47.2 and 134; four images of 512 x 512, 192 and 256
+// 42.6, 38.2 and 106 -> 30.0, 25.4 and 70; 1024 x 1536, 192 to 384 67, 57 and
+// 140 -> 53, 44 and 110).  A single length keeps its own kernels, whose row
+// tiles are of whole lines at 512 points.
+bool several_merged(const std::vector<int>& lens) {
+  return std::count_if(lens.begin(), lens.end(), [](int L) { return pc::merged_index(L) >= 0; }) > 1;
+}
+
+// Rows per block of a batch's row-inverse pass.
+int inv_block_rows(const pc_batch_s* b, int L2) {
+  const int merged = b->merged_rows ? pc::merged_block_rows(L2) : 0;
+  return merged ? merged : pc::row_block_rows(L2, pc::tune_get(b->tune_key, PC_TUNE_ROWS_INV_SMALL, L2, 0) != 0);
+}
+
 // Launch lists of one batch call.  Each call (apply, apply_adjoint) runs a
 // forward-type chain (windowed row FFTs, term-split column pass with the
 // spectral sum, inverse rows) for the instances that need the
@@ -896,49 +996,17 @@ std::set<const void*> g_batches;  // live batches (guarded by g_registry_mu)
 // convolution-product one.
 struct BatchLists {
   std::vector<pc::LaunchSet> f_rows_in, f_cols, f_rows_out, a_rows_in, a_fft, a_cols, a_rows_out;
-  // merged passes (pc::MergedKind): the blocks and jobs collected for each
-  struct Merged {
-    struct Item {
-      pc::MergedBlock blk;
-      int work;  // sort key: the block's share of the pass
-    };
-    std::vector<Item> items;
-    std::vector<pc::RowJob> rows;
-    std::vector<pc::ColJob> cols;
-    pc::MergedTw tw = {};
-    int lds = 0;
-    std::vector<pc::RowJob>& jobs(const pc::RowJob*) { return rows; }
-    std::vector<pc::ColJob>& jobs(const pc::ColJob*) { return cols; }
-  } merged[4];
+  Merged merged[pc::MK_KINDS];  // merged passes
 };
-
-// A merged block's share of its pass, the order of the list: the chip takes
-// blocks roughly in list order, so the short ones fill its last round.  Row
-// blocks: by length alone, which keeps the neighbours of xcd_major_blocks
-// together.
-int merged_work(const pc::RowJob&, int, int L) { return L; }
-int merged_work(const pc::ColJob& j, int kind, int L) {
-  const int terms = kind == pc::MK_COLS_ADJ ? j.m1 : j.m1 * j.m2 / j.ngroups;
-  return (terms + 1) * pc::points_per_thread(L);
-}
 
 template <class J>
 pc_status batch_set(pc_batch b, std::vector<pc::LaunchSet>& seq, int kind, int L, const std::vector<J>& jobs,
                     const std::vector<pc::BlockRef>& bm, const float2* tw, bool multi_term = true,
                     bool small_rows = false, BatchLists* pl = nullptr, int mkind = -1, int msub = 0) {
   if (jobs.empty()) return PC_SUCCESS;
-  if (pl && b->merged && pc::merged_index(L) >= 0) {
-    BatchLists::Merged& mg = pl->merged[mkind];
-    std::vector<J>& all = mg.jobs(jobs.data());
-    const int j0 = (int)all.size();
-    all.insert(all.end(), jobs.begin(), jobs.end());
-    for (pc::BlockRef r : bm) {
-      const int work = merged_work(jobs[(size_t)r.job], mkind, L);
-      r.job += j0;
-      mg.items.push_back({pc::MergedBlock{r, L, msub}, work});
-    }
-    mg.tw.tw[pc::merged_index(L)] = tw;
-    mg.lds = std::max(mg.lds, pc::merged_lds_bytes(mkind, L));
+  const bool rows = kind == pc::KK_ROWS_FWD || kind == pc::KK_ROWS_INV;
+  if (pl && (rows ? b->merged_rows : b->merged_cols) && pc::merged_index(L) >= 0) {
+    collect_merged(pl->merged[mkind], jobs, bm, tw, mkind, L, msub);
     return PC_SUCCESS;
   }
   J* dj = nullptr;
@@ -947,7 +1015,6 @@ pc_status batch_set(pc_batch b, std::vector<pc::LaunchSet>& seq, int kind, int L
   if (st) return st;
   if ((st = b->upload(&db, bm))) return st;
   pc::LaunchSet ls;
-  const bool rows = kind == pc::KK_ROWS_FWD || kind == pc::KK_ROWS_INV;
   ls.kind = kind;
   ls.L = L;
   ls.threads = rows ? pc::row_threads(L, small_rows) : pc::col_threads(L);
@@ -1074,6 +1141,14 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
     if (std::find(n2s.begin(), n2s.end(), x.q->p2.N2) == n2s.end()) n2s.push_back(x.q->p2.N2);
     if (std::find(n1s.begin(), n1s.end(), x.q->p2.N1) == n1s.end()) n1s.push_back(x.q->p2.N1);
   }
+  if (gather) {
+    b->merged_rows = several_merged(n2s);
+    b->merged_cols = several_merged(n1s);
+  }
+  // a sectioned plan's jobs have one term and one plane
+  const int mk_inv = gather ? pc::MK_ROWS_INV1 : pc::MK_ROWS_INV;
+  const int mk_cfwd = gather ? (keep ? pc::MK_COLS_KEEP1 : pc::MK_COLS_FWD1) : pc::MK_COLS_FWD;
+  const int mk_cadj = gather ? pc::MK_COLS_ADJ1 : pc::MK_COLS_ADJ;
   BatchLists lists[2];  // [0]: pc_batch_apply, [1]: pc_batch_apply_adjoint
   // Blocks are listed instance by instance, the instances with the most
   // terms first: a block's work grows with its instance's terms, and the
@@ -1127,7 +1202,7 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
       const bool sf = pc::tune_get(b->tune_key, PC_TUNE_ROWS_FWD_SMALL, L2, 0) != 0;  // row tiles
       const bool si = pc::tune_get(b->tune_key, PC_TUNE_ROWS_INV_SMALL, L2, 0) != 0;
       // the merged row passes have blocks of their own heights
-      const int pbr = b->merged ? pc::merged_block_rows(L2) : 0;
+      const int pbr = b->merged_rows ? pc::merged_block_rows(L2) : 0;
       std::vector<pc::RowJob> jf, jfo, ja, jao;
       std::vector<pc::BlockRef> bf, bfo, ba, bao;
       const float2* tw = nullptr;
@@ -1203,24 +1278,24 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
       }
       if ((st = batch_set(b, bl.f_rows_in, pc::KK_ROWS_FWD, L2, jf, bf, tw, true, sf, &bl, pc::MK_ROWS_FWD)))
         return st;
-      if ((st = batch_set(b, bl.f_rows_out, pc::KK_ROWS_INV, L2, jfo, bfo, tw, true, si, &bl, pc::MK_ROWS_INV, 1)))
+      if ((st = batch_set(b, bl.f_rows_out, pc::KK_ROWS_INV, L2, jfo, bfo, tw, true, si, &bl, mk_inv, 1)))
         return st;
       if (gather && !ba.empty()) {
         // the sections' output boxes overlap: the adjoint's row-forward
         // blocks over the same image rows (same band of the row-block
         // height from the box origin) share their lines
-        const int br = pc::row_block_rows(L2, sf);
+        const int rb = pbr ? pbr : pc::row_block_rows(L2, sf), br = std::max(16, rb);  // whole lines
         std::vector<int64_t> band(ba.size());
         for (size_t k = 0; k < ba.size(); ++k) {
           const pc::RowJob& j = ja[(size_t)ba[k].job];
-          const int64_t r = ((int64_t)j.g1 + (int64_t)ba[k].blk * br) % (j.gN1 > 0 ? j.gN1 : 1);
+          const int64_t r = ((int64_t)j.g1 + (int64_t)ba[k].blk * rb) % (j.gN1 > 0 ? j.gN1 : 1);
           band[k] = (int64_t)ba[k].img * 1000003 + r / br;
         }
         xcd_group_blocks(ba, band);
       }
       if ((st = batch_set(b, bl.a_rows_in, pc::KK_ROWS_FWD, L2, ja, ba, tw, true, sf, &bl, pc::MK_ROWS_FWD)))
         return st;
-      if ((st = batch_set(b, bl.a_rows_out, pc::KK_ROWS_INV, L2, jao, bao, tw, true, si, &bl, pc::MK_ROWS_INV)))
+      if ((st = batch_set(b, bl.a_rows_out, pc::KK_ROWS_INV, L2, jao, bao, tw, true, si, &bl, mk_inv)))
         return st;
     }
     for (int L1 : n1s) {
@@ -1246,7 +1321,7 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
           if (st) {
             jf.back().nvalid_in = st->ea1;  // the row pass transformed the window box rows only
             // the row-inverse pass reads whole row blocks of the output box rows
-            const int br = pc::row_block_rows(q.N2, pc::tune_get(b->tune_key, PC_TUNE_ROWS_INV_SMALL, q.N2, 0) != 0);
+            const int br = inv_block_rows(b, q.N2);
             jf.back().nvalid_out = std::min(q.N1, (st->ef1 + br - 1) / br * br);
           }
           if (keep) {
@@ -1263,54 +1338,30 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
           pc::ColJob j{q.Tws, q.RA, nullptr, q.Hs, q.wrows, plane * cap, 0, q.H2, q.m1, q.m2, dense, 1};
           j.fft_src = own ? 1 : 0;
           if (st) {  // the row-inverse pass reads whole row blocks of the window box rows
-            const int br = pc::row_block_rows(q.N2, pc::tune_get(b->tune_key, PC_TUNE_ROWS_INV_SMALL, q.N2, 0) != 0);
+            const int br = inv_block_rows(b, q.N2);
             j.nvalid_out = std::min(q.N1, (st->ea1 + br - 1) / br * br);
             j.nvalid_in = st->ef1;  // the row pass transformed the output box rows only
           }
           ja.push_back(j);
         }
       }
-      if ((st = batch_set(b, bl.f_cols, pc::KK_COLS_FWD, L1, jf, bf, tw, f_multi, false, &bl, pc::MK_COLS_FWD)))
+      if ((st = batch_set(b, bl.f_cols, pc::KK_COLS_FWD, L1, jf, bf, tw, f_multi, false, &bl, mk_cfwd)))
         return st;
       if ((st = batch_set(b, bl.a_fft, pc::KK_COLS_FFT, L1, jt, bt, tw, true, false, &bl, pc::MK_COLS_FWD, 1)))
         return st;
-      if ((st = batch_set(b, bl.a_cols, pc::KK_COLS_ADJ, L1, ja, ba, tw, true, false, &bl, pc::MK_COLS_ADJ))) return st;
+      if ((st = batch_set(b, bl.a_cols, pc::KK_COLS_ADJ, L1, ja, ba, tw, true, false, &bl, mk_cadj))) return st;
     }
   }
   for (int c = 0; c < 2; ++c) {
     BatchLists& bl = lists[c];
-    std::vector<pc::LaunchSet> merged[4];
-    for (int k = 0; k < 4; ++k) {
-      BatchLists::Merged& mg = bl.merged[k];
-      if (mg.items.empty()) continue;
-      std::stable_sort(mg.items.begin(), mg.items.end(),
-                       [](const BatchLists::Merged::Item& x, const BatchLists::Merged::Item& y) { return x.work > y.work; });
-      std::vector<pc::MergedBlock> blocks;
-      blocks.reserve(mg.items.size());
-      for (const BatchLists::Merged::Item& x : mg.items) blocks.push_back(x.blk);
-      const bool rows = k == pc::MK_ROWS_FWD || k == pc::MK_ROWS_INV;
-      pc::MergedBlock* db = nullptr;
-      pc::RowJob* dr = nullptr;
-      pc::ColJob* dc = nullptr;
-      if ((st = b->upload(&db, blocks)) || (st = rows ? b->upload(&dr, mg.rows) : b->upload(&dc, mg.cols))) return st;
-      pc::LaunchSet ls;
-      ls.kind = k == pc::MK_ROWS_FWD   ? pc::KK_ROWS_FWD
-                : k == pc::MK_ROWS_INV ? pc::KK_ROWS_INV
-                : k == pc::MK_COLS_FWD ? pc::KK_COLS_FWD
-                                       : pc::KK_COLS_ADJ;
-      ls.merged = k;
-      ls.mblocks = db;
-      ls.jobs = rows ? static_cast<const void*>(dr) : dc;
-      ls.mtw = mg.tw;
-      ls.lds_bytes = mg.lds;
-      ls.blocks = (int64_t)blocks.size();
-      ls.threads = pc::MERGED_THREADS;
-      merged[k].push_back(ls);
+    std::vector<pc::LaunchSet> merged[pc::MK_KINDS];
+    for (int k = 0; k < pc::MK_KINDS; ++k) {
+      auto up = [&](auto** d, const auto& host) { return b->upload(d, host); };
+      if ((st = finish_merged(bl.merged[k], k, merged[k], up))) return st;
     }
     std::vector<pc::LaunchSet>& seq = c == 0 ? b->fwd_seq : b->adj_seq;
-    for (auto* v : {&merged[pc::MK_ROWS_FWD], &bl.f_rows_in, &bl.a_rows_in, &merged[pc::MK_COLS_FWD], &bl.f_cols,
-                    &bl.a_fft, &merged[pc::MK_COLS_ADJ], &bl.a_cols, &merged[pc::MK_ROWS_INV], &bl.f_rows_out,
-                    &bl.a_rows_out})
+    for (auto* v : {&merged[pc::MK_ROWS_FWD], &bl.f_rows_in, &bl.a_rows_in, &merged[mk_cfwd], &bl.f_cols, &bl.a_fft,
+                    &merged[mk_cadj], &bl.a_cols, &merged[mk_inv], &bl.f_rows_out, &bl.a_rows_out})
       seq.insert(seq.end(), v->begin(), v->end());
     // the overlap-add of each sectioned plan of a user batch, into the
     // table's output entry (a sectioned plan's own calls add it themselves)
@@ -1429,6 +1480,7 @@ pc_status build_sec_bwd(pc_plan p, const std::vector<pc::SecTerm>& terms, bool k
   for (int gu = 0; gu < 2; ++gu) {
     std::vector<pc::LaunchSet>& seq = p->sec_bwd[gu][kept ? 1 : 0];
     seq.clear();
+    Merged mg;
     for (int L1 : lens) {
       std::vector<pc::ColJob> jobs;
       std::vector<pc::BlockRef> bm;
@@ -1445,7 +1497,7 @@ pc_status build_sec_bwd(pc_plan p, const std::vector<pc::SecTerm>& terms, bool k
         tw = q.tw1;
         pc::ColJob j{q.Tws, q.RA, nullptr, q.Hs, nullptr, plane * cap, 0, q.H2, 1, 1, 1, 1};
         const pc::SecTerm& t = terms[i];
-        const int br = pc::row_block_rows(q.N2, pc::tune_get(p->tune_key, PC_TUNE_ROWS_INV_SMALL, q.N2, 0) != 0);
+        const int br = inv_block_rows(p->sec_batch, q.N2);
         j.nvalid_in = t.ea1;
         j.nvalid_out = std::min(q.N1, (t.ea1 + br - 1) / br * br);
         j.nv_src = t.ef1;
@@ -1461,12 +1513,18 @@ pc_status build_sec_bwd(pc_plan p, const std::vector<pc::SecTerm>& terms, bool k
         jobs.push_back(j);
       }
       if (jobs.empty()) continue;
+      if (p->sec_batch->merged_cols && pc::merged_index(L1) >= 0) {
+        collect_merged(mg, jobs, bm, tw, pc::MK_COLS_BWD1, L1, 0);
+        continue;
+      }
       pc::LaunchSet ls;
       pc_status st = make_set(p, ls, pc::KK_COLS_BWD1, L1, jobs, bm, 0, tw, nullptr);
       if (st) return st;
       ls.blocks_per_img = 0;
       seq.push_back(ls);
     }
+    auto up = [&](auto** d, const auto& host) { return p->upload(d, host, nullptr); };
+    if (pc_status st = finish_merged(mg, pc::MK_COLS_BWD1, seq, up)) return st;
   }
   return PC_SUCCESS;
 }
@@ -2100,7 +2158,7 @@ pc_status pc_batch_create(pc_batch* out, int32_t count, const pc_plan* plans, ui
     for (pc_plan q : b->plans) ds.push_back(q->d);
     b->tune_key = pc::tune_batch_key(ds);
   }
-  b->merged = (flags & PC_BATCH_PERSISTENT) || pc::tune_get(b->tune_key, PC_TUNE_BATCH_PERSISTENT, 0, 1) != 0;
+  b->merged_rows = b->merged_cols = (flags & PC_BATCH_PERSISTENT) || pc::tune_get(b->tune_key, PC_TUNE_BATCH_PERSISTENT, 0, 1) != 0;
   b->use_graph = !(flags & PC_BATCH_NO_GRAPH);
   DeviceGuard g(device);
   const size_t tab_bytes = (size_t)4 * count * sizeof(float*);

@@ -239,9 +239,13 @@ struct BlockRef {
 
 enum KernelKind { KK_ROWS_FWD = 0, KK_ROWS_INV, KK_COLS_FWD, KK_COLS_ADJ, KK_COLS_FFT, KK_COLS_BWD1, KK_SEC_SCATTER };
 
-// Merged batch passes: the blocks of a pass over every transform length up
-// to 512, in one launch.
-enum MergedKind { MK_ROWS_FWD = 0, MK_COLS_FWD = 1, MK_COLS_ADJ = 2, MK_ROWS_INV = 3 };
+// Merged passes of a batch or a sectioned plan: the blocks of a pass over
+// every transform length up to 512, in one launch.  The kinds ending in 1 are
+// the sections' (one term, one plane), without the registers of the others.
+enum MergedKind {
+  MK_ROWS_FWD = 0, MK_COLS_FWD, MK_COLS_ADJ, MK_ROWS_INV,
+  MK_COLS_FWD1, MK_COLS_KEEP1, MK_COLS_ADJ1, MK_ROWS_INV1, MK_COLS_BWD1, MK_KINDS
+};
 struct MergedBlock {
   BlockRef bm;  // (job: index into the launch's one job table)
   int L;        // transform length

@@ -103,6 +103,43 @@ def test_sectioned_backward_matches_oracle(idx, mode):
     assert err <= TOL
 
 
+# sections of several lengths, whose blocks share one launch per pass: columns
+# and rows of 96 to 192, of 96 to 256 in different orders with three images,
+# columns of 256 to 512 and rows of 128 to 384, columns beyond 512 beside them
+SEVERAL = [(512, 512, 8, 8, 2, (0.6, 4.0), (0.6, 4.0)), (256, 512, 4, 8, 3, (0.5, 4.0), (0.5, 5.0)),
+           (768, 512, 4, 8, 1, (0.8, 6.0), (0.6, 6.0)), (1536, 512, 8, 8, 1, (1.0, 20.0), (0.6, 1.0))]
+
+
+@pytest.mark.parametrize("case", SEVERAL, ids=lambda c: f"{c[0]}x{c[1]}b{c[4]}")
+@pytest.mark.parametrize("mode", ["kept", "recomputed"])
+def test_sections_of_several_lengths(case, mode):
+    # TOL is the file's
+    import torch
+    import paper_1604_04374_amd as pcm
+    n1, n2, m1, m2, batch, sy, sx = case
+    p = wl.small_2d(n1, n2, m1, m2, batch, seed=64, kind="tile", sig_y_fn=lambda a, b: sy[0] + sy[1] * (a + b) / 1024.0,
+                    sig_x_fn=lambda a, b: sx[0] + sx[1] * (a + b) / 1024.0)
+    print(f"[gpu] sections of several lengths {p.name} ({mode})", flush=True)
+    gy = np.random.default_rng(65).standard_normal(p.u.shape).astype(np.float32)
+    u = torch.from_numpy(p.u).cuda()
+    with pcm.Plan(plan_args(p), p.h, batch=p.batch, gradients=True) as plan:
+        if mode == "recomputed":
+            plan.set_budget(0)
+        secs = _secs(plan)
+        assert len({s["m1"] for s in secs}) > 1 and len({(s["m1"], s["m2"]) for s in secs}) > 2
+        y = plan.apply_save(u)
+        gu, gs = plan.backward(u, torch.from_numpy(gy).cuda(), use_saved=True)
+        part = plan.apply(u[:1].contiguous())  # a partial batch leaves the other images' blocks out
+        torch.cuda.synchronize()
+        y, gu, gs, part = y.cpu().numpy(), gu.cpu().numpy(), gs.cpu().numpy(), part.cpu().numpy()
+    w, h = p.dense_windows(), p.h.astype(np.float64)
+    uu, g64 = p.u.astype(np.float64), gy.astype(np.float64)
+    assert max(rel_l2(a, b) for a, b in zip(y, ex.apply_fft(uu, w, h))) <= TOL
+    assert max(rel_l2(a, b) for a, b in zip(gu, ex.adjoint_fft(g64, w, h))) <= TOL
+    assert max(rel_l2(a, b) for a, b in zip(_split(gs, secs), sc.grad_section_spectra(uu, g64, w, secs))) <= TOL
+    assert np.array_equal(part[0], y[0])
+
+
 def test_tuning_table_can_choose_recomputing():
     # a table entry "keep" = 0 makes a gradient plan recompute the windowed
     # spectra in the backward although they fit its budget; results unchanged
