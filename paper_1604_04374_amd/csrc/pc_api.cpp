@@ -1454,15 +1454,19 @@ pc_status create_plan(const pc_plan_desc& d, const float* windows, const float* 
 
 pc_status make_transpose_set(pc_plan p, pc::TransposeSet& ts, std::vector<pc::TransposeJob> jobs) {
   int64_t b0 = 0;
+  std::vector<int> job_of;
   for (pc::TransposeJob& j : jobs) {
     j.block0 = b0;
     b0 += pc::transpose_blocks(j.N1, j.H2);
+    job_of.resize((size_t)b0, (int)(&j - jobs.data()));
   }
   pc::TransposeJob* dj = nullptr;
   pc_status st = p->upload(&dj, jobs, nullptr);
   if (st) return st;
+  int* djo = nullptr;
+  if ((st = p->upload(&djo, job_of, nullptr))) return st;
   ts.jobs = dj;
-  ts.njobs = (int)jobs.size();
+  ts.job_of = djo;
   ts.blocks = b0;
   return PC_SUCCESS;
 }

@@ -402,8 +402,8 @@ struct TransposeJob {
 };
 struct TransposeSet {
   const TransposeJob* jobs = nullptr;  // device
-  int njobs = 0;
-  int64_t blocks = 0;
+  const int* job_of = nullptr;         // device: each tile's job
+  int64_t blocks = 0;                  // tiles
 };
 // workgroups of one plane
 int64_t transpose_blocks(int N1, int H2);
