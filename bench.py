@@ -135,7 +135,7 @@ def algorithmic_counts(p, info):
         # and the reverse on the way out); the column passes move those planes
         # and the spectra
         kb = {"cols_fwd": B * (nq + 1) * plane + spec_bytes, "cols_adj": B * (nq + 1) * plane + spec_bytes,
-              "cols_fft": 2 * B * plane, "cols_sum": B * 2 * plane,
+              "cols_fft": 2 * B * plane,
               "rows_fwd": B * (2 * ntot * 4 + (nq + 1) * plane), "rows_inv": B * (2 * ntot * 4 + (nq + 1) * plane)}
     bytes_dir = B * ntot * 4 * 2 + m * (ntot // p.shape[-1]) * (p.shape[-1] // 2 + 1) * 8 + support_sum * 4
     return {"flops_per_step": 2 * B * per_sig, "bytes_per_step": 2 * bytes_dir, "kernel_flops": kf,
