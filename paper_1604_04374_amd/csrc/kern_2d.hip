@@ -541,6 +541,81 @@ __global__ __launch_bounds__(G * fft_threads(L2)) void k_rows_inv(
   rows_inv_body<L2, G, PIPE, ONE, SUM>(jobs, bm, y_arg, lds, twl, tw, rfac, threadIdx.x);
 }
 
+// The same for jobs of several windowed planes where the launch leaves most
+// of the chip idle (rows_inv_side): QP groups of G * T threads take the
+// planes q, q + QP, ... side by side, nq a multiple of QP, and their sums are
+// added through LDS.  The pass, bound by one workgroup's chain of loads and
+// transforms, is then one plane's chain long instead of nq (us per adjoint:
+// 192 x 384, 3 planes 23.9 -> 21.2; 256 x 256, 3 17.7 -> 15.6; 512 x 512, 4 23.4
+// -> 21.3; 1024 x 1024, 4 44.5 -> 43.2; 768 x 768, 4 38.5 -> 35.7).
+template <int L2, int QP>
+constexpr bool side_fits() {
+  constexpr int G = row_pairs_small(L2);
+  return G * fft_threads(L2) * QP <= 1024 && (QP * G * lds_len<L2>() + L2) * (int)sizeof(float2) <= 156 * 1024;
+}
+template <int L2, int QP>
+__global__ __launch_bounds__(row_pairs_small(L2) * fft_threads(L2) * QP) void k_rows_inv_side(
+    const RowJob* __restrict__ jobs, const BlockRef* __restrict__ bmap, float* __restrict__ y_arg,
+    const float2* __restrict__ tw, int64_t img_limit) {
+  constexpr int G = row_pairs_small(L2), P = points_per_thread(L2), T = L2 / P, H2 = L2 / 2 + 1;
+  constexpr int NT = G * T, REG = G * lds_len<L2>(), CH = H2 * G, PS = (CH + NT - 1) / NT;
+  static_assert(REG % 2 == 0 && CH * 2 <= REG, "each group's tile in its own region, 16-byte aligned");
+  __shared__ __attribute__((aligned(16))) float2 lds[QP * REG];
+  __shared__ float2 twl[L2];
+  const BlockRef bm = bmap[blockIdx.x];
+  if (bm.img >= img_limit) return;  // uniform over the workgroup
+  const int tid = threadIdx.x, g = tid / NT, gt = tid % NT;
+  TwStage<L2, NT * QP> ts;
+  ts.load(tw, tid);
+  const RowJob& jb = jobs[bm.job];
+  const int N1 = jb.N1;
+  const int c = gt / T, t = gt % T;
+  const int64_t img = bm.img;
+  const int r0 = bm.blk * 2 * G, r = r0 + 2 * c;
+  float2* region = lds + g * REG;
+  float4* tl = reinterpret_cast<float4*>(region);
+  const float2* src0 = jb.sin + img * ((int64_t)H2 * N1) + r0;
+  float2 acc[P];
+#pragma unroll
+  for (int e = 0; e < P; ++e) acc[e] = make_float2(0.f, 0.f);
+  for (int q = g; q < jb.nq; q += QP) {  // as many rounds in every group
+    const float2* src = src0 + (int64_t)q * jb.q_stride;
+    float4 v[PS];
+#pragma unroll
+    for (int i = 0; i < PS; ++i) {
+      const int ch = gt + i * NT;
+      if (ch < CH) v[i] = gld2(src, (int64_t)(ch / G) * N1 + 2 * ((ch % G) ^ tile_swz<G>(ch / G)));
+    }
+    if (q == g)
+      ts.commit(twl, tid);
+    else
+      __syncthreads();  // the previous transform is done with LDS
+#pragma unroll
+    for (int i = 0; i < PS; ++i) {
+      const int ch = gt + i * NT;
+      if (ch < CH) tl[ch] = v[i];
+    }
+    __syncthreads();
+    rows_inv_plane<L2, G>(jb, q, jb.mode, jb.wsrc, r, tl, region + c * lds_len<L2>(), twl, c, t, acc);
+  }
+  __syncthreads();
+  if (g > 0) {
+#pragma unroll
+    for (int e = 0; e < P; ++e) region[e * NT + gt] = acc[e];
+  }
+  __syncthreads();
+  if (g > 0) return;
+#pragma unroll
+  for (int k = 1; k < QP; ++k)
+#pragma unroll
+    for (int e = 0; e < P; ++e) {
+      const float2 a = lds[k * REG + e * NT + gt];
+      acc[e].x += a.x;
+      acc[e].y += a.y;
+    }
+  rows_inv_store<L2>(jb, y_arg, img, r, t, jb.scale, jb.scale, acc);
+}
+
 // ---------------------------------------------------------------------------
 // column kernels: NF columns per workgroup, each column contiguous
 // ---------------------------------------------------------------------------
@@ -1277,6 +1352,47 @@ int col_groups_for(int L1, int H2, int64_t batch, int nq) {
 // chip.
 bool adj_own_fft(int m1, int64_t slots) { return m1 >= 2 || slots <= 4096; }
 
+// Planes side by side (k_rows_inv_side) for a small-tile row-inverse launch
+// of nq windowed planes, or 0: where the planes' groups fit the chip together
+// (1024 x 1024, 4 planes: 4096 wavefronts, 16 per CU, as many as its LDS
+// regions leave room for); beyond, the groups of one tile would only wait
+// for the next round of workgroups.
+template <int L2>
+static int side_of(int nq, int64_t blocks) {
+  const int64_t waves = blocks * row_pairs_small(L2) * fft_threads(L2) / 64;
+  if (side_fits<L2, 4>() && nq % 4 == 0 && waves * 4 <= 4096) return 4;
+  if (side_fits<L2, 3>() && nq % 3 == 0 && waves * 3 <= 4096) return 3;
+  if (side_fits<L2, 2>() && nq % 2 == 0 && waves * 2 <= 4096) return 2;
+  return 0;
+}
+int rows_inv_side(int L2, int nq, int64_t blocks) {
+  switch (L2) {
+#define PC_CASE(LL) \
+  case LL:          \
+    return side_of<LL>(nq, blocks);
+    PC_FOR_EACH_L2(PC_CASE)
+#undef PC_CASE
+  }
+  return 0;
+}
+template <int L2, int QP>
+static LaunchStatus launch_side_q(const LaunchSet& ls, dim3 grid, hipStream_t s, const RowJob* rj, float* y_arg,
+                                  int64_t img_limit) {
+  if constexpr (side_fits<L2, QP>()) {
+    hipLaunchKernelGGL((k_rows_inv_side<L2, QP>), grid, dim3(row_pairs_small(L2) * fft_threads(L2) * QP), 0, s, rj,
+                       ls.bmap, y_arg, ls.tw, img_limit);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+template <int L2>
+static LaunchStatus launch_side(const LaunchSet& ls, dim3 grid, hipStream_t s, const RowJob* rj, float* y_arg,
+                                int64_t img_limit) {
+  return ls.side == 4   ? launch_side_q<L2, 4>(ls, grid, s, rj, y_arg, img_limit)
+         : ls.side == 3 ? launch_side_q<L2, 3>(ls, grid, s, rj, y_arg, img_limit)
+                        : launch_side_q<L2, 2>(ls, grid, s, rj, y_arg, img_limit);
+}
+
 LaunchStatus launch_set(const LaunchSet& ls, int64_t nblocks, const float* x_arg, float* y_arg, hipStream_t s,
                         Tracer* tr, int64_t img_limit) {
   if (nblocks <= 0) return hipSuccess;
@@ -1306,6 +1422,8 @@ LaunchStatus launch_set(const LaunchSet& ls, int64_t nblocks, const float* x_arg
       switch (ls.L) {
 #define PC_CASE(LL) \
   case LL:          \
+    if (ls.side)  \
+      return launch_side<LL>(ls, grid, s, rj, y_arg, img_limit);  \
     if (ls.small_rows && ls.sum)  \
       hipLaunchKernelGGL((k_rows_inv<LL, row_pairs_small(LL), false, true, true>), grid, block, 0, s, rj, ls.bmap, y_arg, ls.tw, img_limit); \
     else if (ls.sum)  \

@@ -642,6 +642,14 @@ pc_status make_set(pc_plan p, pc::LaunchSet& ls, int kind, int L, const std::vec
   ls.pipe = kind == pc::KK_ROWS_INV &&
             pc::tune_get(key, PC_TUNE_ROWS_INV_PIPE, L, !ls.one_plane && pc::rows_inv_pipe(L, ls.small_rows));
   ls.sum = kind == pc::KK_ROWS_INV && sums_planes(jobs);
+  if constexpr (std::is_same<J, pc::RowJob>::value) {
+    // one windowed job of several planes, unless the tuning table asks for one
+    // of the variants that take them in turn
+    const pc::RowJob& j = jobs[0];
+    if (kind == pc::KK_ROWS_INV && ls.small_rows && jobs.size() == 1 && (j.mode == 1 || j.mode == 2) && j.oN2 == 0 &&
+        j.ocols == 0 && pc::tune_get(key, PC_TUNE_ROWS_INV_PIPE, L, -1) < 0)
+      ls.side = pc::rows_inv_side(L, j.nq, (int64_t)bm.size());
+  }
   ls.jobs = dj;
   ls.bmap = db;
   ls.blocks = (int64_t)bm.size();

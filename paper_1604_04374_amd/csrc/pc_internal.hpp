@@ -280,6 +280,7 @@ struct LaunchSet {
   bool pipe = false;               // row-inverse kernel: the pipelined variant (rows_inv_pipe)
   bool one_plane = false;          // row-inverse kernel: every job sums one plane (its ONE variant)
   bool sum = false;                // row-inverse kernel: windowless jobs, some of several planes (its SUM variant)
+  int side = 0;                    // row-inverse kernel: planes side by side (rows_inv_side)
   bool keep = false;               // forward column kernel: the variant storing U_k (jobs' keep pointers)
   bool one = false;                // column kernels: every job single-term (k_cols_1term)
   // merged pass (merged >= 0: a MergedKind): its blocks (device), the
@@ -324,6 +325,8 @@ int col_groups_for(int L1, int H2, int64_t batch, int nq);
 // Whether the adjoint column pass of a plan of several terms transforms its
 // input itself, in every column slot of m1 terms, instead of a pass before it.
 bool adj_own_fft(int m1, int64_t slots);
+// Planes a small-tile row-inverse launch transforms side by side (0: in turn)
+int rows_inv_side(int L2, int nq, int64_t blocks);
 
 // ---------------------------------------------------------------------------
 // Tuning table (tune.cpp): measured choices of the per-length variants for

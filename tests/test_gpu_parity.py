@@ -253,3 +253,29 @@ def test_fourstep_split_choice(n, m, deg, expect):
         info = plan.info()
     assert info["path"] == 1
     assert (info["fft_inner"], info["fft_outer"], info["n_items"]) == expect
+
+
+# adjoints whose planes are transformed side by side: two, three and four
+# planes, two rounds of four, several images, groups of half a wavefront (192)
+# and of a workgroup's most threads (1024), the longest length, dense windows,
+# and a plane count that none divides
+SIDE = [(64, 512, 2, 2, 1, False), (64, 192, 2, 3, 2, False), (64, 1024, 1, 4, 1, False), (96, 64, 3, 8, 3, False),
+        (64, 2048, 2, 2, 1, False), (64, 256, 2, 3, 1, True), (128, 384, 1, 5, 1, False)]
+
+
+@pytest.mark.parametrize("case", SIDE, ids=lambda c: f"{c[0]}x{c[1]}q{c[3]}b{c[4]}{'d' if c[5] else ''}")
+def test_adjoint_planes_side_by_side(case):
+    # TOL is the file's; a smaller batch runs the same blocks
+    import torch
+    import paper_1604_04374_amd as pcm
+    n1, n2, m1, m2, batch, dense = case
+    p = wl.small_2d(n1, n2, m1, m2, batch, seed=91, kind="hat")
+    print(f"[gpu] planes side by side {p.name}", flush=True)
+    v = torch.from_numpy(p.u).cuda()
+    args = p.dense_windows().astype(np.float32) if dense else plan_args(p)
+    with pcm.Plan(args, p.h, batch=batch, full_grid=True) as plan:
+        x = plan.apply_adjoint(v).cpu().numpy()
+        part = plan.apply_adjoint(v[:1].contiguous()).cpu().numpy()
+    _, rx = oracle_fft(p)
+    assert per_instance_rel(x, rx) <= TOL
+    assert np.array_equal(part[0], x[0])
