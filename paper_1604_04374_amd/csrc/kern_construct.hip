@@ -10,9 +10,8 @@
 // the path: it runs on the matrix cores in FP32 (v_mfma_f32_16x16x4f32), split
 // along n into chunks whose partial sums are added in float64; the m x m
 // inverse or factorisation and the per-row solves are float64.
-#include <algorithm>
-
 #include "pc_internal.hpp"
+#include "project_tile.hpp"
 
 namespace pc {
 
@@ -52,39 +51,39 @@ __global__ __launch_bounds__(256) void k_gemm_nt_f32(const float* __restrict__ A
   const int c0 = (int)blockIdx.y * GEMM_COLS;
   const int64_t k_begin = (int64_t)blockIdx.z * seg_stages * GEMM_KT;
   const int64_t k_left = K - k_begin;
-  const int ns = (int)(k_left < (int64_t)seg_stages * GEMM_KT ? (k_left + GEMM_KT - 1) / GEMM_KT : seg_stages);
+  const int ns = gemm_stages(k_left, seg_stages);
   // rows and columns past the last read the last one; their sums are not stored
   const float* ap[AQ];
   const float* bp[BQ];
 #pragma unroll
   for (int j = 0; j < AQ; ++j) {
     const int64_t row = t0 + r + 16 * j < have ? t0 + r + 16 * j : have - 1;
-    ap[j] = (gram ? B : A) + row * K + k_begin + 4 * c;
+    ap[j] = (gram ? B : A) + row * K + k_begin;
   }
 #pragma unroll
   for (int j = 0; j < BQ; ++j) {
     const int col = c0 + r + 16 * j < cols ? c0 + r + 16 * j : cols - 1;
-    bp[j] = B + (int64_t)col * K + k_begin + 4 * c;
+    bp[j] = B + (int64_t)col * K + k_begin;
   }
   floatx4 ra0[AQ], rb0[BQ], ra1[AQ], rb1[BQ];
   auto load = [&](floatx4(&a)[AQ], floatx4(&b)[BQ], int s) {
-    // K need not be whole stages: chunks past its end count as zero (and
-    // stages past the segment's last are loaded and not used)
-    const bool in = (int64_t)s * GEMM_KT + 4 * c < k_left;
-    const int64_t o = in ? (int64_t)s * GEMM_KT : 0;
+    // (stages past the segment's last are loaded and not used)
+    const int64_t o = gemm_chunk_offset(s, c, k_left);
 #pragma unroll
     for (int j = 0; j < AQ; ++j) a[j] = *reinterpret_cast<const floatx4*>(ap[j] + o);
 #pragma unroll
-    for (int j = 0; j < BQ; ++j) {
-      const floatx4 v = *reinterpret_cast<const floatx4*>(bp[j] + o);
-      b[j] = in ? v : floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int j = 0; j < BQ; ++j) b[j] = *reinterpret_cast<const floatx4*>(bp[j] + o);
   };
-  auto put = [&](int buf, const floatx4(&a)[AQ], const floatx4(&b)[BQ]) {
+  auto put = [&](int buf, const floatx4(&a)[AQ], const floatx4(&b)[BQ], int s) {
+    // chunks past the row's end count as zero on both sides: a NaN or an
+    // infinity read in their place would turn the other side's zeros into NaN
+    const bool in = gemm_chunk_inside(s, c, k_left);
+    const floatx4 zero{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < AQ; ++j) As[buf][(r + 16 * j) * GEMM_CPR + (c ^ r)] = a[j];  // (r + 16 j) mod 16 = r
+    for (int j = 0; j < AQ; ++j)
+      As[buf][(r + 16 * j) * GEMM_CPR + (c ^ r)] = in ? a[j] : zero;  // (r + 16 j) mod 16 = r
 #pragma unroll
-    for (int j = 0; j < BQ; ++j) Bs[buf][(r + 16 * j) * GEMM_CPR + (c ^ r)] = b[j];
+    for (int j = 0; j < BQ; ++j) Bs[buf][(r + 16 * j) * GEMM_CPR + (c ^ r)] = in ? b[j] : zero;
   };
   const int g = lane >> 4, li = lane & 15;
   floatx4 acc0{0.f, 0.f, 0.f, 0.f}, acc1{0.f, 0.f, 0.f, 0.f};
@@ -118,7 +117,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt_f32(const float* __restrict__ A
   // stage s: stage s + 1 goes from its registers to the other buffer, whose
   // readers passed the barrier before; stage s + 3 is loaded in their place
   auto stage = [&](int s, floatx4(&a)[AQ], floatx4(&b)[BQ], int buf) {
-    put(buf ^ 1, a, b);
+    put(buf ^ 1, a, b, s + 1);
     load(a, b, s + 3);
     compute(buf);
     if ((s + 1) % (GEMM_CHUNK / GEMM_KT) == 0) flush();
@@ -126,7 +125,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt_f32(const float* __restrict__ A
   };
   load(ra0, rb0, 0);
   load(ra1, rb1, 1);
-  put(0, ra0, rb0);
+  put(0, ra0, rb0, 0);
   load(ra0, rb0, 2);
   __syncthreads();
   for (int s = 0; s < ns; s += 2) {
@@ -358,22 +357,6 @@ __global__ __launch_bounds__(256) void k_flip(const float* __restrict__ in, floa
 }
 
 static inline unsigned blocks_of(int64_t n) { return (unsigned)((n + 255) / 256); }
-
-// Stages per segment and segments of the contraction: about five workgroups
-// per CU (enough that the last round costs little), as few segments as that
-// needs.
-static int gemm_seg_stages(int64_t rows, int m, int64_t K) {
-  const int64_t tiles = ((rows + GEMM_ROWS - 1) / GEMM_ROWS + (m + GEMM_ROWS - 1) / GEMM_ROWS) *
-                        ((m + GEMM_COLS - 1) / GEMM_COLS);
-  const int64_t stages = (K + GEMM_KT - 1) / GEMM_KT;
-  const int64_t segs = std::min(stages, (1280 + tiles - 1) / tiles);
-  return (int)((stages + segs - 1) / segs);
-}
-
-int gemm_segments(int64_t rows, int m, int64_t K) {
-  const int64_t per = gemm_seg_stages(rows, m, K), stages = (K + GEMM_KT - 1) / GEMM_KT;
-  return (int)((stages + per - 1) / per);
-}
 
 LaunchStatus launch_project(const float* tvir, int64_t rows, const float* windows, int m, int64_t n, double* part,
                             double* inv, int* fail, const int64_t* lags, float* h, hipStream_t s) {

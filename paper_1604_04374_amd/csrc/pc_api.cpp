@@ -30,6 +30,7 @@
 #include "../../include/pc.h"
 #include "fft_engine.hpp"
 #include "pc_internal.hpp"
+#include "project_tile.hpp"
 
 namespace {
 

@@ -478,9 +478,7 @@ LaunchStatus launch_sec_scatter(const Sec2D& q, float* y, bool adjoint, int64_t 
 // Construction of h_k from a TVIR (section 4.2 projection, section 4.4
 // interpolation)
 // --------------------------------------------------------------------------
-constexpr int GEMM_ROWS = 64, GEMM_COLS = 32, GEMM_KT = 64, GEMM_CHUNK = 512;
 constexpr int CONSTRUCT_MAX_M = 128;
-int gemm_segments(int64_t rows, int m, int64_t K);
 // h = the projection of the TVIR rows onto the span of the windows (n % 16 ==
 // 0, rows of both 16-byte aligned): part holds gemm_segments x (rows + m) x m
 // values, inv m x m; *fail = 1 for numerically dependent windows

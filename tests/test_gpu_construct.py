@@ -83,6 +83,44 @@ def test_projection_tiles(n, m, rows):
     assert not h[:, rest].any()
 
 
+# a last stage of 16, 32 or 48 samples: alone in the row (16, 48), alone in its
+# segment (80, 1040, 2064, 4112) and behind whole stages (6000 with many rows)
+@pytest.mark.parametrize("n,m,rows", [(16, 1, 1), (16, 3, 16), (48, 5, 1), (48, 5, 48), (80, 3, 1), (80, 3, 65),
+                                      (1040, 9, 1), (1040, 33, 130), (2064, 33, 64), (4112, 49, 127), (6000, 16, 3000)])
+def test_projection_reads_nothing_beside_its_rows(n, m, rows):
+    """NaN right before and behind both operands and in one TVIR row: every
+    other lag is finite and what it is without them.  FP32 sums of at most 512
+    products err by about 512^(1/2) 2^-24 of their size, on both sides of the
+    system, the solve by the condition number times that."""
+    import torch
+    import paper_1604_04374_amd as pcm
+    print(f"[gpu] projection beside NaN n={n} m={m} rows={rows}", flush=True)
+    rng = np.random.default_rng(n + m + rows)
+    T = rng.standard_normal((rows, n)).astype(np.float32)
+    W = rng.standard_normal((m, n)).astype(np.float32)
+    lags = rng.permutation(n)[:rows]
+
+    def within_nan(a):
+        flat = torch.full((a.size + 128,), float("nan"), device="cuda")
+        flat[64:-64] = torch.from_numpy(a.ravel()).cuda()
+        return flat[64:-64].view(a.shape)
+
+    plain = pcm.construct_project(torch.from_numpy(T).cuda(), lags, torch.from_numpy(W).cuda()).cpu().numpy()
+    G = W.astype(np.float64) @ W.astype(np.float64).T
+    ref = np.linalg.solve(G, W.astype(np.float64) @ T.astype(np.float64).T) / n
+    tol = 2 * 512 ** 0.5 * 2.0 ** -24 * max(np.linalg.cond(G), 1.0)
+    assert rel_l2(plain[:, lags], ref) <= tol
+    Td, Wd = within_nan(T), within_nan(W)
+    assert np.array_equal(pcm.construct_project(Td, lags, Wd).cpu().numpy(), plain)
+    if rows > 1:
+        bad = rows // 2
+        Td[bad] = float("nan")
+        h = pcm.construct_project(Td, lags, Wd).cpu().numpy()
+        assert np.isnan(h[:, lags[bad]]).all()
+        h[:, lags[bad]] = plain[:, lags[bad]]
+        assert np.array_equal(h, plain)
+
+
 @pytest.mark.parametrize("n,m,deg", [(1024, 8, 1), (4096, 16, 3), (16384, 32, 3)])
 def test_interpolation_matches_oracle(n, m, deg):
     import torch
