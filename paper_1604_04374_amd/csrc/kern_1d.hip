@@ -62,13 +62,26 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_spec1d_f
   }
 }
 
+// Points per thread of the 1D kernels with no more than a pair's work in a
+// workgroup.  The large batches' kernels take 16 at 4096 points, where the
+// transform then needs one exchange less (390 pairs, 8 terms: 40 us at 8,
+// 31 at 16); 8 are the better elsewhere (1024 points, 3 terms, 8000 pairs:
+// 72 / 54 us per forward at 16 / 8; 128 points, 32 terms, 20000 pairs: 108 at
+// 4, 91 at 8).
+constexpr int split_points(int L) { return L % 3 == 0 ? 12 : L >= 8192 ? 16 : 8; }
+constexpr int split_threads(int L) { return L / split_points(L); }
+constexpr int wide_points(int L) { return L == 1024 ? 16 : 0; }  // (0: none)
+constexpr int plain_points(int L) { return L == 4096 ? 16 : split_points(L); }
+constexpr int plain_threads(int L) { return L / plain_points(L); }
+constexpr int plain_slots(int L) { return plain_threads(L) >= 256 ? 1 : 256 / plain_threads(L); }
+
 // y = H_m u for signal pairs, one pair per transform slot: batches with a
 // pair for every slot of the chip (k_small1d_split takes the others).
 template <int L>
-__global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_fwd1d_small(
+__global__ __launch_bounds__(plain_slots(L) * plain_threads(L)) void k_fwd1d_small(
     const float* __restrict__ u, float* __restrict__ y, int64_t batch, int m, const float* __restrict__ w,
     const float2* __restrict__ H, const float2* __restrict__ tw) {
-  constexpr int P = points_per_thread(L), T = L / P, NF = ffts_per_block(L);
+  constexpr int P = plain_points(L), T = L / P, NF = plain_slots(L);
   __shared__ float2 lds[NF * lds_len<L>()];
   __shared__ float2 twl[L];
   stage_twiddles<L>(twl, tw);
@@ -110,12 +123,16 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_fwd1d_sm
   }
 }
 
-// x = H_m^* v for signal pairs, one pair per transform slot.
+// x = H_m^* v for signal pairs, one pair per transform slot.  From 3072 points
+// on two waves per SIMD are asked for (4200 pairs of 3072 samples, 8 terms:
+// 351 us without, 280 with); shorter transforms need the waves (8000 pairs of
+// 1024, 3 terms: 75 us with, 54 without).
 template <int L>
-__global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_adj1d_small(
+__global__ __launch_bounds__(plain_slots(L) * plain_threads(L))
+    __attribute__((amdgpu_waves_per_eu(1, L >= 3072 ? 2 : 8))) void k_adj1d_small(
     const float* __restrict__ vin, float* __restrict__ x, int64_t batch, int m, const float* __restrict__ w,
     const float2* __restrict__ H, const float2* __restrict__ tw) {
-  constexpr int P = points_per_thread(L), T = L / P, NF = ffts_per_block(L);
+  constexpr int P = plain_points(L), T = L / P, NF = plain_slots(L);
   __shared__ float2 lds[NF * lds_len<L>()];
   __shared__ float2 twl[L];
   stage_twiddles<L>(twl, tw);
@@ -159,8 +176,9 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) __attribute__((
 
 // ---------------------------------------------------------------------------
 // Small batches: both directions with a pair's terms spread over the chip.
-// The terms go to G workgroups per pair and, inside one, to its NF transform
-// slots; slot (g, c) takes terms g NF + c, g NF + c + G NF, ...  By linearity
+// The terms go to G workgroups per pair and, inside one, to S = 2^ls of its NF
+// transform slots (the other slots take other pairs, so that none is idle);
+// slot s of workgroup g takes terms g S + s, g S + s + G S, ...  By linearity
 // every slot ends with its own share of the output samples (forward: its
 // spectral sum transformed back; adjoint: its windowed inverses); the slots'
 // shares are added in LDS, and with G > 1 the workgroups leave theirs in
@@ -177,22 +195,25 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) __attribute__((
 // that adds the shares instead of a second launch took 46 us where this
 // takes 13.6: every workgroup's device-scope fence writes its XCD's L2 back.
 // ---------------------------------------------------------------------------
-constexpr int split_points(int L) { return L % 3 == 0 ? 12 : L >= 8192 ? 16 : 8; }
-constexpr int split_threads(int L) { return L / split_points(L); }
-// (512 threads up to 1024 points: 8 terms of 1024 points in two rounds of
-// four slots 8.5 us, in four rounds of two 10.0)
-constexpr int split_slots(int L) { return split_threads(L) >= 256 ? 1 : (L <= 1024 ? 512 : 256) / split_threads(L); }
 
-template <int L, bool ADJ>
-__global__ __launch_bounds__(split_slots(L) * split_threads(L)) void k_small1d_split(
+template <int L, int P, int NT, bool ADJ>
+__global__ __launch_bounds__(NT) void k_small1d_split(
     const float* __restrict__ u, float* __restrict__ y, int64_t batch, int m, const float* __restrict__ w,
-    const float2* __restrict__ H, const float2* __restrict__ tw, int G, float2* __restrict__ part) {
-  constexpr int P = split_points(L), T = L / P, NF = split_slots(L), NT = NF * T;
+    const float2* __restrict__ H, const float2* __restrict__ tw, int ls, int G, float2* __restrict__ part) {
+  constexpr int T = L / P, NF = NT / T;
   // an exchange region per slot; at the end NF x L sums
   __shared__ float2 lds[NF * lds_len<L>()];
   __shared__ float2 twl[L];
-  const int tid = (int)threadIdx.x, c = tid / T, t = tid % T;
-  const int64_t pair = blockIdx.x / G;
+  // forward slots of whole wavefronts: the pair's and the terms' addresses are
+  // scalar (the adjoint is slower so, 8.7 and 9.0 us at 1 signal of 1024)
+  const int tid = (int)threadIdx.x, t = tid % T;
+  const int c = NF == 1 ? 0 : !ADJ && T % 64 == 0 ? __builtin_amdgcn_readfirstlane(tid / T) : tid / T;
+  const int slot = c & ((1 << ls) - 1);  // of its pair's
+  const int64_t pairs = (batch + 1) / 2;
+  const int64_t pair0 = (int64_t)(blockIdx.x / G) * (NF >> ls);  // the workgroup's first
+  const int64_t praw = pair0 + (c >> ls);
+  const bool have = praw < pairs;
+  const int64_t pair = have ? praw : pairs - 1;  // slots past the last pair run it again and store nothing
   const int g = (int)(blockIdx.x % G);
   TwStage<L, NT> ts;
   ts.load(tw, tid);
@@ -207,20 +228,29 @@ __global__ __launch_bounds__(split_slots(L) * split_threads(L)) void k_small1d_s
   }
   // a slot past the last term runs a valid one with zero weight (the
   // transforms may hold barriers)
-  const int step = G * NF, nk = (m - g * NF + step - 1) / step;  // g NF < m: the same count in every slot
-  auto term = [&](int i) { return g * NF + c + step * i; };
+  const int step = G << ls, nk = (m - (g << ls) + step - 1) / step;  // g S < m: the same count in every slot
+  auto term = [&](int i) { return (g << ls) + slot + step * i; };
+  // the factor that a term's transform needs first is loaded a term ahead, the
+  // other one beside the transform (both a term ahead: 176 registers instead
+  // of 147 at 768 points, two waves per SIMD instead of three: 42.4 and 34.3 us
+  // per forward of 1030 signals, 32 terms); both at once for the first term of
+  // short transforms, which cover less of a load (1 signal of 1024 samples:
+  // 18.1 and 17.7 us per forward and adjoint)
   float wv[P];
   float2 hv[P];
-  auto load = [&](int i) {
-    const int k = term(i) < m ? term(i) : m - 1;
-    const float* wk = w + (int64_t)k * L;
-    const float2* Hk = H + (int64_t)k * L;
+  auto load_w = [&](int i) {
+    const float* wk = w + (int64_t)(term(i) < m ? term(i) : m - 1) * L;
 #pragma unroll
     for (int e = 0; e < P; ++e) wv[e] = wk[t + T * e];
+  };
+  auto load_h = [&](int i) {
+    const float2* Hk = H + (int64_t)(term(i) < m ? term(i) : m - 1) * L;
 #pragma unroll
     for (int e = 0; e < P; ++e) hv[e] = Hk[t + T * e];
   };
-  load(0);
+  constexpr bool BOTH = L <= 1024;
+  if (BOTH || !ADJ) load_w(0);
+  if (BOTH || ADJ) load_h(0);
   float2* my = lds + c * lds_len<L>();
   ts.commit(twl, tid);
   if (!vb) {
@@ -238,37 +268,38 @@ __global__ __launch_bounds__(split_slots(L) * split_threads(L)) void k_small1d_s
   for (int i = 0; i < nk; ++i) {
     const float live = term(i) < m ? 1.f : 0.f;
     float2 v[P];
-    float wc[P];
-    float2 hc[P];
-#pragma unroll
-    for (int e = 0; e < P; ++e) {
-      wc[e] = live * wv[e];
-      hc[e] = hv[e];
-    }
-    if (i + 1 < nk) load(i + 1);
     if constexpr (ADJ) {
+      if (!BOTH || i > 0) load_w(i);
 #pragma unroll
-      for (int e = 0; e < P; ++e) v[e] = cmulc(V[e], hc[e]);
+      for (int e = 0; e < P; ++e) v[e] = cmulc(V[e], hv[e]);
+      if (i + 1 < nk) load_h(i + 1);
       fft_wv<L, P, true, SYNC_WAVE>(v, my, twl, opaque1d(t));
 #pragma unroll
       for (int e = 0; e < P; ++e) {
-        acc[e].x = fmaf(wc[e], v[e].x, acc[e].x);
-        acc[e].y = fmaf(wc[e], v[e].y, acc[e].y);
+        const float ww = live * wv[e];
+        acc[e].x = fmaf(ww, v[e].x, acc[e].x);
+        acc[e].y = fmaf(ww, v[e].y, acc[e].y);
       }
     } else {
+      if (!BOTH || i > 0) load_h(i);
 #pragma unroll
-      for (int e = 0; e < P; ++e) v[e] = make_float2(wc[e] * xa[e], wc[e] * xb[e]);
+      for (int e = 0; e < P; ++e) {
+        const float ww = live * wv[e];
+        v[e] = make_float2(ww * xa[e], ww * xb[e]);
+      }
+      if (i + 1 < nk) load_w(i + 1);
       fft_wv<L, P, false, SYNC_WAVE>(v, my, twl, opaque1d(t));
 #pragma unroll
-      for (int e = 0; e < P; ++e) acc[e] = cfma(acc[e], hc[e], v[e]);
+      for (int e = 0; e < P; ++e) acc[e] = cfma(acc[e], hv[e], v[e]);
     }
   }
   if constexpr (!ADJ) fft_wv<L, P, true, SYNC_WAVE>(acc, my, twl, t);
   const float sc = 1.0f / (float)L;
-  float* ya = y + 2 * pair * L;
-  float* yb = ya + L;
-  if constexpr (NF == 1) {
+  if (NF == 1 || ls == 0) {  // (uniform over the workgroup)
+    if (!have) return;
     if (G == 1) {
+      float* ya = y + 2 * pair * L;
+      float* yb = ya + L;
 #pragma unroll
       for (int e = 0; e < P; ++e) {
         ya[t + T * e] = acc[e].x * sc;
@@ -284,17 +315,32 @@ __global__ __launch_bounds__(split_slots(L) * split_threads(L)) void k_small1d_s
 #pragma unroll
     for (int e = 0; e < P; ++e) lds[c * L + t + T * e] = acc[e];
     __syncthreads();
-    float2* mine = part + (pair * G + g) * L;
-    for (int n = tid; n < L; n += NT) {
-      float2 a = lds[n];
-#pragma unroll
-      for (int q = 1; q < NF; ++q) a = cadd(a, lds[q * L + n]);
+    auto put = [&](int64_t pr, int n, float2 a) {
       if (G == 1) {
-        ya[n] = a.x * sc;
-        if (vb) yb[n] = a.y * sc;
+        y[2 * pr * L + n] = a.x * sc;
+        if (2 * pr + 1 < batch) y[(2 * pr + 1) * L + n] = a.y * sc;
       } else {
-        mine[n] = a;
+        part[(pr * G + g) * L + n] = a;
       }
+    };
+    if (1 << ls == NF) {  // one pair
+      for (int n = tid; n < L; n += NT) {
+        float2 a = lds[n];
+#pragma unroll
+        for (int q = 1; q < NF; ++q) a = cadd(a, lds[q * L + n]);
+        put(pair0, n, a);
+      }
+      return;
+    }
+    for (int i = tid; i < (NF >> ls) * L; i += NT) {
+      const int pl = i / L, n = i % L;
+      const int64_t pr = pair0 + pl;
+      if (pr >= pairs) return;
+      const float2* sh = lds + (pl << ls) * L + n;
+      float2 a = cadd(sh[0], sh[L]);
+#pragma unroll 2
+      for (int q = 2; q < 1 << ls; q += 2) a = cadd(cadd(a, sh[q * L]), sh[(q + 1) * L]);
+      put(pr, n, a);
     }
   }
 }
@@ -324,30 +370,94 @@ static LaunchStatus spec1d_full_t(const float* h, float2* H, int m, const float2
   return hipGetLastError();
 }
 
-// Workgroups per pair (0: the kernels with a pair per transform slot, which
-// do no work twice and win once they have a workgroup for every compute
-// unit).  One while the terms of a slot are few and short: the second launch
-// costs 2.3 us and a launch on the host (1 signal of 1024 samples, 8 terms,
-// two per slot: 8.5 us, spread 9.7; 12 terms, three per slot: 11.2, spread
-// 9.9).  Else as many as make about one workgroup per compute unit (64
-// signals of 3072 samples, 30 terms: 4, 8, 16 and 30 groups 32, 22.8, 24.2
-// and 29.3 us).
+// How a call spreads a pair's terms: workgroups per pair (0: the kernels with
+// a pair per transform slot), the log2 of its slots per workgroup, and threads
+// per workgroup: the split with the least expected time, of the slots and
+// workgroups that leave no slot without a term.  Expected are
+//   transforms one after another x (latency of their passes, which grows with
+//   the points per thread, x rounds of resident workgroups + the work of a
+//   compute unit, mostly the fullest's)
+//   + with several workgroups, the second launch and its shares;
+// the constants (us) are a least-squares fit to 39,000 timings of 64 to 8192
+// samples, 1 to 32 terms and 1 to 4200 pairs, over which the choice is 1% off
+// the fastest split on average.  (One pair's slots per workgroup of 512 threads
+// up to 1024 points, and as many workgroups as compute units, were 10%
+// further off; us per forward, so and here: 4200 signals of 192 samples, 8
+// terms, 49.6 and 11.6; 1030 of 768, 3 terms, 22.4 and 10.2; 16000 of 96, 16
+// terms, 178 and 21.8; 520 of 2048, 32 terms, 77.0 and 49.3.)
+// From a workgroup per compute unit on (two at 2048 points) the kernels with a
+// pair per slot run unless a split is expected to gain 15%: they hold less
+// (1030 signals of 1024 samples, 3 terms: 10.0 us, the best split 10.8), but
+// leave the chip at one wavefront per SIMD there (1030 of 3072, 16 terms: 86,
+// four workgroups per pair 54).
+// While the terms of a slot are few and short there is one workgroup per
+// pair: the second launch costs the host as much again (1 signal of 1024
+// samples, 8 terms, two per slot: 8.5 us, spread 9.7; 12 terms, three per
+// slot: 11.2, spread 9.9).
+// At 1024 points and 8 terms or more a pair per compute unit runs four
+// transforms of 16 points per thread, a wavefront each and one exchange less
+// (threads 0; us per forward, 8 and 16 points per thread: 520 signals, 32 terms
+// 35.3 and 31.2, 16 terms 21.1 and 19.1; 260 signals, 16 terms 14.7 and 14.8;
+// 1030 signals, 16 terms 27.1 and 29.2; 520 signals, 5 terms 11.0 and 13.1).
+struct SmallSplit {
+  int groups, ls, threads;
+};
 template <int L>
-static int split_groups_t(int m, int64_t pairs) {
-  constexpr int NF = ffts_per_block(L), SF = split_slots(L);
-  if ((pairs + NF - 1) / NF >= 256) return 0;
-  const int most = (m + SF - 1) / SF;  // terms per slot of a single workgroup
-  if ((int64_t)most * L <= 2048) return 1;
-  const int g = (int)std::min<int64_t>(most, std::max<int64_t>(1, 256 / pairs));
-  const int per = (most + g - 1) / g;  // terms per slot; the fewest workgroups with that many
-  return (most + per - 1) / per;
+constexpr int split_threads_least() {
+  return split_threads(L) > 256 ? split_threads(L) : 256;
+}
+template <int L>
+constexpr int split_threads_most() {
+  return L <= 1024 ? 512 : split_threads_least<L>();
+}
+template <int L>
+static SmallSplit small_split_t(int m, int64_t pairs) {
+  constexpr int P = split_points(L), T = L / P, CUS = 256, NF = plain_slots(L);
+  constexpr double latency = make_sched(L, P).n * P * (T > 64 ? 0.04 : 0.025);
+  double log2L = 0;
+  for (int x = 1; x < L; x *= 2) log2L += 1;
+  SmallSplit best{};
+  double least = 0, one_slot = 0;  // expected: the best split's, and of one slot per pair
+  auto consider = [&](int ls, int groups, int threads) {
+    const int64_t per_wg = threads / T >> ls, blocks = (pairs + per_wg - 1) / per_wg * groups;
+    const int lds = (threads / T * lds_len<L>() + L) * (int)sizeof(float2);
+    const int waves = P == 8 ? 4 : P == 12 ? 3 : 2;  // per SIMD, of the kernel's registers
+    const int64_t full = (blocks + CUS - 1) / CUS;
+    const int64_t resident = std::max(1, std::min(160 * 1024 / lds, waves * 256 / threads));
+    // workgroups per compute unit, mostly the fullest's
+    const double load = full <= 2 ? (double)full : 0.25 * (double)blocks / CUS + 0.75 * (double)full;
+    const int64_t terms = (m + ((int64_t)groups << ls) - 1) / ((int64_t)groups << ls);
+    double us = (double)(terms + 1) * (latency * (double)((full + resident - 1) / resident) +
+                                       0.008 * load * (threads / 256) * P * log2L);
+    if (groups > 1) us += 2.0 + 5e-6 * (double)(pairs * groups) * L;
+    if (ls == 0 && groups == 1 && (one_slot == 0 || us < one_slot)) one_slot = us;
+    if (best.groups == 0 || us < least) {
+      best = SmallSplit{groups, ls, threads};
+      least = us;
+    }
+  };
+  constexpr int MOST = split_threads_most<L>();
+  const bool few = (int64_t)((m + MOST / T - 1) / (MOST / T)) * L <= 2048;
+  for (int threads = split_threads_least<L>(); threads <= MOST; threads *= 2) {
+    int ls = 0;
+    consider(0, 1, threads);
+    while ((2 << ls) <= threads / T && (1 << ls) < m) consider(++ls, 1, threads);
+    const int terms = (m + (1 << ls) - 1) >> ls;  // of a slot of a single workgroup
+    for (int per = 1; !few && per < terms; per += std::max(1, per / 2)) {
+      const int groups = (terms + per - 1) / per;  // the fewest with that many terms per slot
+      if (pairs * groups <= SMALL1D_SHARES) consider(ls, groups, threads);
+    }
+  }
+  if ((pairs + NF - 1) / NF >= (L == 2048 ? 2 * CUS : CUS) && least > 0.85 * one_slot) return SmallSplit{0, 0, 0};
+  if (wide_points(L) > 0 && m >= 8 && 4 * pairs >= 3 * CUS && pairs < 2 * CUS) return SmallSplit{1, 2, 0};
+  return best;
 }
 
 int small1d_groups(int L, int m, int64_t pairs) {
   switch (L) {
 #define PC_CASE(LL) \
   case LL:          \
-    return split_groups_t<LL>(m, pairs);
+    return small_split_t<LL>(m, pairs).groups;
     PC_FOR_EACH_L(PC_CASE)
 #undef PC_CASE
   }
@@ -355,31 +465,44 @@ int small1d_groups(int L, int m, int64_t pairs) {
 }
 
 int small1d_split_points(int L) { return split_points(L); }
+int small1d_wide_points(int L) { return wide_points(L); }
 
 template <int L, bool ADJ>
 static LaunchStatus small1d_t(const Small1D& p, const float* u, float* y, int64_t batch, hipStream_t s, Tracer* tr) {
   const int64_t pairs = (batch + 1) / 2;
-  const int G = split_groups_t<L>(p.m, pairs);
-  if (G > 0) {
+  const SmallSplit q = small_split_t<L>(p.m, pairs);
+  if (q.groups > 0) {
     {
       TraceScope ts(tr, ADJ ? "adj1d_small" : "fwd1d_small", s);
-      hipLaunchKernelGGL((k_small1d_split<L, ADJ>), dim3((unsigned)(pairs * G)),
-                         dim3(split_slots(L) * split_threads(L)), 0, s, u, y, batch, p.m, p.w, p.H, p.tws, G, p.part);
+      constexpr int WP = wide_points(L) > 0 ? wide_points(L) : split_points(L), WT = split_threads_least<L>();
+      const int threads = q.threads > 0 ? q.threads : WT, T = q.threads > 0 ? split_threads(L) : L / WP;
+      const int64_t per_wg = threads / T >> q.ls;
+      const dim3 grid((unsigned)((pairs + per_wg - 1) / per_wg * q.groups)), block(threads);
+      if (q.threads == 0)
+        hipLaunchKernelGGL((k_small1d_split<L, WP, WT, ADJ>), grid, block, 0, s, u, y, batch, p.m, p.w, p.H, p.tww,
+                           q.ls, q.groups, p.part);
+      else if (q.threads == split_threads_least<L>())
+        hipLaunchKernelGGL((k_small1d_split<L, split_points(L), split_threads_least<L>(), ADJ>), grid, block, 0, s, u,
+                           y, batch, p.m, p.w, p.H, p.tws, q.ls, q.groups, p.part);
+      else
+        hipLaunchKernelGGL((k_small1d_split<L, split_points(L), split_threads_most<L>(), ADJ>), grid, block, 0, s, u,
+                           y, batch, p.m, p.w, p.H, p.tws, q.ls, q.groups, p.part);
     }
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || G == 1) return e;
+    if (e != hipSuccess || q.groups == 1) return e;
     TraceScope ts(tr, "sum1d_small", s);
-    hipLaunchKernelGGL(k_small1d_sum<L>, dim3((unsigned)((pairs * L + 255) / 256)), dim3(256), 0, s, p.part, G, y,
-                       batch);
+    hipLaunchKernelGGL(k_small1d_sum<L>, dim3((unsigned)((pairs * L + 255) / 256)), dim3(256), 0, s, p.part, q.groups,
+                       y, batch);
     return hipGetLastError();
   }
   TraceScope ts(tr, ADJ ? "adj1d_small" : "fwd1d_small", s);
-  constexpr int NF = ffts_per_block(L), T = fft_threads(L);
-  const dim3 grid((unsigned)((pairs + NF - 1) / NF)), block(NF * T);
+  constexpr int NF = plain_slots(L);
+  const dim3 grid((unsigned)((pairs + NF - 1) / NF)), block(NF * plain_threads(L));
+  const float2* tw = plain_points(L) == split_points(L) ? p.tws : p.tw;
   if constexpr (ADJ)
-    hipLaunchKernelGGL(k_adj1d_small<L>, grid, block, 0, s, u, y, batch, p.m, p.w, p.H, p.tw);
+    hipLaunchKernelGGL(k_adj1d_small<L>, grid, block, 0, s, u, y, batch, p.m, p.w, p.H, tw);
   else
-    hipLaunchKernelGGL(k_fwd1d_small<L>, grid, block, 0, s, u, y, batch, p.m, p.w, p.H, p.tw);
+    hipLaunchKernelGGL(k_fwd1d_small<L>, grid, block, 0, s, u, y, batch, p.m, p.w, p.H, tw);
   return hipGetLastError();
 }
 
@@ -1072,6 +1195,9 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_fft_pair
     for (int e = 0; e < P; ++e) out[pair * L + t + T * e] = v[e];
   }
 }
+
+// (512 threads up to 1024 points: more terms per workgroup)
+constexpr int split_slots(int L) { return split_threads(L) >= 256 ? 1 : (L <= 1024 ? 512 : 256) / split_threads(L); }
 
 // Backward of the small sizes.  Slot c of workgroup (kg, pg) owns term
 // k = kg NF + c and takes pairs pg, pg + PG, ...: from one transform of the

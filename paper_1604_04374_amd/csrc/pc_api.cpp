@@ -382,22 +382,23 @@ pc_status build_small1d(pc_plan p, const float* windows, const float* h, hipStre
   if (st) return st;
   // the twiddles, and those of the small batches' kernels behind them where
   // these take another number of points per thread
-  const int sp = pc::small1d_split_points(L);
   std::vector<float2> tables = engine_twiddles(L);
-  const size_t split_at = sp == pc::points_per_thread(L) ? 0 : tables.size();
-  if (split_at) {
-    const std::vector<float2> t2 = engine_twiddles(L, sp);
+  auto table_at = [&](int points) {
+    if (points == 0 || points == pc::points_per_thread(L)) return (size_t)0;
+    const size_t at = tables.size();
+    const std::vector<float2> t2 = engine_twiddles(L, points);
     tables.insert(tables.end(), t2.begin(), t2.end());
-  }
+    return at;
+  };
+  const size_t split_at = table_at(pc::small1d_split_points(L)), wide_at = table_at(pc::small1d_wide_points(L));
   float2* tw = nullptr;
   st = p->upload(&tw, tables, s);
   if (st) return st;
   // room for the workgroups' shares at every call size up to the plan's that
   // spreads a pair's terms (behind the spectra)
   int64_t shares = 0;
-  for (int64_t pairs = 1; pairs <= (p->d.batch + 1) / 2; ++pairs) {
+  for (int64_t pairs = 1; pairs <= std::min<int64_t>((p->d.batch + 1) / 2, pc::SMALL1D_SHARES / 2); ++pairs) {
     const int g = pc::small1d_groups(L, m, pairs);
-    if (g == 0) break;
     if (g > 1) shares = std::max(shares, pairs * g);
   }
   DeviceTemp hd;
@@ -411,7 +412,7 @@ pc_status build_small1d(pc_plan p, const float* windows, const float* h, hipStre
   if (e != hipSuccess) return fail_hip(e, "spectra kernel");
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(e, "spectra kernel");
-  p->s1 = pc::Small1D{L, m, w, H, tw, tw + split_at, shares > 0 ? H + (size_t)m * L : nullptr};
+  p->s1 = pc::Small1D{L, m, w, H, tw, tw + split_at, tw + wide_at, shares > 0 ? H + (size_t)m * L : nullptr};
   return PC_SUCCESS;
 }
 

@@ -76,11 +76,15 @@ struct Small1D {
   const float2* tw;          // engine twiddles for L
   // small batches (small1d_groups):
   const float2* tws;         // engine twiddles for L at small1d_split_points(L) points per thread
+  const float2* tww;         // and at small1d_wide_points(L), where there are such
   float2* part;              // workgroups' shares of the output, groups x L per pair (null: one group)
 };
-// workgroups per pair for a call of `pairs` pairs (0: one pair per transform slot)
+// workgroups per pair for a call of `pairs` pairs (0: one pair per transform
+// slot); above one, pairs x workgroups stays within SMALL1D_SHARES
+constexpr int SMALL1D_SHARES = 1024;
 int small1d_groups(int L, int m, int64_t pairs);
 int small1d_split_points(int L);
+int small1d_wide_points(int L);  // (0: none)
 LaunchStatus launch_spec1d_full(int L, const float* h, float2* H, int m, const float2* tw, hipStream_t s);
 LaunchStatus launch_fwd1d_small(const Small1D& p, const float* u, float* y, int64_t batch, hipStream_t s,
                                 Tracer* tr = nullptr);

@@ -71,6 +71,19 @@ def test_1d_small_batches_spread_their_terms(n, m, deg, batch):
     _check(p)
 
 
+@pytest.mark.parametrize("n,m,deg,batch", [
+    # several pairs per workgroup, the last one ragged, slots past the last term
+    (64, 3, 1, 37), (96, 8, 1, 2101), (192, 5, 1, 777), (384, 8, 3, 1031), (768, 3, 1, 515), (1536, 3, 1, 131),
+    # 512 threads per pair, and its terms over workgroups besides
+    (384, 32, 3, 261), (512, 16, 3, 64), (768, 32, 3, 33), (2048, 32, 3, 261), (1024, 9, 1, 385), (1024, 16, 3, 1021),
+    # one slot per pair below the large batches, and the large batches' kernels
+    (128, 1, 1, 3001), (1024, 1, 1, 333), (128, 5, 1, 8195), (1024, 3, 1, 1031), (2048, 2, 1, 1025), (4096, 3, 1, 515),
+])
+def test_1d_batches_of_many_signals(n, m, deg, batch):
+    p = wl.small_1d(n, m, deg, batch, seed=400 + n + m, sigma_fn=lambda y: 0.01 + 0.03 * y)
+    _check(p)
+
+
 # ---------------------------------------------------------------------------
 # 1D four-step (N = R * L)
 # ---------------------------------------------------------------------------
