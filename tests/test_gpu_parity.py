@@ -88,6 +88,14 @@ def test_1d_batches_of_many_signals(n, m, deg, batch):
 # 1D four-step (N = R * L)
 # ---------------------------------------------------------------------------
 
+@pytest.mark.parametrize("n,m,batch", [(12288, 2, 1), (24576, 3, 2), (16384, 4, 3), (32768, 5, 1), (65536, 6, 1),
+                                       (98304, 31, 1), (65536, 18, 5)])
+def test_1d_fourstep_sums_every_slice(n, m, batch):
+    # a slice per term or few: every remainder of the sums' unrolled loads
+    p = wl.small_1d(n, m, 1, batch, seed=220 + m, sigma_fn=wl.gen.c2_sigma)
+    _check(p)
+
+
 @pytest.mark.parametrize("n,m,deg,batch", [
     (16384, 4, 3, 3), (12288, 5, 1, 2), (32768, 16, 3, 2), (24576, 8, 3, 1),
     (49152, 12, 1, 2), (98304, 16, 3, 1), (131072, 32, 3, 1),
