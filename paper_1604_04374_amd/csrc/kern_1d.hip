@@ -70,7 +70,7 @@ __global__ __launch_bounds__(ffts_per_block(L) * fft_threads(L)) void k_spec1d_f
 // 4, 91 at 8).
 constexpr int split_points(int L) { return L % 3 == 0 ? 12 : L >= 8192 ? 16 : 8; }
 constexpr int split_threads(int L) { return L / split_points(L); }
-constexpr int wide_points(int L) { return L == 1024 ? 16 : 0; }  // (0: none)
+constexpr int wide_points(int L) { return L == 256 || L == 1024 || L == 2048 ? 16 : 0; }  // (0: none)
 constexpr int plain_points(int L) { return L == 4096 ? 16 : split_points(L); }
 constexpr int plain_threads(int L) { return L / plain_points(L); }
 constexpr int plain_slots(int L) { return plain_threads(L) >= 256 ? 1 : 256 / plain_threads(L); }
@@ -163,6 +163,75 @@ __global__ __launch_bounds__(plain_slots(L) * plain_threads(L))
       const float ww = wk[t + T * e];
       acc[e].x = fmaf(ww, g[e].x, acc[e].x);
       acc[e].y = fmaf(ww, g[e].y, acc[e].y);
+    }
+  }
+  const float sc = 1.0f / (float)L;
+#pragma unroll
+  for (int e = 0; e < P; ++e) {
+    const int n = t + T * e;
+    if (va) x[sa * L + n] = acc[e].x * sc;
+    if (vb) x[sb * L + n] = acc[e].y * sc;
+  }
+}
+
+// The same at 16 points per thread: one exchange less per transform, and two
+// workgroups per compute unit with every address in registers.  split: the NF
+// slots of a workgroup share one pair, take its terms in turn and add their
+// sums in LDS.  For calls that fill those workgroups' rounds (adj_wide).
+// (split is an argument: the loop of a kernel without it is scheduled worse,
+// 191 instead of 170 us at 4096 signals of 1024 samples, 64 terms)
+template <int L>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_adj1d_wide(
+    const float* __restrict__ vin, float* __restrict__ x, int64_t batch, int m, const float* __restrict__ w,
+    const float2* __restrict__ H, const float2* __restrict__ tw, int split) {
+  constexpr int P = 16, T = L / P, NF = 256 / T;
+  __shared__ float2 lds[NF * lds_len<L>()];
+  __shared__ float2 twl[L];
+  stage_twiddles<L>(twl, tw);
+  const int c = threadIdx.x / T, t = threadIdx.x % T;
+  const int64_t pair = split ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * NF + c;
+  const int64_t sa = 2 * pair, sb = sa + 1;
+  const bool va = sa < batch, vb = sb < batch;
+  float2 V[P];
+#pragma unroll
+  for (int e = 0; e < P; ++e) {
+    const int n = t + T * e;
+    V[e] = make_float2(va ? vin[sa * L + n] : 0.f, vb ? vin[sb * L + n] : 0.f);
+  }
+  float2* my = lds + c * lds_len<L>();
+  fft_wg<L, P, false>(V, my, twl, t);
+  float2 acc[P];
+#pragma unroll
+  for (int e = 0; e < P; ++e) acc[e] = make_float2(0.f, 0.f);
+  // every slot makes the same number of transform calls (they hold barriers):
+  // a slot past the last term transforms a valid one with zero weight
+  const int nk = split ? (m + NF - 1) / NF : m;
+  for (int i = 0; i < nk; ++i) {
+    const int kt = split ? c + NF * i : i;
+    const int k = kt < m ? kt : m - 1;
+    const float live = kt < m ? 1.f : 0.f;
+    const float2* Hk = H + (int64_t)k * L;
+    float2 g[P];
+#pragma unroll
+    for (int e = 0; e < P; ++e) g[e] = cmulc(V[e], Hk[t + T * e]);
+    fft_wg<L, P, true>(g, my, twl, t);
+    const float* wk = w + (int64_t)k * L;
+#pragma unroll
+    for (int e = 0; e < P; ++e) {
+      const float ww = live * wk[t + T * e];
+      acc[e].x = fmaf(ww, g[e].x, acc[e].x);
+      acc[e].y = fmaf(ww, g[e].y, acc[e].y);
+    }
+  }
+  if (split) {
+    __syncthreads();  // every slot's transforms are done with LDS
+#pragma unroll
+    for (int e = 0; e < P; ++e) my[lpad(t + T * e)] = acc[e];
+    __syncthreads();
+    if (c > 0) return;
+    for (int sl = 1; sl < NF; ++sl) {
+#pragma unroll
+      for (int e = 0; e < P; ++e) acc[e] = cadd(acc[e], lds[sl * lds_len<L>() + lpad(t + T * e)]);
     }
   }
   const float sc = 1.0f / (float)L;
@@ -449,7 +518,7 @@ static SmallSplit small_split_t(int m, int64_t pairs) {
     }
   }
   if ((pairs + NF - 1) / NF >= (L == 2048 ? 2 * CUS : CUS) && least > 0.85 * one_slot) return SmallSplit{0, 0, 0};
-  if (wide_points(L) > 0 && m >= 8 && 4 * pairs >= 3 * CUS && pairs < 2 * CUS) return SmallSplit{1, 2, 0};
+  if (L == 1024 && m >= 8 && 4 * pairs >= 3 * CUS && pairs < 2 * CUS) return SmallSplit{1, 2, 0};
   return best;
 }
 
@@ -464,17 +533,52 @@ int small1d_groups(int L, int m, int64_t pairs) {
   return 0;
 }
 
+// Whether an adjoint call takes k_adj1d_wide, whose 512 resident workgroups
+// it has to fill: a pair per slot from 256 workgroups on, a pair per workgroup
+// below (us per adjoint, without it and with: a pair per slot, 4096 signals of
+// 1024 samples, 64 terms 192 and 170, 2600 of them 154 and 171; 2000 of 2048,
+// 32 terms 107 and 94, 1300 of them 88 and 94, 4096 of them 198 and 188, of 16
+// terms the same; 16384 of 256, 16 terms 41.3 and 37.6, 8192 of them 26 and
+// 35; a pair per workgroup, 774 of 2048, 32 terms 66 and 50, 520 of them, 64
+// terms 84 and 91, 366 of them, 8 terms 17.9 and 17.1, 16 terms 24.4 and 27.4;
+// 640 of 1024, 64 terms 54.6 and 49.2, 8 terms 12.2 and 12.7; 1600 of them, 64
+// terms 109 and 97, 16 terms 33 and 34).  At 512 points 8 per thread win
+// throughout.
+template <int L>
+static bool adj_wide(int m, int64_t pairs, bool& split) {
+  constexpr int NF = 256 * 16 / L;
+  const int64_t slots = (pairs + NF - 1) / NF;
+  split = slots < 256;
+  if (!split)
+    return (slots <= 512 && slots >= (L == 256 ? 480 : 384)) ||
+           (L == 2048 && m >= 32 && slots <= 1024 && slots >= 960);
+  if (L == 1024) return (m >= 16 && pairs > 256 && pairs <= 512) || (m >= 32 && pairs > 768);
+  if (L == 2048) return m >= 8 && pairs > (m <= 12 ? 176 : 256) && (m < 32 || pairs >= 384);
+  return false;
+}
+
 int small1d_split_points(int L) { return split_points(L); }
 int small1d_wide_points(int L) { return wide_points(L); }
 
 template <int L, bool ADJ>
 static LaunchStatus small1d_t(const Small1D& p, const float* u, float* y, int64_t batch, hipStream_t s, Tracer* tr) {
   const int64_t pairs = (batch + 1) / 2;
+  if constexpr (ADJ && wide_points(L) > 0) {
+    bool split = false;
+    if (adj_wide<L>(p.m, pairs, split)) {
+      constexpr int NF = 256 * 16 / L;
+      TraceScope ts(tr, "adj1d_small", s);
+      const int64_t blocks = split ? pairs : (pairs + NF - 1) / NF;
+      hipLaunchKernelGGL(k_adj1d_wide<L>, dim3((unsigned)blocks), dim3(256), 0, s, u, y, batch, p.m, p.w, p.H, p.tww,
+                         split ? 1 : 0);
+      return hipGetLastError();
+    }
+  }
   const SmallSplit q = small_split_t<L>(p.m, pairs);
   if (q.groups > 0) {
     {
       TraceScope ts(tr, ADJ ? "adj1d_small" : "fwd1d_small", s);
-      constexpr int WP = wide_points(L) > 0 ? wide_points(L) : split_points(L), WT = split_threads_least<L>();
+      constexpr int WP = L == 1024 ? wide_points(L) : split_points(L), WT = split_threads_least<L>();
       const int threads = q.threads > 0 ? q.threads : WT, T = q.threads > 0 ? split_threads(L) : L / WP;
       const int64_t per_wg = threads / T >> q.ls;
       const dim3 grid((unsigned)((pairs + per_wg - 1) / per_wg * q.groups)), block(threads);
