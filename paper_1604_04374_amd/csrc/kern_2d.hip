@@ -1207,8 +1207,12 @@ void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int
   for (size_t i0 = from; i0 < bm.size(); i0 += per_img) {
     // position p runs on XCD (i0 + p) mod 8: each XCD takes a run of blocks
     int64_t next = 0;
-    for (int64_t x = 0; x < XCDS; ++x)
-      for (int64_t p = ((x - (int64_t)i0) % XCDS + XCDS) % XCDS; p < per_img; p += XCDS) img[p] = bm[i0 + next++];
+    for (int64_t x = 0; x < XCDS; ++x) {
+      const int64_t p0 = ((x - (int64_t)i0) % XCDS + XCDS) % XCDS, n = p0 < per_img ? (per_img - p0 + XCDS - 1) / XCDS : 0;
+      const auto run = bm.begin() + i0 + next;
+      std::stable_sort(run, run + n, [](const BlockRef& a, const BlockRef& b) { return a.q < b.q; });
+      for (int64_t p = p0; p < per_img; p += XCDS) img[p] = bm[i0 + next++];
+    }
     std::copy(img.begin(), img.end(), bm.begin() + i0);
   }
 }
