@@ -551,7 +551,8 @@ __global__ __launch_bounds__(G * fft_threads(L2)) void k_rows_inv(
 template <int L2, int QP>
 constexpr bool side_fits() {
   constexpr int G = row_pairs_small(L2);
-  return G * fft_threads(L2) * QP <= 1024 && (QP * G * lds_len<L2>() + L2) * (int)sizeof(float2) <= 156 * 1024;
+  return G * fft_threads(L2) * QP <= (points_per_thread(L2) == 16 ? 768 : 1024) &&
+         (QP * G * lds_len<L2>() + L2) * (int)sizeof(float2) <= 156 * 1024;
 }
 template <int L2, int QP>
 __global__ __launch_bounds__(row_pairs_small(L2) * fft_threads(L2) * QP) void k_rows_inv_side(
@@ -1360,10 +1361,17 @@ bool adj_own_fft(int m1, int64_t slots) { return m1 >= 2 || slots <= 4096; }
 // of nq windowed planes, or 0: where the planes' groups fit the chip together
 // (1024 x 1024, 4 planes: 4096 wavefronts, 16 per CU, as many as its LDS
 // regions leave room for); beyond, the groups of one tile would only wait
-// for the next round of workgroups.
+// for the next round of workgroups.  Not with 1024 threads of 16 points (70 of
+// their registers spill: 2048 points, 4 planes, 30 us where the pipelined pass
+// takes 20), and from 2048 points on only where every plane has its group
+// (3072 points, 4 planes two at a time 30.4, pipelined 29.1).
 template <int L2>
 static int side_of(int nq, int64_t blocks) {
   const int64_t waves = blocks * row_pairs_small(L2) * fft_threads(L2) / 64;
+  if (L2 >= 2048) {
+    if (side_fits<L2, 3>() && nq == 3 && waves * 3 <= 4096) return 3;
+    return side_fits<L2, 2>() && nq == 2 && waves * 2 <= 4096 ? 2 : 0;
+  }
   if (side_fits<L2, 4>() && nq % 4 == 0 && waves * 4 <= 4096) return 4;
   if (side_fits<L2, 3>() && nq % 3 == 0 && waves * 3 <= 4096) return 3;
   if (side_fits<L2, 2>() && nq % 2 == 0 && waves * 2 <= 4096) return 2;

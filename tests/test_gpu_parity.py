@@ -313,3 +313,14 @@ def test_adjoint_planes_side_by_side(case):
     _, rx = oracle_fft(p)
     assert per_instance_rel(x, rx) <= TOL
     assert np.array_equal(part[0], x[0])
+
+
+# the lengths at which some plane counts go side by side and others in turn
+LONG_ROWS = [(64, 2048, 2, 3, 1), (64, 2048, 2, 4, 2), (64, 2048, 1, 6, 1), (96, 3072, 1, 2, 1), (64, 3072, 1, 4, 1),
+             (64, 4096, 1, 2, 1), (64, 1536, 1, 8, 1)]
+
+
+@pytest.mark.parametrize("n1,n2,m1,m2,batch", LONG_ROWS)
+def test_adjoint_of_few_long_rows(n1, n2, m1, m2, batch):
+    p = wl.small_2d(n1, n2, m1, m2, batch, seed=92, kind="hat")
+    _check(p)
