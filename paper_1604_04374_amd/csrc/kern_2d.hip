@@ -1209,7 +1209,8 @@ void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int
     // position p runs on XCD (i0 + p) mod 8: each XCD takes a run of blocks
     int64_t next = 0;
     for (int64_t x = 0; x < XCDS; ++x) {
-      const int64_t p0 = ((x - (int64_t)i0) % XCDS + XCDS) % XCDS, n = p0 < per_img ? (per_img - p0 + XCDS - 1) / XCDS : 0;
+      const int64_t p0 = ((x - (int64_t)i0) % XCDS + XCDS) % XCDS;
+      const int64_t n = p0 < per_img ? (per_img - p0 + XCDS - 1) / XCDS : 0;
       const auto run = bm.begin() + i0 + next;
       std::stable_sort(run, run + n, [](const BlockRef& a, const BlockRef& b) { return a.q < b.q; });
       for (int64_t p = p0; p < per_img; p += XCDS) img[p] = bm[i0 + next++];
@@ -1225,8 +1226,8 @@ void append_col_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int H
       for (int q = 0; q < nsub; ++q) out.push_back(BlockRef{job, (int)img, b, q});
 }
 
-// Batches (single plans always take the late variant: 2 to 10% faster from 128
-// to 3072 points).  Late loads pay where the early variant is down to two
+// Batches (single plans take the late variant up to 3072 points: 2 to 10% faster
+// from 128 on).  Late loads pay where the early variant is down to two
 // waves per SIMD and the late one has more.  With three or more waves, early
 // loads are worth more when a launch's instances loop over several terms
 // (each term's spectrum loads during the previous term's transform; measured
@@ -1332,20 +1333,55 @@ bool cols_adj_prefetch(int L1) {
   });
 }
 
-int col_groups_for(int L1, int H2, int64_t batch, int nq) {
-  // split the forward column pass over groups of column factors until the
-  // chip has about three wavefronts per SIMD of column transforms; each group
-  // costs an inverse transform per column and a plane that the row-inverse
-  // pass reads (measured, us per forward at 1, 2 and 4 groups: 1024 x 1024,
-  // 16 terms 57, 46.9 and 46.0; 2048 x 2048 141.7, 140.1 and 148.8; 1536 x
-  // 1536 101, 92 and 97; four images of 512 x 512 47.8, 40.8 and 39.1).  A
-  // transform of 256 threads or more needs a third of that: 4096 x 512, 4
-  // terms, 42.1 at one group and 47.8 at two.
+// Term groups of the forward column pass over nq column factors of m1 terms
+// each: those of the least expected time.  More groups shorten a workgroup's
+// chain of transforms and fill the chip's last round, but each costs an
+// inverse transform per column and a plane that the row-inverse pass reads.
+// Expected are, per transform of the longest chain, the latency of its passes
+// times the rounds of resident workgroups plus the work of a compute unit,
+// mostly the fullest's; and the planes, by size and by count.  The constants
+// (us) are fitted to 197 shapes of 64 to 4096 points per column, 1 to 16 terms
+// per factor, 2 to 16 factors and 1 to 8 images, over which the choice is 0.4%
+// off the fastest on average.  (A target of wavefronts, 3000 or 1024 at 256
+// threads per transform, was 4% off, most where a column has many terms: us
+// per forward, so and here, 4096 x 1024, 16 x 4 terms 565 and 427, 3072 x 256,
+// two images, 4 x 8 terms 162 and 110, 4096 x 128, 6 x 6 terms 65 and 45; a
+// target of 4096 columns too: four images of 4096 x 512, 8 x 3 terms.)
+int col_groups_for(int L1, int H2, int64_t batch, int m1, int nq) {
+  constexpr int CUS = 256;
+  const int P = points_per_thread(L1), T = fft_threads(L1), NF = ffts_per_block(L1), threads = NF * T;
+  int passes = 0;
+  for (int64_t x = 1; x < L1; x *= P) ++passes;
+  double log2L = 0;
+  for (int x = L1; x > 1 && x % 2 == 0; x /= 2) log2L += 1;
+  if (L1 % 3 == 0) log2L += 1.585;
+  const int waves = P == 16 ? 3 : P == 12 ? 4 : P == 8 ? 5 : 8;  // per SIMD
+  const int64_t lds = (int64_t)(NF * (L1 + L1 / 16) + L1) * 8;
+  const int64_t resident = std::max<int64_t>(1, std::min<int64_t>(160 * 1024 / lds, waves * 256 / threads));
+  const double plane_mb = (double)L1 * H2 * (double)batch * 8e-6;
+  int best = 1;
+  double least = 0;
+  for (int g = 1;; g = std::min(2 * g, nq)) {
+    const int64_t blocks = (int64_t)((H2 + NF - 1) / NF) * batch * g, full = (blocks + CUS - 1) / CUS;
+    const double load = full <= 2 ? (double)full : 0.25 * (double)blocks / CUS + 0.75 * (double)full;
+    const int chain = (nq + g - 1) / g * m1 + 1;
+    const double us = chain * (0.079 * passes * P * (double)((full + resident - 1) / resident) +
+                               0.01 * load * threads / 256.0 * P * log2L) +
+                      (0.05 * plane_mb + 0.86) * g;
+    if (g == 1 || us < least) {
+      best = g;
+      least = us;
+    }
+    if (g >= nq) return best;
+  }
+}
+
+// Whether the column transforms of a batch leave the chip room for one term
+// group per column factor: below about three wavefronts per SIMD, or one
+// where a transform takes 256 threads or more.
+bool cols_leave_room(int L1, int64_t columns) {
   const int T = fft_threads(L1);
-  const int64_t waves = (int64_t)H2 * batch * T / 64, target = T >= 256 ? 1024 : 3000;
-  int g = 1;
-  while (g < nq && waves * g < target) g *= 2;
-  return g < nq ? g : nq;
+  return columns * T / 64 < (T >= 256 ? 1024 : 3000);
 }
 
 // A slot with several terms transforms its column of V once more than a pass

@@ -633,7 +633,9 @@ pc_status make_set(pc_plan p, pc::LaunchSet& ls, int kind, int L, const std::vec
   ls.threads = rows ? pc::row_threads(L, small_rows) : pc::col_threads(L);
   ls.small_rows = rows && small_rows;
   const uint64_t key = p->tune_key;
-  ls.late = kind == pc::KK_COLS_FWD && pc::tune_get(key, PC_TUNE_COLS_FWD_LATE, L, 1);
+  // (from 4096 points on LDS allows two waves per SIMD whatever the registers: us per forward, early and late, 4096 x
+  // 2048, 8 x 1 terms 147 and 161, 4096 x 1024, 16 x 4 terms 393 and 427; 2048 x 2048, 4 x 4 terms 166 and 148)
+  ls.late = kind == pc::KK_COLS_FWD && pc::tune_get(key, PC_TUNE_COLS_FWD_LATE, L, L < 4096);
   ls.prefetch = kind == pc::KK_COLS_ADJ && pc::tune_get(key, PC_TUNE_COLS_ADJ_PREFETCH, L, pc::cols_adj_prefetch(L));
   ls.one = single_term_cols(kind, jobs);
   ls.one_plane = kind == pc::KK_ROWS_INV && max_planes(jobs) == 1;
@@ -715,7 +717,7 @@ pc_status build_2d(pc_plan p, const float* windows, const float* h, hipStream_t 
   if ((st = p->alloc(&q.RA, (size_t)(nq * cap * plane), &p->workspace_bytes))) return st;
   if ((st = p->alloc(&q.Tws, (size_t)(cap * plane), &p->workspace_bytes))) return st;
   q.col_groups = std::max(1, std::min(nq, pc::tune_get(p->tune_key, PC_TUNE_COL_GROUPS, N1,
-                                                        pc::col_groups_for(N1, H2, cap, nq))));
+                                                        pc::col_groups_for(N1, H2, cap, q.dense ? 1 : q.m1, nq))));
   q.Part = nullptr;
   if (q.col_groups > 1 && (st = p->alloc(&q.Part, (size_t)(q.col_groups * cap * plane), &p->workspace_bytes)))
     return st;
@@ -1203,7 +1205,7 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
   auto grouped = [&](size_t i, int c) {
     const pc::Plan2D& q = inst[i].q->p2;
     if ((q.dense ? q.m : q.m2) == 1 || keep || gather || !fwd_type(i, c)) return false;
-    return pc::col_groups_for(q.N1, (int)std::min<int64_t>(fwd_cols[c][q.N1], INT32_MAX), 1, 2) > 1;
+    return pc::cols_leave_room(q.N1, fwd_cols[c][q.N1]);
   };
   pc_status st;
   for (int c = 0; c < 2; ++c) {

@@ -325,7 +325,8 @@ struct Plan2D {
   LaunchSet spec_rows, spec_cols;
 };
 
-int col_groups_for(int L1, int H2, int64_t batch, int nq);
+int col_groups_for(int L1, int H2, int64_t batch, int m1, int nq);
+bool cols_leave_room(int L1, int64_t columns);
 // Whether the adjoint column pass of a plan of several terms transforms its
 // input itself, in every column slot of m1 terms, instead of a pass before it.
 bool adj_own_fft(int m1, int64_t slots);
@@ -374,10 +375,11 @@ int col_threads(int L1);
 void append_row_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int N1, int L2, int nq,
                        bool small = false, int rows = 0, int block_rows = 0);
 // Reorders the blocks from `from` on, image by image (n_img of them), so that
-// neighbouring ones run on one XCD: row tiles of less than 16 rows share the
-// 128-byte lines of the spectral planes with their neighbours (with 4-row
-// tiles in order, four XCDs fetched every line: 17 us to read four planes of
-// 1024 x 513 entries, 13 here).
+// neighbouring ones run on one XCD, one plane's blocks after another's: row
+// tiles of less than 16 rows share the 128-byte lines of the spectral planes
+// with their neighbours (with 4-row tiles in order, four XCDs fetched every
+// line: 17 us to read four planes of 1024 x 513 entries, 13 here; with all
+// planes of a tile in turn, 183 us to write 16 planes of 2048 x 1025, 91 here).
 void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int L2, bool small, int block_rows = 0);
 void append_col_blocks(std::vector<BlockRef>& out, int job, int64_t n_img, int H2, int L1, int nsub);
 const char* kernel_kind_name(int kind);

@@ -324,3 +324,14 @@ LONG_ROWS = [(64, 2048, 2, 3, 1), (64, 2048, 2, 4, 2), (64, 2048, 1, 6, 1), (96,
 def test_adjoint_of_few_long_rows(n1, n2, m1, m2, batch):
     p = wl.small_2d(n1, n2, m1, m2, batch, seed=92, kind="hat")
     _check(p)
+
+
+# column factors that the term groups divide unevenly, many terms per column,
+# and few (one group)
+GROUPS = [(4096, 64, 6, 6, 1), (3072, 64, 2, 7, 1), (128, 128, 3, 11, 1), (2048, 256, 8, 5, 2), (4096, 512, 1, 3, 2)]
+
+
+@pytest.mark.parametrize("n1,n2,m1,m2,batch", GROUPS)
+def test_term_groups_of_the_forward(n1, n2, m1, m2, batch):
+    p = wl.small_2d(n1, n2, m1, m2, batch, seed=93, kind="hat")
+    _check(p)
