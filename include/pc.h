@@ -466,9 +466,10 @@ enum {
   /* One launch per pass (rows in, forward column passes and column
    * transforms, adjoint column passes, rows out) for every transform length
    * up to 512 together, instead of one launch per pass and transform length.
-   * Longer lengths keep their own launches.  This is what a batch does in any
-   * case, unless a tuning table entry for it (PC_TUNE_BATCH_PERSISTENT 0) asks
-   * for launches per length; the flag overrides that entry. */
+   * Longer lengths keep their own launches.  A pass over several lengths, or
+   * over a single one that does not fill the device, does so by itself, unless
+   * a tuning table entry (PC_TUNE_BATCH_PERSISTENT 0) asks for launches per
+   * length; the flag asks for it in every case and overrides that entry. */
   PC_BATCH_PERSISTENT = 2u
 };
 pc_status pc_batch_create(pc_batch* out, int32_t count, const pc_plan* plans, uint32_t flags, void* stream);
@@ -515,6 +516,10 @@ pc_status pc_batch_destroy(pc_batch batch);
  *           PC_TUNE_COL_GROUPS (clamped to [1, column factors]), the inner
  *           length for PC_TUNE_FOURSTEP_L (ignored unless it splits N).
  *
+ * Passes that a batch or a sectioned plan runs as one launch for several
+ * lengths (PC_TUNE_BATCH_PERSISTENT) have one variant: the switches of the
+ * lengths up to 512 apply there only where that knob is 0.
+ *
  * pc_tune_set replaces the process-wide table (count = 0 clears it); it
  * affects plans and batches created afterwards.  Errors: INVALID_VALUE (null
  * entries with count > 0, count < 0, unknown knob).
@@ -523,11 +528,13 @@ enum {
   PC_TUNE_COLS_FWD_LATE = 1,      /* forward column pass: spectrum loaded after the transform */
   PC_TUNE_COLS_ADJ_PREFETCH = 2,  /* adjoint column pass: next spectrum column loaded during the transform */
   PC_TUNE_ROWS_INV_PIPE = 3,      /* row-inverse pass: next plane's tile loaded during the transform */
-  PC_TUNE_ROWS_FWD_SMALL = 4,     /* row-forward passes: 4-row tiles instead of 16-row ones */
-  PC_TUNE_ROWS_INV_SMALL = 5,     /* row-inverse passes: 4-row tiles instead of 16-row ones */
+  PC_TUNE_ROWS_FWD_SMALL = 4,     /* row-forward passes: 4-row tiles instead of 16-row ones (8 at 1024 points;
+                                     no difference from 2048 on, where both have 4 or fewer) */
+  PC_TUNE_ROWS_INV_SMALL = 5,     /* row-inverse passes: likewise */
   PC_TUNE_COL_GROUPS = 6,         /* full-grid forward column pass: term groups */
   PC_TUNE_FOURSTEP_L = 7,         /* 1D four-step: inner transform length */
-  PC_TUNE_BATCH_PERSISTENT = 8,   /* batches: one launch per pass (1, the rule) or per length (0) (length 0) */
+  PC_TUNE_BATCH_PERSISTENT = 8,   /* batches, and sectioned plans of several lengths: one launch per pass for the
+                                     lengths up to 512 (1) or per length (0) (length 0) */
   PC_TUNE_SEC_STREAMS = 9,        /* sectioned plans: two launch chains, on two streams (length 0) */
   PC_TUNE_KEEP = 10               /* plans with gradients: keep the windowed spectra within the budget (1, the
                                      rule) or recompute them in every backward (0) (length 0) */

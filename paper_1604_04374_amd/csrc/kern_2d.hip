@@ -1342,7 +1342,7 @@ bool cols_adj_prefetch(int L1) {
 // mostly the fullest's; and the planes, by size and by count.  The constants
 // (us) are fitted to 197 shapes of 64 to 4096 points per column, 1 to 16 terms
 // per factor, 2 to 16 factors and 1 to 8 images, over which the choice is 0.4%
-// off the fastest on average.  (A target of wavefronts, 3000 or 1024 at 256
+// off the fastest on average and 7% at most.  (A target of wavefronts, 3000 or 1024 at 256
 // threads per transform, was 4% off, most where a column has many terms: us
 // per forward, so and here, 4096 x 1024, 16 x 4 terms 565 and 427, 3072 x 256,
 // two images, 4 x 8 terms 162 and 110, 4096 x 128, 6 x 6 terms 65 and 45; a

@@ -851,6 +851,7 @@ struct pc_batch_s {
   // one launch per row pass (column pass) for all the lengths the merged
   // kernels hold code for
   bool merged_rows = false, merged_cols = false;
+  int merge = -1;  // asked for: 1 yes, 0 no (the flag, the tuning table), -1 by rule
   hipGraph_t gf = nullptr, ga = nullptr;
   hipGraphExec_t ef = nullptr, ea = nullptr;
   // Buffers of the calls: the jobs read each instance's input and output
@@ -982,13 +983,18 @@ pc_status finish_merged(Merged& mg, int mkind, std::vector<pc::LaunchSet>& seq, 
   return PC_SUCCESS;
 }
 
-// Whether a sectioned plan's pass over these lengths is merged: where it
-// would otherwise take two launches or more (us per forward, adjoint and
+// Whether a pass over these lengths is merged: where it would otherwise take
+// two launches or more (sectioned plans, us per forward, adjoint and
 // training step, apart -> merged: 2048 x 2048 in sections of 384 and 512 74.5,
 // 61.5 and 161 -> 60.3, 47.2 and 134; four images of 512 x 512, 192 and 256
 // 42.6, 38.2 and 106 -> 30.0, 25.4 and 70; 1024 x 1536, 192 to 384 67, 57 and
 // 140 -> 53, 44 and 110).  A single length keeps its own kernels, whose row
-// tiles are of whole lines at 512 points.
+// tiles are of whole lines at 512 points and whose registers are its own, in a
+// batch once its transforms fill the chip, two wavefronts per SIMD (apart and
+// merged: 300 instances of 128 x 128, 16 terms, 139 and 137, 165 and 166; 128
+// of 256 x 256, 9 terms, 149 and 141, 159 and 148; 64 of 512 x 512 413 and
+// 368, 422 and 395; below, 20 of 384 x 384, 4 terms, 53 and 44, 48 and 44; 4
+// of 512 x 512 39 and 36, 34 and 35).
 bool several_merged(const std::vector<int>& lens) {
   return std::count_if(lens.begin(), lens.end(), [](int L) { return pc::merged_index(L) >= 0; }) > 1;
 }
@@ -1153,10 +1159,15 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
     if (std::find(n2s.begin(), n2s.end(), x.q->p2.N2) == n2s.end()) n2s.push_back(x.q->p2.N2);
     if (std::find(n1s.begin(), n1s.end(), x.q->p2.N1) == n1s.end()) n1s.push_back(x.q->p2.N1);
   }
-  if (gather) {
-    b->merged_rows = several_merged(n2s);
-    b->merged_cols = several_merged(n1s);
+  const int merge = gather ? pc::tune_get(b->tune_key, PC_TUNE_BATCH_PERSISTENT, 0, -1) : b->merge;
+  double row_waves = 0, col_waves = 0;
+  for (const BInst& x : inst) {
+    const pc::Plan2D& q = x.q->p2;
+    if (pc::merged_index(q.N2) >= 0) row_waves += (double)q.N1 / 2 * (double)q.batch_cap * pc::fft_threads(q.N2) / 64;
+    if (pc::merged_index(q.N1) >= 0) col_waves += (double)q.H2 * (double)q.batch_cap * pc::fft_threads(q.N1) / 64;
   }
+  b->merged_rows = merge != 0 && (several_merged(n2s) || (!gather && (merge > 0 || row_waves < 2000)));
+  b->merged_cols = merge != 0 && (several_merged(n1s) || (!gather && (merge > 0 || col_waves < 2000)));
   // a sectioned plan's jobs have one term and one plane
   const int mk_inv = gather ? pc::MK_ROWS_INV1 : pc::MK_ROWS_INV;
   const int mk_cfwd = gather ? (keep ? pc::MK_COLS_KEEP1 : pc::MK_COLS_FWD1) : pc::MK_COLS_FWD;
@@ -2174,7 +2185,7 @@ pc_status pc_batch_create(pc_batch* out, int32_t count, const pc_plan* plans, ui
     for (pc_plan q : b->plans) ds.push_back(q->d);
     b->tune_key = pc::tune_batch_key(ds);
   }
-  b->merged_rows = b->merged_cols = (flags & PC_BATCH_PERSISTENT) || pc::tune_get(b->tune_key, PC_TUNE_BATCH_PERSISTENT, 0, 1) != 0;
+  b->merge = flags & PC_BATCH_PERSISTENT ? 1 : pc::tune_get(b->tune_key, PC_TUNE_BATCH_PERSISTENT, 0, -1);
   b->use_graph = !(flags & PC_BATCH_NO_GRAPH);
   DeviceGuard g(device);
   const size_t tab_bytes = (size_t)4 * count * sizeof(float*);

@@ -106,6 +106,83 @@ def test_forced_variants_in_batches(forced):
         assert per_instance_rel(y[i], ry) <= TOL and per_instance_rel(x[i], rx) <= TOL, p.name
 
 
+@pytest.mark.parametrize("forced", [1, 0])
+def test_forced_variants_in_batches_of_a_launch_per_length(forced):
+    # the per-length variants of a batch, which merged passes do not take, and
+    # graph replays of their launches (eager work between them)
+    import torch
+    import paper_1604_04374_amd as pcm
+    probs = [wl.small_2d(a, b, 2, 2, 1, seed=730 + a + b, kind="hat") for a, b in ((128, 192), (192, 512), (512, 128))]
+    plans = [pcm.Plan(plan_args(p), p.h, batch=p.batch, full_grid=True) for p in probs]
+    key = pcm.tune_batch_key(plans)
+    pcm.tune_set([(key, pcm.TUNE_KNOBS["batch_persistent"], 0, 0)] +
+                 [(key, pcm.TUNE_KNOBS[k], L, forced) for k in SWITCHES for L in (128, 192, 512)])
+    inputs = [torch.from_numpy(p.u).cuda() for p in probs]
+    b = pcm.Batch(plans)
+    pcm.tune_set([])
+    print(f"batch with a launch per length: every variant switch = {forced}", flush=True)
+    first = None
+    for rep in range(3):
+        y = [t.cpu().numpy() for t in b.apply(inputs)]
+        torch.randn(1 << 20, device="cuda").sum().item()
+        x = [t.cpu().numpy() for t in b.apply_adjoint(inputs)]
+        first = first or (y, x)
+        for i, p in enumerate(probs):
+            assert np.array_equal(y[i], first[0][i]) and np.array_equal(x[i], first[1][i]), (rep, p.name)
+    b.destroy()
+    for pl in plans:
+        pl.destroy()
+    for i, p in enumerate(probs):
+        ry, rx = oracle_fft(p)
+        assert per_instance_rel(first[0][i], ry) <= TOL and per_instance_rel(first[1][i], rx) <= TOL, p.name
+
+
+@pytest.mark.parametrize("forced", [1, 0, None])
+def test_sections_of_several_lengths_with_a_launch_per_length(forced):
+    # "batch_persistent" = 0 for a sectioned plan: its passes run per length
+    # again, with the table's variants (None: those of the rules)
+    import torch
+    import paper_1604_04374_amd as pcm
+    p = wl.small_2d(512, 512, 8, 8, 2, seed=740, kind="tile", sig_y_fn=lambda a, b: 0.6 + 4.0 * (a + b) / 1024.0,
+                    sig_x_fn=lambda a, b: 0.6 + 4.0 * (a + b) / 1024.0)
+    u = torch.from_numpy(p.u).cuda()
+
+    def run(entries):
+        pcm.tune_set(entries)
+        try:
+            plan = pcm.Plan(plan_args(p), p.h, batch=p.batch, gradients=True)
+        finally:
+            pcm.tune_set([])
+        with plan:
+            key, secs = pcm.tune_key(plan.desc), plan.sections()
+            plan.set_tracing(True)
+            x = plan.apply_adjoint(u)
+            y = plan.apply_save(u)
+            gu, gs = plan.backward(u, y, use_saved=True)
+            torch.cuda.synchronize()
+            launches = {k: v["launches"] for k, v in plan.trace_stats().items()}
+            return key, secs, launches, [t.cpu().numpy() for t in (y, x, gu, gs)]
+
+    key, secs, merged, ref = run([])
+    cols, rows = {s["m1"] for s in secs}, {s["m2"] for s in secs}
+    assert len(cols) > 1 and len(rows) > 1 and max(cols | rows) <= 512
+    print(f"sections of {sorted(cols)} x {sorted(rows)}, a launch per length (switches {forced})", flush=True)
+    _, _, apart, got = run([(key, pcm.TUNE_KNOBS["batch_persistent"], 0, 0)] +
+                           [(key, pcm.TUNE_KNOBS[k], L, forced) for k in SWITCHES for L in cols | rows
+                            if forced is not None])
+    # adjoint, forward and backward: one column pass each, per length when apart
+    assert merged["cols_fwd"] == 1 and apart["cols_fwd"] == len(cols)
+    assert merged["cols_bwd"] == 1 and apart["cols_bwd"] == len(cols)
+    assert merged["cols_adj"] == 1 and apart["cols_adj"] == len(cols)
+    assert apart["rows_fwd"] == len(rows) * merged["rows_fwd"]
+    ry, rx = oracle_fft(p)
+    assert per_instance_rel(got[0], ry) <= TOL and per_instance_rel(got[1], rx) <= TOL
+    _, rgu = oracle_fft(p, ref[0])
+    # the gradients of both against each other: the same sums in another order
+    assert per_instance_rel(got[2], rgu) <= TOL
+    assert np.linalg.norm(got[3] - ref[3]) <= TOL * np.linalg.norm(ref[3])
+
+
 def _table_entries():
     """The committed table's entries, then every other knob its tuner timed
     (with the value it found fastest)."""
