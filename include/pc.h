@@ -358,15 +358,18 @@ pc_status pc_plan_set_responses(pc_plan plan, const float* h, void* stream);
  *            every other lag.
  *
  * The contraction W T^T runs on the matrix cores in FP32 (partial sums over
- * chunks of 2048 positions added in float64); the m x m factorisations
- * (Cholesky of the Gram matrix, LU with partial pivoting of the node matrix)
- * and the per-lag solves are float64.  Both calls are synchronous: they
- * return once h is written.  Their workspace (and that of
- * pc_wavelet_transform and pc_plan_create_meyer) comes from a device scratch
- * buffer that the library keeps between calls, one per device, grown when a
- * call needs more (the projection of rows lags needs about
- * 4 rows m (n / 2048 + 4) bytes) and held until the process ends; calls on
- * one device that use it run one after another.
+ * chunks of 512 positions added in float64), the Gram matrix beside it in the
+ * same launch; the inverse of the Gram matrix, the LU factorisation with
+ * partial pivoting of the node matrix and the per-lag solves are float64.
+ * Both calls are synchronous: they return once h is written.  Their workspace
+ * (and that of pc_wavelet_transform, for vectors too long for one launch, and
+ * of pc_plan_create_meyer) comes from a device scratch buffer that the library
+ * keeps between calls, one per device, grown when a call needs more and held
+ * until the process ends; calls on one device that use it run one after
+ * another.  The projection of rows lags needs about 8 S (rows + m) m bytes, S
+ * the segments that its positions are split into to fill the chip: one for
+ * many lags, up to n / 64 for few (n = 65536, m = 32: 23595 lags S = 4, 24 MB;
+ * 500 lags S = 128, 17 MB).
  * Errors: INVALID_VALUE (null pointers, sizes or indices out of range,
  * misaligned buffers, a singular Gram or node matrix), OUT_OF_MEMORY, HIP.
  */
@@ -500,8 +503,8 @@ pc_status pc_batch_destroy(pc_batch batch);
 /*
  * Tuning table.  Per transform length, the 2D passes come in variants
  * (spectrum loads before or after the transform, prefetching, pipelined
- * tiles, row tiles of 16 or 4 rows, term groups) and 1D four-step plans have
- * a choice of inner length.  Plans and batches take each choice from rules
+ * tiles, two sizes of row tiles, term groups) and 1D four-step plans have a
+ * choice of inner length.  Plans and batches take each choice from rules
  * (the runtime's occupancy and register figures for the built kernels),
  * unless the tuning table holds a measured choice for their workload.  The
  * package's tuner times the variants on the device and writes the table;
