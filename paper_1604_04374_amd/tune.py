@@ -28,6 +28,13 @@ import numpy as np
 from . import (Batch, Plan, TUNE_KNOBS, load_library, tune_batch_key, tune_key, tune_set, tuning_table_path,
                _device_arch)
 
+# lengths whose blocks share a launch per pass in a batch, and in a sectioned
+# plan with several of them on an axis: their per-length switches then have no
+# effect (include/pc.h PC_TUNE_BATCH_PERSISTENT)
+MERGED_LENGTHS = (64, 96, 128, 192, 256, 384, 512)
+# from here on both sizes of row tiles are the same
+ONE_TILE_LENGTH = 2048
+
 KNOB_VALUES = {"cols_fwd_late": (0, 1), "cols_adj_prefetch": (0, 1), "rows_inv_pipe": (0, 1),
                "rows_fwd_small": (0, 1), "rows_inv_small": (0, 1)}
 
@@ -104,25 +111,38 @@ class Workload:
                 rows.add(int(pl.desc.n1))
         return sorted(cols), sorted(rows), sorted(n1d)
 
-    def candidates(self):
+    def candidates(self, chosen):
+        """Knobs that have an effect, given the choices made so far (read as
+        the caller goes along)."""
         cols, rows, n1d = self.lengths()
-        out = []
+
+        def merges(lengths):
+            several = sum(L in MERGED_LENGTHS for L in lengths) > 1
+            return self.name == "c4" or (several and self.plans[0].info()["path"] == 3)
+
+        mcols, mrows = merges(cols), merges(rows)
+        if mcols or mrows:
+            yield "batch_persistent", 0, (0, 1)
+        if chosen.get(("batch_persistent", 0)) == 0:
+            mcols = mrows = False
         for L in cols:
-            out += [("cols_fwd_late", L, KNOB_VALUES["cols_fwd_late"]),
-                    ("cols_adj_prefetch", L, KNOB_VALUES["cols_adj_prefetch"])]
+            if not (mcols and L in MERGED_LENGTHS):
+                yield "cols_fwd_late", L, KNOB_VALUES["cols_fwd_late"]
+                yield "cols_adj_prefetch", L, KNOB_VALUES["cols_adj_prefetch"]
         for L in rows:
-            out += [(k, L, KNOB_VALUES[k]) for k in ("rows_fwd_small", "rows_inv_small", "rows_inv_pipe")]
-        if self.name == "c4":
-            out += [("batch_persistent", 0, (0, 1))]
+            if not (mrows and L in MERGED_LENGTHS):
+                for k in ("rows_fwd_small", "rows_inv_small"):
+                    if L < ONE_TILE_LENGTH:
+                        yield k, L, KNOB_VALUES[k]
+                yield "rows_inv_pipe", L, KNOB_VALUES["rows_inv_pipe"]
         if self.name == "c5ad":
-            out += [("keep", 0, (0, 1))]
+            yield "keep", 0, (0, 1)
         if self.name == "c3":
             pl = self.plans[0]
             nq = pl.desc.m_cols if pl.desc.w_format == 1 else pl.desc.m
-            out += [("col_groups", int(pl.desc.n0), tuple(g for g in (1, 2, 4, 8, 16) if g <= nq))]
+            yield "col_groups", int(pl.desc.n0), tuple(g for g in (1, 2, 4, 8, 16) if g <= nq)
         for n in n1d:
-            out += [("fourstep_l", n, tuple(l for l in (4096, 6144, 8192) if n % l == 0 and n // l in (2, 4, 8, 16)))]
-        return out
+            yield "fourstep_l", n, tuple(l for l in (4096, 6144, 8192) if n % l == 0 and n // l in (2, 4, 8, 16))
 
     def step(self):
         import torch
@@ -176,7 +196,7 @@ def tune_workload(name, others, steps, margin):
     w.build()
     best = w.time_ms(steps)
     _log(f"[tune] {name}: key {key:#018x}, rule-based step {best:.4f} ms")
-    for knob, L, values in w.candidates():
+    for knob, L, values in w.candidates(chosen):
         # the current choices (rules, or entries kept so far) are the
         # reference: an entry is kept only if one of the values beats it
         tune_set(table())
