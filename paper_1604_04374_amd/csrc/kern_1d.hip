@@ -1108,7 +1108,12 @@ bool fourstep_variant_supported(int L, int R, int P) {
 // terms, classes or pairs are split further.  Measured (5 signals of 24576
 // samples, 9 terms; us per launch at 24 points per thread and one group,
 // split, and split at 12 points): forward 119, 25, 13.4; adjoint 60, 21,
-// 11.9; gradient 60, 29, 11.3 (12 to 36 workgroups before, 108 split).
+// 11.9; gradient 60, 29, 11.3 (12 to 36 workgroups before, 108 split).  Fewer
+// leave units idle, more run a second round (us per forward and adjoint at a
+// target of 128, 256, 512 and 1024: 5 signals of 65536, 17 terms 44 and 50, 32
+// and 40, 36 and 37, 58 and 49; 9 of them 65 and 73, 41 and 52, 38 and 42, 49
+// and 49; 5 of 49152, one of 512 threads resident, 31 and 41, 28 and 35, 39
+// and 40, 39 and 40).
 static int64_t large_target(const Large1D& p) { return p.L / p.P >= 512 ? 256 : 512; }
 
 int fwd1d_large_groups(const Large1D& p, int64_t pairs) {

@@ -1342,11 +1342,12 @@ bool cols_adj_prefetch(int L1) {
 // mostly the fullest's; and the planes, by size and by count.  The constants
 // (us) are fitted to 197 shapes of 64 to 4096 points per column, 1 to 16 terms
 // per factor, 2 to 16 factors and 1 to 8 images, over which the choice is 0.4%
-// off the fastest on average and 7% at most.  (A target of wavefronts, 3000 or 1024 at 256
-// threads per transform, was 4% off, most where a column has many terms: us
-// per forward, so and here, 4096 x 1024, 16 x 4 terms 565 and 427, 3072 x 256,
-// two images, 4 x 8 terms 162 and 110, 4096 x 128, 6 x 6 terms 65 and 45; a
-// target of 4096 columns too: four images of 4096 x 512, 8 x 3 terms.)
+// off the fastest on average and 7% at most (2048 x 2048, 4 x 4 terms: 148,
+// two groups 139).  A target of wavefronts, 3000 or 1024 at 256 threads per
+// transform, was 4% off, most where a column has many terms: us per forward,
+// so and here, 4096 x 1024, 16 x 4 terms 565 and 427, 3072 x 256, two images,
+// 4 x 8 terms 162 and 110, 4096 x 128, 6 x 6 terms 65 and 45; a target of 4096
+// columns was as far off.
 int col_groups_for(int L1, int H2, int64_t batch, int m1, int nq) {
   constexpr int CUS = 256;
   const int P = points_per_thread(L1), T = fft_threads(L1), NF = ffts_per_block(L1), threads = NF * T;
@@ -1388,10 +1389,18 @@ bool cols_leave_room(int L1, int64_t columns) {
 // of its own would, 1 / m1 more work, which costs less than that pass's
 // launch and its round trip of the plane (measured, us per adjoint with the
 // pass and without: 256 x 256, 9 terms 20.1 and 17.5; 1024 x 1024, 16 terms
-// 47.2 and 44.1; 2048 x 2048 132.8 and 126.7).  With one term per slot (dense
-// windows) it doubles the transforms: only where they are too few to fill the
-// chip.
-bool adj_own_fft(int m1, int64_t slots) { return m1 >= 2 || slots <= 4096; }
+// 47.2 and 44.1; 2048 x 2048 132.8 and 126.7), except for two or three terms
+// in many slots of 256 threads (two images of 4096 x 768, 3 x 8 terms 325 and
+// 344; of 3072 x 1024, 2 x 6 terms 209 and 215; one of 4096 x 4096, 2 x 2
+// terms, 4098 slots, 287 and 274; 4 x 4 terms 215 and 212).  With one term per
+// slot (dense windows) it doubles the transforms: only while they are few
+// (512 x 512, 4 terms, 1028 slots 20.2 and 17.5; 1024 x 1024, 8 terms, 4104
+// slots 51.5 and 49.4, 16 terms, 8208 slots 77.4 and 76.4; 2048 x 512, 16
+// terms, 4112 slots 67.6 and 68.2).
+bool adj_own_fft(int L1, int m1, int64_t slots) {
+  if (m1 < 2) return slots <= 4096;
+  return fft_threads(L1) < 256 || m1 > 3 || slots <= 6000;
+}
 
 // Planes side by side (k_rows_inv_side) for a small-tile row-inverse launch
 // of nq windowed planes, or 0: where the planes' groups fit the chip together

@@ -786,7 +786,7 @@ pc_status build_2d(pc_plan p, const float* windows, const float* h, hipStream_t 
   pc::append_col_blocks(bm, 0, cap, H2, N1, nq);
   if ((st = make_set(p, q.adj_cols, pc::KK_COLS_ADJ, N1, std::vector<pc::ColJob>{ca}, bm, (int64_t)cpi * nq, tw1, s)))
     return st;
-  q.adj_own_fft = !q.adj_fused && pc::adj_own_fft(q.dense ? 1 : q.m1, (int64_t)H2 * cap * nq);
+  q.adj_own_fft = !q.adj_fused && pc::adj_own_fft(N1, q.dense ? 1 : q.m1, (int64_t)H2 * cap * nq);
   if (q.adj_own_fft) {
     ca.fft_src = 1;
     if ((st = make_set(p, q.adj_cols_fft, pc::KK_COLS_ADJ, N1, std::vector<pc::ColJob>{ca}, bm, (int64_t)cpi * nq, tw1,
@@ -1352,7 +1352,7 @@ pc_status build_batch(pc_batch b, const float* const* in, float* const* fo, floa
             jf.back().keep_stride = plane * cap;
           }
         } else {
-          const bool own = q.adj_fused || (!gather && pc::adj_own_fft(dense ? 1 : q.m1, adj_slots[c][L1]));
+          const bool own = q.adj_fused || (!gather && pc::adj_own_fft(L1, dense ? 1 : q.m1, adj_slots[c][L1]));
           if (!own) {
             pc::append_col_blocks(bt, (int)jt.size(), cap, q.H2, L1, 1);
             jt.push_back(pc::ColJob{nullptr, q.Tws, nullptr, nullptr, nullptr, 0, 0, q.H2, q.m1, q.m2, dense, 1});

@@ -329,7 +329,7 @@ int col_groups_for(int L1, int H2, int64_t batch, int m1, int nq);
 bool cols_leave_room(int L1, int64_t columns);
 // Whether the adjoint column pass of a plan of several terms transforms its
 // input itself, in every column slot of m1 terms, instead of a pass before it.
-bool adj_own_fft(int m1, int64_t slots);
+bool adj_own_fft(int L1, int m1, int64_t slots);
 // Planes a small-tile row-inverse launch transforms side by side (0: in turn)
 int rows_inv_side(int L2, int nq, int64_t blocks);
 

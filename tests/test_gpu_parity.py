@@ -335,3 +335,14 @@ GROUPS = [(4096, 64, 6, 6, 1), (3072, 64, 2, 7, 1), (128, 128, 3, 11, 1), (2048,
 def test_term_groups_of_the_forward(n1, n2, m1, m2, batch):
     p = wl.small_2d(n1, n2, m1, m2, batch, seed=93, kind="hat")
     _check(p)
+
+
+# long columns on both sides of the adjoint's own transform of V: many slots of
+# two and three terms, of four, and few slots
+OWN = [(4096, 768, 2, 8, 2), (3072, 1024, 3, 6, 2), (3072, 768, 4, 8, 2), (4096, 64, 2, 2, 1)]
+
+
+@pytest.mark.parametrize("n1,n2,m1,m2,batch", OWN)
+def test_adjoint_of_long_columns(n1, n2, m1, m2, batch):
+    p = wl.small_2d(n1, n2, m1, m2, batch, seed=94, kind="hat")
+    _check(p)
