@@ -539,18 +539,18 @@ int small1d_groups(int L, int m, int64_t pairs) {
 // 1024 samples, 64 terms 192 and 170, 2600 of them 154 and 171; 2000 of 2048,
 // 32 terms 107 and 94, 1300 of them 88 and 94, 4096 of them 198 and 188, of 16
 // terms the same; 16384 of 256, 16 terms 41.3 and 37.6, 8192 of them 26 and
-// 35; a pair per workgroup, 774 of 2048, 32 terms 66 and 50, 520 of them, 64
-// terms 84 and 91, 366 of them, 8 terms 17.9 and 17.1, 16 terms 24.4 and 27.4;
-// 640 of 1024, 64 terms 54.6 and 49.2, 8 terms 12.2 and 12.7; 1600 of them, 64
-// terms 109 and 97, 16 terms 33 and 34).  At 512 points 8 per thread win
-// throughout.
+// 35, 14297 of 24 terms 57 and 52; a pair per workgroup, 774 of 2048, 32 terms
+// 66 and 50, 520 of them, 64 terms 84 and 91, 366 of them, 8 terms 17.9 and
+// 17.1, 16 terms 24.4 and 27.4; 640 of 1024, 64 terms 54.6 and 49.2, 8 terms
+// 12.2 and 12.7; 1600 of them, 64 terms 109 and 97, 16 terms 33 and 34).  At
+// 512 points 8 per thread win throughout.
 template <int L>
 static bool adj_wide(int m, int64_t pairs, bool& split) {
   constexpr int NF = 256 * 16 / L;
   const int64_t slots = (pairs + NF - 1) / NF;
   split = slots < 256;
   if (!split)
-    return (slots <= 512 && slots >= (L == 256 ? 480 : 384)) ||
+    return (slots <= 512 && slots >= (L == 256 ? 416 : 384)) ||
            (L == 2048 && m >= 32 && slots <= 1024 && slots >= 960);
   if (L == 1024) return (m >= 16 && pairs > 256 && pairs <= 512) || (m >= 32 && pairs > 768);
   if (L == 2048) return m >= 8 && pairs > (m <= 12 ? 176 : 256) && (m < 32 || pairs >= 384);

@@ -88,8 +88,8 @@ def test_1d_batches_of_many_signals(n, m, deg, batch):
     # adjoints at 16 points per thread: a pair per slot (the last workgroup
     # ragged, the fewest and the most workgroups), and a pair per workgroup with
     # slots past the last term, at the edges of the calls that take them
-    (256, 3, 1, 15330), (256, 2, 1, 16384), (1024, 3, 1, 3067), (1024, 4, 1, 4096), (2048, 2, 1, 1534),
-    (2048, 3, 1, 2048), (1024, 17, 3, 513), (1024, 16, 3, 1024), (1024, 33, 3, 1537), (1024, 32, 3, 2039),
+    (256, 3, 1, 13283), (256, 3, 1, 15330), (256, 2, 1, 16384), (1024, 3, 1, 3067), (1024, 4, 1, 4096),
+    (2048, 2, 1, 1534), (2048, 3, 1, 2048), (1024, 17, 3, 513), (1024, 16, 3, 1024), (1024, 33, 3, 1537), (1024, 32, 3, 2039),
     (2048, 9, 1, 513), (2048, 32, 3, 767), (2048, 33, 3, 1021),
 ])
 def test_1d_adjoints_that_fill_wide_workgroups(n, m, deg, batch):
