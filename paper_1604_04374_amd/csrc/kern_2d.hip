@@ -1205,6 +1205,7 @@ void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int
   if ((block_rows > 0 ? block_rows : row_block_rows(L2, small)) >= 16 || n_img < 1) return;  // whole lines
   const int64_t per_img = (int64_t)(bm.size() - from) / n_img;
   std::vector<BlockRef> img(per_img);
+  const bool planes = std::any_of(bm.begin() + from, bm.end(), [](const BlockRef& r) { return r.q > 0; });
   for (size_t i0 = from; i0 < bm.size(); i0 += per_img) {
     // position p runs on XCD (i0 + p) mod 8: each XCD takes a run of blocks
     int64_t next = 0;
@@ -1212,7 +1213,7 @@ void xcd_major_blocks(std::vector<BlockRef>& bm, size_t from, int64_t n_img, int
       const int64_t p0 = ((x - (int64_t)i0) % XCDS + XCDS) % XCDS;
       const int64_t n = p0 < per_img ? (per_img - p0 + XCDS - 1) / XCDS : 0;
       const auto run = bm.begin() + i0 + next;
-      std::stable_sort(run, run + n, [](const BlockRef& a, const BlockRef& b) { return a.q < b.q; });
+      if (planes) std::stable_sort(run, run + n, [](const BlockRef& a, const BlockRef& b) { return a.q < b.q; });
       for (int64_t p = p0; p < per_img; p += XCDS) img[p] = bm[i0 + next++];
     }
     std::copy(img.begin(), img.end(), bm.begin() + i0);
